@@ -9,7 +9,10 @@
 //   index       an exact inverted index: (f, mode value) -> ascending list of
 //               seeds j, as a hash table of run extents over the sorted
 //               (f, value, j) triples.
-//   assign      one wavefront per row probes its F (f, sig[f]) pairs, gathers
+//   bit planes  (k * F <= SIG_DENSE_MAX, k <= SIG_BITS_K) per (f, mode value) a
+//               bit mask of its seeds; a row adds the masks of its F values
+//               into bit-sliced counters of all seeds (k_sig_bits).
+//   assign      otherwise one wavefront per row probes its F (f, sig[f]) pairs, gathers
 //               the matching seeds in LDS, sorts them and takes the longest
 //               run (lowest j on ties); a row whose matches overflow the LDS
 //               list is compared against every mode instead.  Rows with no
@@ -28,6 +31,8 @@ size_t sse_blk_words(int64_t n);
 constexpr int SG_CAP = 2048;  // matched seeds held in LDS per row
 // k * F up to which every row is compared against every mode directly
 constexpr int64_t SIG_DENSE_MAX = 1 << 20;
+// ... by bit planes up to this k (masks of k * F rows of k bits)
+constexpr int SIG_BITS_K = 4096;
 
 __device__ __forceinline__ int seed_of(const uint32_t* __restrict__ so, int k, uint32_t pos) {
   int lo = 0, hi = k;  // so[lo] <= pos < so[hi]
@@ -315,6 +320,339 @@ __global__ __launch_bounds__(256) void k_sig_dense(const uint32_t* __restrict__ 
   }
 }
 
+
+// ---- match counts as bit planes
+//
+// Every distinct (position f, mode value v) gets a bit mask over the seeds
+// that hold v at f; a row's counts against all seeds are then the sum of the
+// masks of its F (f, value) pairs.  GL lanes own a row, each with four mask
+// words (128 seeds), and add the masks into NP bit planes (plane b holds bit
+// b of every seed's count) with carry-save adders: about 2.5 vector
+// operations per mask word, 32 seeds each, where a comparison with every mode
+// takes two per seed.  The largest count is read off the planes from the top
+// (the seeds that still tie are a mask), the lowest seed of the tie wins.
+//
+// What bounds it: half the time is the table probes (one 16-byte load per
+// position from a table of a few MB), half the mask reads (16 * GL bytes per
+// position that any mode shares with the row, 193 of 256 on the sets workload:
+// 49 GB per 10^6 rows at about 20 TB/s, mostly from L2).  Figures at
+// sig_use_bits.
+constexpr int SB_VW = 4;        // mask words per lane
+constexpr int SB_THREADS = 128;
+constexpr int SB_STEP = 8;      // masks added per step
+
+constexpr int BI_THREADS = 512;
+constexpr int BI_BUCKET = 4;    // entries of a bucket: one 16-byte load
+constexpr int BI_BITS_MAX = 15; // buckets per position: at most 2^15
+constexpr int BI_SEEDS = 6;     // hashes tried per bucket count
+
+// A bijection of 32-bit words per seed, so (bucket, remaining bits) names a
+// value exactly.
+GEEK_D uint32_t bits_hash(uint32_t v, uint32_t seed) { return fmix32(v ^ (seed * 0x9E3779B9u)); }
+
+// How position f's values are found: bucket = hash & bmask at table[first +
+// bucket], mask rows from row0; bmask 0: no hash tried kept every bucket within
+// BI_BUCKET entries, the value is searched in runs[].
+struct BitsPos {
+  uint32_t first, bmask, seed, row0;
+};
+
+// One workgroup per position f: the seeds sorted by (mode value, seed) in LDS
+// and written to keys[f][0..k); the number of distinct values and a hash that
+// puts at most BI_BUCKET of them into a bucket, with the fewest buckets of a
+// mean load of at most 0.6 (one load then finds a value or its absence: with
+// linear probing the longest probe of a wavefront's 1,024 set the time).
+__global__ __launch_bounds__(BI_THREADS) void k_bits_sort(const uint32_t* __restrict__ modes, int k, int F, int P,
+                                                          int bits_cap, unsigned long long* __restrict__ keys,
+                                                          uint32_t* __restrict__ distinct, BitsPos* __restrict__ pos) {
+  extern __shared__ __attribute__((aligned(16))) unsigned long long bi_key[];  // [P], P = pow2 >= k
+  __shared__ uint32_t fill[(1 << BI_BITS_MAX) / 4];  // byte counts of the buckets
+  __shared__ uint32_t total, over;
+  const uint32_t f = blockIdx.x;
+  if (threadIdx.x == 0) total = 0u;
+  for (int q = threadIdx.x; q < P; q += BI_THREADS)
+    bi_key[q] = q < k ? ((unsigned long long)modes[(int64_t)q * F + f] << 32) | (uint32_t)q : ~0ull;
+  __syncthreads();
+  for (int kk = 2; kk <= P; kk <<= 1)
+    for (int jj = kk >> 1; jj > 0; jj >>= 1) {
+      for (int q = threadIdx.x; q < P / 2; q += BI_THREADS) {
+        const int lo = 2 * q - (q & (jj - 1)), hi = lo + jj;
+        const unsigned long long x = bi_key[lo], y = bi_key[hi];
+        if ((x > y) == ((lo & kk) == 0)) {
+          bi_key[lo] = y;
+          bi_key[hi] = x;
+        }
+      }
+      __syncthreads();
+    }
+  uint32_t heads = 0;
+  for (int q = threadIdx.x; q < k; q += BI_THREADS) {
+    heads += q == 0 || (bi_key[q] >> 32) != (bi_key[q - 1] >> 32);
+    keys[(size_t)f * k + q] = bi_key[q];
+  }
+  if (heads) atomicAdd(&total, heads);
+  __syncthreads();
+  const uint32_t D = total;
+  int bits = 2;
+  while (3u << bits < 5u * D || (1u << bits) <= D) ++bits;
+  uint32_t bmask = 0u, seed = 0u;
+  for (; bits <= bits_cap && bmask == 0u; ++bits)
+    for (uint32_t sd = 0; sd < BI_SEEDS; ++sd) {
+      const uint32_t bm = (1u << bits) - 1u;
+      for (uint32_t q = threadIdx.x; q <= bm / 4u; q += BI_THREADS) fill[q] = 0u;
+      if (threadIdx.x == 0) over = 0u;
+      __syncthreads();
+      for (int q = threadIdx.x; q < k; q += BI_THREADS)
+        if (q == 0 || (bi_key[q] >> 32) != (bi_key[q - 1] >> 32)) {
+          const uint32_t h = bits_hash((uint32_t)(bi_key[q] >> 32), sd) & bm, sh = 8u * (h & 3u);
+          if ((atomicAdd(&fill[h >> 2], 1u << sh) >> sh & 255u) >= (uint32_t)BI_BUCKET) over = 1u;
+        }
+      __syncthreads();
+      const bool ok = over == 0u;
+      __syncthreads();
+      if (ok) {
+        bmask = bm;
+        seed = sd;
+        break;
+      }
+    }
+  if (threadIdx.x == 0) {
+    distinct[f] = D;
+    pos[f] = BitsPos{0u, bmask, seed, 0u};
+  }
+}
+
+// One workgroup per position f: the first bucket and mask row (tables and rows
+// of all positions lie without gaps; row 0 is all zeros), the bucket entries,
+// runs[f][r] = {value, mask row} of the r-th distinct value, and the masks.  An
+// entry holds the hash above its bucket bits and, below them, 1 + r.
+__global__ __launch_bounds__(BI_THREADS) void k_bits_fill(const unsigned long long* __restrict__ keys, int k,
+                                                          const uint32_t* __restrict__ distinct,
+                                                          const BitsPos* __restrict__ pos_in,
+                                                          BitsPos* __restrict__ pos, uint32_t* __restrict__ table,
+                                                          unsigned long long* __restrict__ runs,
+                                                          uint32_t* __restrict__ masks, int row_words) {
+  __shared__ uint32_t base[2];  // distinct values and buckets of the positions before f
+  __shared__ uint32_t wsum[BI_THREADS / 64];
+  const uint32_t f = blockIdx.x;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (threadIdx.x < 2) base[threadIdx.x] = 0u;
+  __syncthreads();
+  for (uint32_t p = threadIdx.x; p < f; p += BI_THREADS) {
+    atomicAdd(&base[0], distinct[p]);
+    atomicAdd(&base[1], pos_in[p].bmask + 1u);
+  }
+  if (f == 0)
+    for (int q = threadIdx.x; q < row_words; q += BI_THREADS) masks[q] = 0u;
+  const unsigned long long* kf = keys + (size_t)f * k;
+  // rank of an item's value among the distinct ones: thread t owns the items
+  // t per .. t per + per - 1
+  const int per = (k + BI_THREADS - 1) / BI_THREADS, q0 = threadIdx.x * per;
+  uint32_t heads = 0;
+  for (int q = q0; q < q0 + per && q < k; ++q) heads += q == 0 || (kf[q] >> 32) != (kf[q - 1] >> 32);
+  uint32_t incl = heads;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(incl, o);
+    if (lane >= o) incl += y;
+  }
+  if (lane == 63) wsum[wv] = incl;
+  __syncthreads();
+  uint32_t rank = incl - heads;
+  for (int w = 0; w < wv; ++w) rank += wsum[w];
+  const BitsPos p = pos_in[f];
+  const uint32_t D = distinct[f], row0 = base[0] + 1u;
+  if (threadIdx.x == 0) pos[f] = BitsPos{base[1], p.bmask, p.seed, row0};
+  uint32_t* tf = table + (size_t)base[1] * BI_BUCKET;
+  uint32_t* mf = masks + (size_t)row0 * row_words;
+  for (uint32_t q = threadIdx.x; q < (p.bmask + 1u) * BI_BUCKET; q += BI_THREADS) tf[q] = 0u;
+  for (uint32_t q = threadIdx.x; q < D * (uint32_t)row_words; q += BI_THREADS) mf[q] = 0u;
+  __syncthreads();  // the atomics below follow the workgroup's own stores
+  for (int q = q0; q < q0 + per && q < k; ++q) {
+    const uint32_t v = (uint32_t)(kf[q] >> 32), j = (uint32_t)kf[q];
+    if (q == 0 || (uint32_t)(kf[q - 1] >> 32) != v) {
+      if (p.bmask) {
+        const uint32_t h = bits_hash(v, p.seed), e = (h & ~p.bmask) | (rank + 1u);
+        uint32_t* b = tf + (size_t)(h & p.bmask) * BI_BUCKET;
+        while (atomicCAS(b, 0u, e) != 0u) ++b;  // at most BI_BUCKET values per bucket (k_bits_sort)
+      }
+      runs[(size_t)f * k + rank] = ((unsigned long long)v << 32) | (row0 + rank);
+      ++rank;
+    }
+    atomicOr(&mf[(size_t)(rank - 1u) * row_words + (j >> 5)], 1u << (j & 31));
+  }
+}
+
+// Mask row of value v at a position without a hash: binary search, 0 if absent.
+GEEK_D uint32_t bits_search(const unsigned long long* __restrict__ runs, uint32_t D, uint32_t v) {
+  uint32_t lo = 0, hi = D;
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if ((uint32_t)(runs[mid] >> 32) < v) lo = mid + 1u; else hi = mid;
+  }
+  return lo < D && (uint32_t)(runs[lo] >> 32) == v ? (uint32_t)runs[lo] : 0u;
+}
+
+GEEK_D void csa(uint32_t& hi, uint32_t& lo, uint32_t a, uint32_t b, uint32_t c) {
+  hi = (a & b) | (c & (a ^ b));
+  lo = a ^ b ^ c;
+}
+
+template <int GL, int NP>
+__global__ __launch_bounds__(SB_THREADS) void k_sig_bits(const uint32_t* __restrict__ S, int64_t lds, int F,
+                                                         int64_t n, int k,
+                                                         const uint4* __restrict__ table,
+                                                         const BitsPos* __restrict__ tpos,
+                                                         const unsigned long long* __restrict__ runs,
+                                                         const uint32_t* __restrict__ distinct,
+                                                         const uint32_t* __restrict__ masks,
+                                                         int32_t* __restrict__ assign, double* __restrict__ dist,
+                                                         unsigned long long* __restrict__ ctr) {
+  constexpr int R = 64 / GL;  // rows per wavefront
+  constexpr int U = R >= 8 ? 2 : 4;  // words of a row per lane and step
+  extern __shared__ __attribute__((aligned(16))) uint32_t sb_list[];
+  const int fpad = (F + SB_STEP - 1) / SB_STEP * SB_STEP + 2 * SB_STEP;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t* lst = sb_list + (size_t)wave * R * fpad;
+  const int g = lane / GL, sub = lane % GL;
+  const uint32_t row_bytes = GL * SB_VW * 4;
+  const int64_t tiles = (n + R - 1) / R, waves = (int64_t)gridDim.x * (SB_THREADS / 64);
+  unsigned long long rows_done = 0;
+  for (int64_t t = (int64_t)blockIdx.x * (SB_THREADS / 64) + wave; t < tiles; t += waves) {
+    const int64_t i0 = t * R;
+    // mask rows of the positions that share a value with some mode: the words
+    // of all R rows, then all their probes, are in flight together
+    int cnt[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) cnt[r] = 0;
+    for (int f0 = 0; f0 < F; f0 += 64 * U) {
+      uint32_t v[R][U];
+      uint4 e[R][U];
+      BitsPos tp[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        tp[u] = f0 + u * 64 + lane < F ? tpos[f0 + u * 64 + lane] : BitsPos{0u, 1u, 0u, 0u};
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int f = f0 + u * 64 + lane;
+          v[r][u] = f < F && i0 + r < n ? S[(i0 + r) * lds + f] : 0u;
+        }
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          v[r][u] = bits_hash(v[r][u], tp[u].seed);
+          e[r][u] = table[tp[u].first + (v[r][u] & tp[u].bmask)];
+        }
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int f = f0 + u * 64 + lane;
+          const uint32_t bm = tp[u].bmask, q = v[r][u] & ~bm;
+          const uint32_t ex[4] = {e[r][u].x ^ q, e[r][u].y ^ q, e[r][u].z ^ q, e[r][u].w ^ q};
+          uint32_t rk = 0u;  // 1 + the value's rank; the entry's other bits agree
+#pragma unroll
+          for (int z = 0; z < 4; ++z) rk = ex[z] - 1u < bm ? ex[z] : rk;
+          uint32_t row = rk ? tp[u].row0 + rk - 1u : 0u;
+          const bool live = f < F && i0 + r < n;
+          if (live && bm == 0u) row = bits_search(runs + (size_t)f * k, distinct[f], S[(i0 + r) * lds + f]);
+          const bool some = live && row != 0u;
+          const uint64_t hit = __ballot(some);
+          if (some) lst[r * fpad + cnt[r] + __popcll(hit & ((1ull << lane) - 1ull))] = row;
+          cnt[r] += __popcll(hit);
+        }
+    }
+    int most = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      // padded with the zero mask to whole steps
+      if (lane < 2 * SB_STEP) lst[r * fpad + cnt[r] + lane] = 0u;
+      if (g == r) most = cnt[r];
+    }
+    int steps = (most + SB_STEP - 1) / SB_STEP;  // per row
+    int all = steps;
+#pragma unroll
+    for (int o = GL; o < 64; o <<= 1) all = max(all, __shfl_xor(all, o));
+    uint32_t pl[NP][SB_VW];
+#pragma unroll
+    for (int b = 0; b < NP; ++b)
+#pragma unroll
+      for (int w = 0; w < SB_VW; ++w) pl[b][w] = 0u;
+    const uint32_t* my = lst + g * fpad;
+    const char* mbase = reinterpret_cast<const char*>(masks) + sub * (SB_VW * 4);
+    __builtin_amdgcn_wave_barrier();
+    uint4 x[SB_STEP];
+    {
+#pragma unroll
+      for (int u = 0; u < SB_STEP; ++u)
+        x[u] = *reinterpret_cast<const uint4*>(mbase + (uint64_t)(steps > 0 ? my[u] : 0u) * row_bytes);
+    }
+    for (int c = 0; c < all; ++c) {
+      uint4 y[SB_STEP];
+      const bool more = c + 1 < steps;
+#pragma unroll
+      for (int u = 0; u < SB_STEP; ++u)
+        y[u] = *reinterpret_cast<const uint4*>(mbase + (uint64_t)(more ? my[(c + 1) * SB_STEP + u] : 0u) * row_bytes);
+#pragma unroll
+      for (int w = 0; w < SB_VW; ++w) {
+        uint32_t m[SB_STEP];
+#pragma unroll
+        for (int u = 0; u < SB_STEP; ++u) m[u] = w == 0 ? x[u].x : w == 1 ? x[u].y : w == 2 ? x[u].z : x[u].w;
+        uint32_t t2a, t2b, t2c, t2d, t4a, t4b, t8;
+        csa(t2a, pl[0][w], pl[0][w], m[0], m[1]);
+        csa(t2b, pl[0][w], pl[0][w], m[2], m[3]);
+        csa(t4a, pl[1][w], pl[1][w], t2a, t2b);
+        csa(t2c, pl[0][w], pl[0][w], m[4], m[5]);
+        csa(t2d, pl[0][w], pl[0][w], m[6], m[7]);
+        csa(t4b, pl[1][w], pl[1][w], t2c, t2d);
+        csa(t8, pl[2][w], pl[2][w], t4a, t4b);
+#pragma unroll
+        for (int b = 3; b < NP; ++b) {
+          const uint32_t c2 = pl[b][w] & t8;
+          pl[b][w] ^= t8;
+          t8 = c2;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < SB_STEP; ++u) x[u] = y[u];
+    }
+    // largest count: seeds that tie on the bits read so far
+    uint32_t cand[SB_VW];
+#pragma unroll
+    for (int w = 0; w < SB_VW; ++w) {
+      const int j0 = (sub * SB_VW + w) * 32;
+      cand[w] = j0 + 32 <= k ? ~0u : j0 >= k ? 0u : (1u << (k - j0)) - 1u;
+    }
+    const uint64_t gmask = (GL == 64 ? ~0ull : ((1ull << (GL & 63)) - 1ull) << (g * GL));
+    uint32_t best = 0;
+#pragma unroll
+    for (int b = NP - 1; b >= 0; --b) {
+      uint32_t q[SB_VW], any = 0;
+#pragma unroll
+      for (int w = 0; w < SB_VW; ++w) {
+        q[w] = cand[w] & pl[b][w];
+        any |= q[w];
+      }
+      const bool some = (__ballot(any != 0u) & gmask) != 0ull;
+      if (some) best |= 1u << b;
+#pragma unroll
+      for (int w = 0; w < SB_VW; ++w) cand[w] = some ? q[w] : cand[w];
+    }
+    const uint64_t holders = __ballot((cand[0] | cand[1] | cand[2] | cand[3]) != 0u) & gmask;
+    if (holders != 0ull && lane == __ffsll((unsigned long long)holders) - 1 && i0 + g < n) {
+      const int w = cand[0] ? 0 : cand[1] ? 1 : cand[2] ? 2 : 3;
+      const uint32_t cw = cand[0] ? cand[0] : cand[1] ? cand[1] : cand[2] ? cand[2] : cand[3];
+      assign[i0 + g] = (sub * SB_VW + w) * 32 + __ffs(cw) - 1;
+      dist[i0 + g] = 1.0 - (double)best / (double)F;
+    }
+    rows_done += (unsigned long long)(n - i0 < R ? n - i0 : R);
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (lane == 0 && rows_done) atomicAdd(ctr + 2, rows_done);
+}
+
 __global__ void k_zero_words(uint32_t* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -324,6 +662,26 @@ __global__ void k_copy_ctr(const unsigned long long* a, unsigned long long* b) {
 }
 
 // ---------------------------------------------------------------- host side
+// Lanes per row of the bit-plane counts (a power of two of at least 8 and
+// k / 128; rows of more than 512 positions take at least 16, so that the
+// match lists of a wavefront's rows fit in LDS).
+static int sig_lanes(int F, int k) {
+  int gl = F > 512 ? 16 : 8;
+  while (gl * 32 * SB_VW < k) gl *= 2;
+  return gl;
+}
+
+// Whether rows are counted by bit planes where every row meets every mode
+// (k * F <= SIG_DENSE_MAX).  Measured per call against k_sig_dense's path, which
+// also sorted an index it did not read (us, F = 256): n = 1,000, k = 16: 277
+// against 517; n = 10^5, k = 16: 477 against 590, k = 1,000: 693 against 3,683;
+// 10^6 sets, k = 2,000: the counting alone 4.35 ms against 33 ms.  The bit
+// planes won at every size tried; above SIG_BITS_K seeds the masks outgrow
+// half a gigabyte and the direct comparison stays.
+static bool sig_use_bits(const geek_assign_job& J) {
+  return (int64_t)J.k * J.F <= SIG_DENSE_MAX && J.k <= SIG_BITS_K;
+}
+
 struct SigWs {
   int64_t NI;  // mode items: members * F
   uint32_t *val, *seg, *val2, *seg2;
@@ -332,12 +690,23 @@ struct SigWs {
   uint32_t *dense, *small, *rtmp;
   double *dist, *sse_blk;
   uint32_t hmask;
+  // bit-plane counts (sig_use_bits): per-position slot tables and the masks
+  unsigned long long *btab, *bkeys, *runs;
+  BitsPos *bpos, *tpos;
+  uint32_t *masks, *distinct;
+  int row_words, bits_cap;
 };
 
 static uint32_t pow2_at_least(uint64_t v) {
   uint32_t p = 1;
   while (p < v && p < (1u << 31)) p <<= 1;
   return p;
+}
+
+static int bits_of(uint64_t v) {
+  int b = 0;
+  while (b < 32 && (v >> b)) ++b;
+  return b;
 }
 
 static size_t carve_sig(const geek_assign_job& J, void* ws, SigWs& W) {
@@ -359,8 +728,19 @@ static size_t carve_sig(const geek_assign_job& J, void* ws, SigWs& W) {
   W.wf2 = c.take<uint32_t>(KI + 1);
   const uint32_t HS = pow2_at_least(2 * (uint64_t)KI + 2);
   W.hmask = HS - 1;
-  W.hkey = c.take<unsigned long long>(HS);
-  W.hval = c.take<unsigned long long>(HS);
+  const bool bits = sig_use_bits(J), index = KI > SIG_DENSE_MAX;
+  W.hkey = c.take<unsigned long long>(index ? HS : 0);
+  W.hval = c.take<unsigned long long>(index ? HS : 0);
+  W.row_words = sig_lanes(J.F, J.k) * SB_VW;
+  // at most 2^bits_cap buckets per position (mean load 1/8 or less)
+  W.bits_cap = std::min(BI_BITS_MAX, bits_of((uint64_t)J.k) + 3);
+  W.btab = c.take<unsigned long long>(bits ? ((size_t)F << W.bits_cap) * BI_BUCKET / 2 : 0);
+  W.bkeys = c.take<unsigned long long>(bits ? KI : 0);
+  W.runs = c.take<unsigned long long>(bits ? KI : 0);
+  W.bpos = c.take<BitsPos>(bits ? F : 0);
+  W.tpos = c.take<BitsPos>(bits ? F : 0);
+  W.distinct = c.take<uint32_t>(bits ? F : 0);
+  W.masks = c.take<uint32_t>(bits ? (size_t)(KI + 1) * W.row_words : 0);
   W.ctr = c.take<unsigned long long>(4);
   W.dense = c.take<uint32_t>(J.n + 1);
   W.small = c.take<uint32_t>(16);
@@ -373,12 +753,6 @@ static size_t carve_sig(const geek_assign_job& J, void* ws, SigWs& W) {
 size_t assign_sig_ws(const geek_assign_job& J) {
   SigWs W;
   return carve_sig(J, nullptr, W);
-}
-
-static int bits_of(uint64_t v) {
-  int b = 0;
-  while (b < 32 && (v >> b)) ++b;
-  return b;
 }
 
 int32_t modes_run(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32_t* so, const uint32_t* sm, int k,
@@ -440,39 +814,56 @@ int32_t assign_sig(const geek_assign_job& J, void* ws, size_t ws_bytes, int32_t*
   hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, W.small, 16);
   hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(W.ctr), 8);
   modes_run(J.sig, F, F, J.n, J.seed_offsets, J.seed_members, k, NC, J.modes, W, st, s);
-  // inverted index over (f, mode value) -> seeds
   const int64_t KI = (int64_t)k * F;
-  hipLaunchKernelGGL(k_index_items, dim3(ceil_div(KI, 256)), dim3(256), 0, s, J.modes, k, F, W.wj, W.wv, W.wf);
-  int words[12], shifts[12], np = 0;
-  for (int sh = 0; sh < bits_of((uint64_t)k - 1); sh += 8) {
-    words[np] = 0;
-    shifts[np++] = sh;
+  const bool bits = sig_use_bits(J), index = KI > SIG_DENSE_MAX;
+  const uint32_t *sj = nullptr, *sv = nullptr, *sf = nullptr;
+  if (index) {  // seeds by (f, mode value)
+    hipLaunchKernelGGL(k_index_items, dim3(ceil_div(KI, 256)), dim3(256), 0, s, J.modes, k, F, W.wj, W.wv, W.wf);
+    int words[12], shifts[12], np = 0;
+    for (int sh = 0; sh < bits_of((uint64_t)k - 1); sh += 8) {
+      words[np] = 0;
+      shifts[np++] = sh;
+    }
+    for (int sh = 0; sh < 32; sh += 8) {
+      words[np] = 1;
+      shifts[np++] = sh;
+    }
+    for (int sh = 0; sh < bits_of((uint64_t)F - 1); sh += 8) {
+      words[np] = 2;
+      shifts[np++] = sh;
+    }
+    RsView A{{W.wj, W.wv, W.wf, nullptr}, nullptr}, B{{W.wj2, W.wv2, W.wf2, nullptr}, nullptr};
+    const int alt = radix_sort(A, B, 3, KI, words, shifts, np, W.rtmp, s);
+    sj = alt ? W.wj2 : W.wj;
+    sv = alt ? W.wv2 : W.wv;
+    sf = alt ? W.wf2 : W.wf;
   }
-  for (int sh = 0; sh < 32; sh += 8) {
-    words[np] = 1;
-    shifts[np++] = sh;
-  }
-  for (int sh = 0; sh < bits_of((uint64_t)F - 1); sh += 8) {
-    words[np] = 2;
-    shifts[np++] = sh;
-  }
-  RsView A{{W.wj, W.wv, W.wf, nullptr}, nullptr}, B{{W.wj2, W.wv2, W.wf2, nullptr}, nullptr};
-  const int alt = radix_sort(A, B, 3, KI, words, shifts, np, W.rtmp, s);
-  const uint32_t* sj = alt ? W.wj2 : W.wj;
-  const uint32_t* sv = alt ? W.wv2 : W.wv;
-  const uint32_t* sf = alt ? W.wf2 : W.wf;
-  hipLaunchKernelGGL(k_fill_u64, dim3(ceil_div((int64_t)W.hmask + 1, 256)), dim3(256), 0, s, W.hkey,
-                     (int64_t)W.hmask + 1, ~0ull);
-  hipLaunchKernelGGL(k_index_insert, dim3(ceil_div(KI, 256)), dim3(256), 0, s, sv, sf, KI, W.hkey, W.hval,
-                     W.hmask);
-  prof_begin(GEEK_PROF_ASSIGN_SCAN, s);
   const int dgrid = (int)std::max<int64_t>(1, std::min<int64_t>(2048, ceil_div(J.n, 256)));
-  if ((int64_t)k * F <= SIG_DENSE_MAX) {
-    // few seeds: comparing against every mode costs less than building and
-    // sorting per-row match lists
+  if (bits) {
+    const int P = (int)pow2_at_least((uint64_t)k);
+    hipLaunchKernelGGL(k_bits_sort, dim3(F), dim3(BI_THREADS), sizeof(unsigned long long) * P, s, J.modes, k, F, P,
+                       W.bits_cap, W.bkeys, W.distinct, W.bpos);
+    hipLaunchKernelGGL(k_bits_fill, dim3(F), dim3(BI_THREADS), 0, s, W.bkeys, k, W.distinct, W.bpos, W.tpos,
+                       reinterpret_cast<uint32_t*>(W.btab), W.runs, W.masks, W.row_words);
+    prof_begin(GEEK_PROF_ASSIGN_SCAN, s);
+    const int gl = W.row_words / SB_VW, R = 64 / gl, per_block = R * (SB_THREADS / 64);
+    const int fpad = (F + SB_STEP - 1) / SB_STEP * SB_STEP + 2 * SB_STEP;
+    const size_t shm = sizeof(uint32_t) * (size_t)per_block * fpad;
+    const dim3 grid((unsigned)std::min<int64_t>(8192, (J.n + per_block - 1) / per_block));
+    const auto kern = F < 512 ? (gl == 8 ? k_sig_bits<8, 9> : gl == 16 ? k_sig_bits<16, 9> : k_sig_bits<32, 9>)
+                              : (gl == 8 ? k_sig_bits<8, 11> : gl == 16 ? k_sig_bits<16, 11> : k_sig_bits<32, 11>);
+    hipLaunchKernelGGL(kern, grid, dim3(SB_THREADS), shm, s, J.sig, (int64_t)F, F, J.n, k,
+                       reinterpret_cast<const uint4*>(W.btab), W.tpos, W.runs, W.distinct, W.masks, J.assign, dist, W.ctr);
+  } else if (!index) {
+    prof_begin(GEEK_PROF_ASSIGN_SCAN, s);
     hipLaunchKernelGGL(k_sig_dense, dim3(dgrid), dim3(256), 0, s, J.sig, (int64_t)F, F, J.modes, k, nullptr,
                        nullptr, J.n, J.assign, dist, W.ctr);
   } else {
+    hipLaunchKernelGGL(k_fill_u64, dim3(ceil_div((int64_t)W.hmask + 1, 256)), dim3(256), 0, s, W.hkey,
+                       (int64_t)W.hmask + 1, ~0ull);
+    hipLaunchKernelGGL(k_index_insert, dim3(ceil_div(KI, 256)), dim3(256), 0, s, sv, sf, KI, W.hkey, W.hval,
+                       W.hmask);
+    prof_begin(GEEK_PROF_ASSIGN_SCAN, s);
     const int grid = J.n < 65536 ? (int)J.n : 65536;
     hipLaunchKernelGGL(k_sig_assign, dim3(grid), dim3(64), 0, s, J.sig, (int64_t)F, F, J.n, W.hkey, W.hval,
                        W.hmask, sj, J.assign, dist, W.dense, W.small, W.ctr);
