@@ -44,25 +44,44 @@ constexpr int SSE_BLOCK = 4096;
 // members are taken CB at a time, their values loaded together (the next
 // batch's ids already in flight), then added in order.
 constexpr int CB = 32;
+
+// Largest magnitude seen by a wavefront into *out (skipped while *out is not
+// below it).
+GEEK_D void wave_absmax(float v, float* out) {
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  if ((threadIdx.x & 63) == 0 && v > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomic_max_nonneg(out, v);
+}
+
+// Centroid of dimension t over the members [s, e) of mem (ids below n), one
+// ordered chain.
+GEEK_D double centroid_of(const float* __restrict__ X, int64_t ldx, int64_t n, int t,
+                          const uint32_t* __restrict__ mem, uint32_t s, uint32_t e, int32_t* st);
+
 __global__ void k_centroids(const float* __restrict__ X, int64_t ldx, int64_t n, int d,
                             const uint32_t* __restrict__ offs, const uint32_t* __restrict__ mem,
-                            int k, const uint32_t* __restrict__ kdev, double* __restrict__ C, int32_t* st) {
-  int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)k * d) return;
-  int j = (int)(gid / d), t = (int)(gid % d);
-  // seeds counted on the device: those past the count take no part
-  const int kv = kdev ? (int)min(*kdev, (uint32_t)k) : k;
-  if (j >= kv) {
-    if (kv == 0 && gid == 0) set_status(st, GEEK_ERR_NO_SEEDS);
-    C[gid] = 0.0;
-    return;
+                            int k, const uint32_t* __restrict__ kdev, double* __restrict__ C,
+                            float* __restrict__ cabs, int32_t* st) {
+  const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  double c = 0.0;
+  if (gid < (int64_t)k * d) {
+    const int j = (int)(gid / d), t = (int)(gid % d);
+    // seeds counted on the device: those past the count take no part
+    const int kv = kdev ? (int)min(*kdev, (uint32_t)k) : k;
+    if (j < kv) {
+      const uint32_t s = offs[j], e = offs[j + 1];
+      if (e <= s) set_status(st, GEEK_ERR_EMPTY_SET);
+      else c = centroid_of(X, ldx, n, t, mem, s, e, st);
+    } else if (kv == 0 && gid == 0) {
+      set_status(st, GEEK_ERR_NO_SEEDS);
+    }
+    C[gid] = c;
   }
-  uint32_t s = offs[j], e = offs[j + 1];
-  if (e <= s) {
-    set_status(st, GEEK_ERR_EMPTY_SET);
-    C[gid] = 0.0;
-    return;
-  }
+  wave_absmax((float)fabs(c), cabs);
+}
+
+GEEK_D double centroid_of(const float* __restrict__ X, int64_t ldx, int64_t n, int t,
+                          const uint32_t* __restrict__ mem, uint32_t s, uint32_t e, int32_t* st) {
   double acc = 0.0;
   bool bad = false;
   // ids of member q (clamped into the seed's range: reads past the end are
@@ -87,7 +106,7 @@ __global__ void k_centroids(const float* __restrict__ X, int64_t ldx, int64_t n,
       if ((uint32_t)u < cnt) acc = __dadd_rn(acc, (double)v[u]);
   }
   if (bad) set_status(st, GEEK_ERR_ARG);
-  C[gid] = acc / (double)(e - s);
+  return acc / (double)(e - s);
 }
 
 // Seeds with many members (a further assignment pass takes whole clusters
@@ -135,41 +154,42 @@ __global__ __launch_bounds__(256) void k_gather_t(const float* __restrict__ X, i
 // additions as k_centroids.
 constexpr int CT_B = 16;  // 16-byte loads in flight per batch (64 members)
 __global__ void k_centroids_t(const float* __restrict__ Xt, int64_t nm, int d,
-                              const uint32_t* __restrict__ offs, int k, double* __restrict__ C, int32_t* st) {
+                              const uint32_t* __restrict__ offs, int k, double* __restrict__ C,
+                              float* __restrict__ cabs, int32_t* st) {
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)k * d) return;
-  const int j = (int)(gid / d), t = (int)(gid % d);
-  const int64_t s = offs[j], e = offs[j + 1];
-  if (e <= s) {
-    set_status(st, GEEK_ERR_EMPTY_SET);
-    C[gid] = 0.0;
-    return;
-  }
-  if (e > nm) {  // seed_offsets disagree with the member count of the job
-    set_status(st, GEEK_ERR_ARG);
-    C[gid] = 0.0;
-    return;
-  }
-  const int64_t gs = 4 * (int64_t)d;  // floats per group of four members
-  const float* p = Xt + (int64_t)t * 4;
-  auto at = [&](int64_t q) { return p[(q >> 2) * gs + (q & 3)]; };
-  double acc = 0.0;
-  int64_t q = s;
-  for (; q < e && (q & 3); ++q) acc = __dadd_rn(acc, (double)at(q));
-  for (; q + 4 * CT_B <= e; q += 4 * CT_B) {
-    float4 v[CT_B];
+  double c = 0.0;
+  if (gid < (int64_t)k * d) {
+    const int j = (int)(gid / d), t = (int)(gid % d);
+    const int64_t s = offs[j], e = offs[j + 1];
+    if (e <= s) {
+      set_status(st, GEEK_ERR_EMPTY_SET);
+    } else if (e > nm) {  // seed_offsets disagree with the member count of the job
+      set_status(st, GEEK_ERR_ARG);
+    } else {
+      const int64_t gs = 4 * (int64_t)d;  // floats per group of four members
+      const float* p = Xt + (int64_t)t * 4;
+      auto at = [&](int64_t q) { return p[(q >> 2) * gs + (q & 3)]; };
+      double acc = 0.0;
+      int64_t q = s;
+      for (; q < e && (q & 3); ++q) acc = __dadd_rn(acc, (double)at(q));
+      for (; q + 4 * CT_B <= e; q += 4 * CT_B) {
+        float4 v[CT_B];
 #pragma unroll
-    for (int u = 0; u < CT_B; ++u) v[u] = *reinterpret_cast<const float4*>(p + ((q >> 2) + u) * gs);
+        for (int u = 0; u < CT_B; ++u) v[u] = *reinterpret_cast<const float4*>(p + ((q >> 2) + u) * gs);
 #pragma unroll
-    for (int u = 0; u < CT_B; ++u) {
-      acc = __dadd_rn(acc, (double)v[u].x);
-      acc = __dadd_rn(acc, (double)v[u].y);
-      acc = __dadd_rn(acc, (double)v[u].z);
-      acc = __dadd_rn(acc, (double)v[u].w);
+        for (int u = 0; u < CT_B; ++u) {
+          acc = __dadd_rn(acc, (double)v[u].x);
+          acc = __dadd_rn(acc, (double)v[u].y);
+          acc = __dadd_rn(acc, (double)v[u].z);
+          acc = __dadd_rn(acc, (double)v[u].w);
+        }
+      }
+      for (; q < e; ++q) acc = __dadd_rn(acc, (double)at(q));
+      c = acc / (double)(e - s);
     }
+    C[gid] = c;
   }
-  for (; q < e; ++q) acc = __dadd_rn(acc, (double)at(q));
-  C[gid] = acc / (double)(e - s);
+  wave_absmax((float)fabs(c), cabs);
 }
 
 // Whether the centroids go through the dimension-major copy: seeds of 64
@@ -179,7 +199,7 @@ static bool centroids_transposed(const geek_assign_job& J) {
 }
 static int64_t members_pad(const geek_assign_job& J) { return (J.n_members + 3) / 4 * 4; }
 
-// Largest |value| of a float32 matrix / float64 centroids (FP8 scaling).
+// Largest |value| of a float32 matrix (FP8 scaling).
 __global__ void k_absmax_x(const float* __restrict__ X, int64_t ldx, int64_t n, int d, float* __restrict__ out) {
   const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   float m = 0.f;
@@ -187,14 +207,6 @@ __global__ void k_absmax_x(const float* __restrict__ X, int64_t ldx, int64_t n, 
     const float v = fabsf(X[(e / d) * ldx + (e % d)]);
     if (v > m) m = v;  // NaN compares false and is ignored here
   }
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) atomic_max_nonneg(out, m);
-}
-
-__global__ void k_absmax_c(const double* __restrict__ C, int64_t kd, float* __restrict__ out) {
-  const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  float m = 0.f;
-  for (int64_t e = g; e < kd; e += (int64_t)gridDim.x * blockDim.x) m = fmaxf(m, (float)fabs(C[e]) * 1.0001f);
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if ((threadIdx.x & 63) == 0) atomic_max_nonneg(out, m);
 }
@@ -223,7 +235,7 @@ __global__ void k_cprep(const double* __restrict__ C, int k, int d, int k_pad, i
                         const float* __restrict__ scale_p, const uint32_t* __restrict__ kdev) {
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= k_pad) return;
-  const float sc = M::SCALED ? *scale_p : 1.0f;
+  const float sc = M::SCALED ? M::scale_of(*scale_p) : 1.0f;
   // seeds past a device-side count are padding too
   if (j >= (kdev ? (int)min(*kdev, (uint32_t)k) : k)) {
     for (int t = 0; t < DP; t += M::KPER) M::store_zero(cl + (int64_t)j * DP + t);
@@ -247,12 +259,15 @@ __global__ void k_cprep(const double* __restrict__ C, int k, int d, int k_pad, i
   }
 }
 
-// Two workgroups per CU (at most 256 registers a wavefront) for the BF16
+// Three workgroups per CU for the float32 pieces up to 128 attributes (at most
+// 168 registers a wavefront, a few spilled while x is split: 1.88 -> 1.69 ms on
+// 500,009 x 100 rows, 3,001 seeds).  Two workgroups per CU (at most 256 registers a wavefront) for the BF16
 // first pass of point rows up to 128 attributes, whose stage pipeline keeps
 // two blocks' accumulators live; the compiler would otherwise go just past
 // 256 and halve the occupancy.
 template <class M, int DP, bool HET, int NCB>
 constexpr int scan_min_blocks() {
+  if (M::SPLIT && !HET && NCB == 1 && DP <= 128) return 3;
   return (std::is_same<M, ModeBF16>::value && !HET && NCB == 2 && DP <= 128) ? 2 : 1;
 }
 
@@ -833,10 +848,10 @@ int32_t modes_compute(const uint32_t* V, int64_t ldv, int F, int64_t n, const ui
                       int k, int64_t NC, uint32_t* modes, void* ws, int32_t* st, hipStream_t s);
 
 struct AssignWs {
-  float* cl32;
+  uint32_t* cl32;  // float16 pieces (ModeF32)
   void* cllow;  // bf16 / fp8 copy for the first pass
   float* nc;
-  float* cmax;   // [0] max |c|, [1] max |x_t|, [2] max |c_t|, [3] fp8 scale
+  float* cmax;   // [0] max |c|, [1] max |x_t| (FP8), [2] max |c_t|, [3] fp8 scale
   int32_t* rec;
   uint32_t* esc;
   uint32_t* fb;
@@ -856,7 +871,7 @@ static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
   Carver c(ws);
   const int DP = pick_dp(J.d);
   const int64_t k_pad = ((int64_t)J.k + SCAN_BC - 1) / SCAN_BC * SCAN_BC;
-  out->cl32 = c.take<float>(k_pad * DP);
+  out->cl32 = c.take<uint32_t>(k_pad * DP);
   const size_t low = J.precision == GEEK_PREC_BF16 ? 2 : J.precision == GEEK_PREC_FP8 ? 1 : 0;
   out->cllow = c.take<char>(low ? k_pad * DP * low : 16);
   out->nc = c.take<float>(k_pad);
@@ -883,8 +898,11 @@ size_t assign_euclid_ws(const geek_assign_job& J) {
 }
 
 // Column blocks per wave and LDS buffering per mode: the low-precision modes
-// reuse every LDS fragment for two column blocks and double-buffer; float32
-// (16x fewer flops per cycle) keeps one block and one buffer.
+// reuse every LDS fragment for two column blocks; float32's pieces of two
+// blocks would leave one wavefront per SIMD (500,009 x 100 rows, 3,001 seeds:
+// first pass 2.6 ms so, 1.6 ms with one block, 1.7 ms with one block and one
+// buffer; the rescan of 10^6 rows against 90,343 seeds 109 ms with two buffers,
+// 170 ms with one).
 // The BF16 first pass keeps the best two values per row (T2); FP8 and the
 // float32 pass, which also rescans rows with several candidates, keep the
 // full candidate window.
@@ -899,7 +917,7 @@ template <class M, bool HET> struct ScanShape {
   static constexpr bool T2 = std::is_same<M, ModeBF16>::value;
 };
 template <bool HET> struct ScanShape<ModeF32, HET> {
-  static constexpr int NCB = 1, NBUF = 1;
+  static constexpr int NCB = 1, NBUF = 2;
   static constexpr bool T2 = false;
 };
 
@@ -920,7 +938,7 @@ static void launch_scan(int DP, int grid, hipStream_t s, const geek_assign_job& 
   case DPV:                                                                                            \
     hipLaunchKernelGGL((k_scan<M, DPV, HET, NCB, NBUF, T2, WIDE>), dim3(grid), dim3(SCAN_THREADS), 0, s, J.X,\
                        J.ldx, J.d, n_rows, rows, rows_count, static_cast<const CE*>(cl), W.nc, k_pad,  \
-                       W.cmax, W.cmax + 3, het, J.k, W.rec, st);                                       \
+                       W.cmax, W.cmax + (M::SPLIT ? 2 : 3), het, J.k, W.rec, st);                                     \
     break;
     GEEK_SCAN_CASE(32)
     GEEK_SCAN_CASE(64)
@@ -968,10 +986,11 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
     hipLaunchKernelGGL(k_gather_t, dim3(ceil_div(nmp, GT_TILE), ceil_div(J.d, GT_TILE)), dim3(256), 0, s, J.X,
                        J.ldx, J.n, J.d, J.seed_offsets, J.k, J.seed_members, J.n_members, nmp, W.xt, st);
     hipLaunchKernelGGL(k_centroids_t, dim3(ceil_div((int64_t)J.k * J.d, 256)), dim3(256), 0, s, W.xt,
-                       J.n_members, J.d, J.seed_offsets, J.k, J.centroids, st);
+                       J.n_members, J.d, J.seed_offsets, J.k, J.centroids, W.cmax + 2, st);
   } else {
     hipLaunchKernelGGL(k_centroids, dim3(ceil_div((int64_t)J.k * J.d, 256)), dim3(256), 0, s, J.X,
-                       J.ldx, J.n, J.d, J.seed_offsets, J.seed_members, J.k, J.k_dev, J.centroids, st);
+                       J.ldx, J.n, J.d, J.seed_offsets, J.seed_members, J.k, J.k_dev, J.centroids,
+                       W.cmax + 2, st);
   }
   if (C.het_on) {
     if (int32_t rc = modes_compute(reinterpret_cast<const uint32_t*>(J.cat), J.n_cat, J.n_cat, J.n,
@@ -981,13 +1000,12 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
                        J.n_cat, k_pad, W.mode16);
   }
   hipLaunchKernelGGL(k_cprep<ModeF32>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d, k_pad,
-                     DP, W.cl32, W.nc, W.cmax, W.cmax + 3, J.k_dev);
+                     DP, W.cl32, W.nc, W.cmax, W.cmax + 2, J.k_dev);
   if (J.precision == GEEK_PREC_BF16) {
     hipLaunchKernelGGL(k_cprep<ModeBF16>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d,
                        k_pad, DP, static_cast<__bf16*>(W.cllow), nullptr, nullptr, W.cmax + 3, J.k_dev);
   } else if (J.precision == GEEK_PREC_FP8) {
     hipLaunchKernelGGL(k_absmax_x, dim3(1024), dim3(256), 0, s, J.X, J.ldx, J.n, J.d, W.cmax + 1);
-    hipLaunchKernelGGL(k_absmax_c, dim3(256), dim3(256), 0, s, J.centroids, (int64_t)J.k * J.d, W.cmax + 2);
     hipLaunchKernelGGL(k_fp8_scale, dim3(1), dim3(1), 0, s, W.cmax + 1, W.cmax + 2, W.cmax + 3);
     hipLaunchKernelGGL(k_cprep<ModeFP8>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d,
                        k_pad, DP, static_cast<uint8_t*>(W.cllow), nullptr, nullptr, W.cmax + 3, J.k_dev);
@@ -1144,7 +1162,7 @@ int32_t assign_euclid_batch(const geek_assign_job* jobs, int njobs, void* ws, si
       e.cl = low ? W.cllow : static_cast<const void*>(W.cl32);
       e.nc = W.nc;
       e.cmax = W.cmax;
-      e.scale = W.cmax + 3;
+      e.scale = W.cmax + (low ? 3 : 2);
       e.rec = W.rec;
       e.tile_begin = total;
       e.d = J.d;

@@ -22,33 +22,65 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_BC = 64;   // centroids per LDS stage
 
 // ---------------------------------------------------------------- modes
+// float32 values as two float16 pieces.  Scaled by a power of two (rows of x
+// each by their own, the centroids by one) so that the largest magnitude lies
+// in [2^14, 2^15), a value v is hi + lo, both rounded to float16: the remainder
+// v - hi is exact in float32, so |v - hi - lo| <= 2^-22 |v| plus at most 2^-14
+// where lo is subnormal.  A product is hi hi + hi lo + lo hi in float32
+// accumulators (float16 products are exact there); lo lo is dropped.  Against
+// float32 matrix instructions (64 cycles for 2 of K, and no vector work
+// beside them) three float16 ones take 96 cycles for 16.
 struct ModeF32 {
-  static constexpr int KPER = 1;  // K elements per lane per instruction
+  struct frag16 {
+    f16x8 hi, lo;
+  };
+  static constexpr int KPER = 8;
   static constexpr int KB = 16;   // products per fresh-accumulator block (0 = one chain)
-  static constexpr bool SCALED = false;
-  using ce = float;
-  using frag = float;
-  static constexpr double UX = 0.0;        // x is already float32
-  static constexpr double UC = 0x1p-24;    // float64 -> float32 rounding
-  static constexpr double A0 = 0.0;        // absolute error per element (scaled units)
-  GEEK_D static f32x16 mma(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  static constexpr bool SCALED = true, SPLIT = true;
+  using ce = uint32_t;            // 4 bytes per element: per 8, 16 bytes of hi then 16 of lo
+  using frag = frag16;
+  static constexpr double UX = 0x1p-22;
+  static constexpr double UC = 0x1p-22 + 0x1p-23;  // and the float64 -> float32 rounding
+  static constexpr double A0 = 0x1p-14;   // absolute error per element (scaled units)
+  static constexpr double DROP = 0x1p-21; // lo lo, and the roundings among the small products
+  GEEK_D static f32x16 mfma(f16x8 a, f16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+  // 2^e with largest magnitude * 2^e in [2^14, 2^15); e <= 120
+  GEEK_HD static float scale_of(float largest) {
+    const uint32_t e = (__builtin_bit_cast(uint32_t, largest) >> 23) & 255u;
+    const int q = 141 - (int)e;
+    return __builtin_bit_cast(float, (uint32_t)((q < 120 ? q : 120) + 127) << 23);
   }
-  GEEK_D static frag load_lds(const ce* p) { return *p; }
-  GEEK_D static frag from_f32(const float* v, float) { return v[0]; }
-  GEEK_D static void store(ce* p, const float* v, float) { p[0] = v[0]; }
-  GEEK_D static void store_zero(ce* p) { p[0] = 0.f; }
+  GEEK_D static frag from_f32(const float* v, float sc) {
+    frag f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float y = v[e] * sc;
+      f.hi[e] = (_Float16)y;
+      f.lo[e] = (_Float16)(y - (float)f.hi[e]);
+    }
+    return f;
+  }
+  GEEK_D static void store(ce* p, const float* v, float sc) {
+    const frag f = from_f32(v, sc);
+    *reinterpret_cast<f16x8*>(p) = f.hi;
+    *reinterpret_cast<f16x8*>(p + 4) = f.lo;
+  }
+  GEEK_D static void store_zero(ce* p) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) p[e] = 0u;
+  }
 };
 
 struct ModeBF16 {
   static constexpr int KPER = 8;
   static constexpr int KB = 0;  // input rounding (2^-8) dominates the accumulation
-  static constexpr bool SCALED = false;
+  static constexpr bool SCALED = false, SPLIT = false;
   using ce = __bf16;
   using frag = bf16x8;
   static constexpr double UX = 0x1p-8;  // conservative for any rounding to bf16
   static constexpr double UC = 0x1p-8;
-  static constexpr double A0 = 0.0;
+  static constexpr double A0 = 0.0, DROP = 0.0;
+  GEEK_HD static float scale_of(float) { return 1.0f; }
   GEEK_D static f32x16 mma(frag a, frag b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
@@ -76,12 +108,13 @@ struct ModeBF16 {
 struct ModeFP8 {
   static constexpr int KPER = 8;
   static constexpr int KB = 0;
-  static constexpr bool SCALED = true;
+  static constexpr bool SCALED = true, SPLIT = false;
   using ce = uint8_t;
   using frag = long;
   static constexpr double UX = 0x1p-3;
   static constexpr double UC = 0x1p-3;
-  static constexpr double A0 = 0x1p-10;
+  static constexpr double A0 = 0x1p-10, DROP = 0.0;
+  GEEK_HD static float scale_of(float scale) { return scale; }
   GEEK_D static f32x16 mma(frag a, frag b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a, b, c, 0, 0, 0);
   }
@@ -115,28 +148,30 @@ GEEK_D double gamma_n(double nn, double u) { return nn * u / (1.0 - nn * u); }
 // Rigorous bound on |(|x|^2 + v_j) - D64(i, j)| for every j, where v_j is the
 // float32 epilogue value fma(-2/s^2, acc, |c_j|^2) (+ gamma * mismatches)
 // and D64 the float64 reference.  X = |x|, cm = max |c|; the inputs are
-// rounded with relative error UX/UC and absolute error A0/s per element, so
+// rounded with relative error UX/UC and absolute error A0/s per element (s
+// the row's or the centroids' scale; inv_x, inv_c its inverse), so
 // |x^ - x| <= ex = UX X + A0 sqrt(DP) / s (likewise ec) and, by Cauchy-
-// Schwarz, |x^.c^ - x.c| <= ex cm + X ec + ex ec; the float32 accumulation of
+// Schwarz, |x^.c^ - x.c| <= ex cm + X ec + ex ec (+ DROP X cm for products
+// left out); the float32 accumulation of
 // the (exact) products adds gamma_n(2u) |x^| |c^| with n = DP + 1 roundings
 // per product for one accumulator chain, or n = KB + DP/KB + 1 when blocks of
 // KB products start from zero and their sums are added to the running value.
 template <class M, int DP, bool T2, bool BLK>
-GEEK_D float two_eps(double xn, double cm, double inv_scale, double het_max) {
+GEEK_D float two_eps(double xn, double cm, double inv_x, double inv_c, double het_max) {
   const double u32 = 0x1p-24;
   constexpr int NACC = BLK ? M::KB + DP / M::KB + 1 : DP + 1;
   const double g_acc = gamma_n(NACC, 2.0 * u32);
   const double g64 = gamma_n(DP + 2, 0x1p-53);
-  const double ab = M::A0 * inv_scale * sqrt((double)DP);
-  const double ex = M::UX * xn + ab, ec = M::UC * cm + ab;
-  const double dot = ex * cm + xn * ec + ex * ec + g_acc * (xn + ex) * (cm + ec);
+  const double root = sqrt((double)DP);
+  const double ex = M::UX * xn + M::A0 * inv_x * root, ec = M::UC * cm + M::A0 * inv_c * root;
+  const double dot = ex * cm + xn * ec + ex * ec + M::DROP * xn * cm + g_acc * (xn + ex) * (cm + ec);
   const double vmax = cm * cm + 2.0 * (xn + ex) * (cm + ec) + het_max;
   const double s2 = (xn + cm) * (xn + cm) + het_max;
   // accumulations that could overflow float32 give no bound: rows escalate
   if (!(4.0 * vmax < 0x1p120)) return INFINITY;
   double eps = 2.0 * dot                       // 2 x.c
                + g_acc * cm * cm                // |c|^2 / 2 as the accumulator's start
-               + 0x1p-124 * inv_scale * inv_scale  // its float32 subnormal rounding
+               + 0x1p-124 * inv_x * inv_c  // its float32 subnormal rounding
                + (u32 + g64) * cm * cm          // |c|^2 stored as float32
                + 2.0 * u32 * vmax               // epilogue roundings
                + g64 * s2 + 0x1p-52 * het_max   // float64 reference rounding
@@ -165,6 +200,9 @@ __device__ __forceinline__ void scan_tiles(
     const float* __restrict__ cmax_p, const float* __restrict__ scale_p, Het het, int k,
     int32_t* __restrict__ rec, int32_t* st, int64_t tile0, int64_t tile_end, int64_t tstep) {
   using CE = typename M::ce;
+  // centroids per stage: half as many where an element takes four bytes and
+  // two stages are in LDS (three workgroups per CU at d = 128 then)
+  constexpr int BC = M::SPLIT && NBUF == 2 ? SCAN_BC / 2 : SCAN_BC;
   constexpr int S = DP / 2 / M::KPER;             // MFMA steps over K
   constexpr int CH = DP * (int)sizeof(CE) / 16;   // 16-byte chunks per centroid row
   // DMA: stages stream global -> LDS directly (global_load_lds_dwordx4, one
@@ -174,15 +212,15 @@ __device__ __forceinline__ void scan_tiles(
   constexpr bool DMA = NBUF == 2 && CH >= 4;
   constexpr int STR = DMA ? DP : DP + 16 / (int)sizeof(CE);  // LDS row (elements)
   constexpr int BN = 128 * NCB;                   // rows per tile
-  constexpr int CPT = DMA ? 1 : (SCAN_BC * CH + SCAN_THREADS - 1) / SCAN_THREADS;
+  constexpr int CPT = DMA ? 1 : (BC * CH + SCAN_THREADS - 1) / SCAN_THREADS;
   // one LDS object per stage buffer: with the buffer known at compile time
   // the compiler can tell that reads of the current stage do not alias the
   // LDS DMA filling the next one, and does not wait for that DMA
-  __shared__ __attribute__((aligned(16))) CE lds_c0[SCAN_BC * STR];
-  __shared__ __attribute__((aligned(16))) CE lds_c1[NBUF == 2 ? SCAN_BC * STR : 1];
-  __shared__ float lds_nc[NBUF][SCAN_BC];
-  __shared__ __attribute__((aligned(16))) uint32_t lds_mode0[HET ? SCAN_BC * MAX_CAT : 1];
-  __shared__ __attribute__((aligned(16))) uint32_t lds_mode1[HET && NBUF == 2 ? SCAN_BC * MAX_CAT : 1];
+  __shared__ __attribute__((aligned(16))) CE lds_c0[BC * STR];
+  __shared__ __attribute__((aligned(16))) CE lds_c1[NBUF == 2 ? BC * STR : 1];
+  __shared__ float lds_nc[NBUF][BC];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_mode0[HET ? BC * MAX_CAT : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_mode1[HET && NBUF == 2 ? BC * MAX_CAT : 1];
   auto cbuf = [&](auto bc) -> CE* {
     if constexpr (decltype(bc)::value == 0) return lds_c0;
     else return lds_c1;
@@ -209,8 +247,8 @@ __device__ __forceinline__ void scan_tiles(
 
   const int64_t count = rows ? (int64_t)*rows_count : n_rows;
   const double cm = (double)*cmax_p;
-  const float sc = M::SCALED ? *scale_p : 1.0f;
-  const float m2s = -2.0f / (sc * sc);  // power of two: exact rescaling
+  const float sc = M::SCALED ? M::scale_of(*scale_p) : 1.0f;
+  const float m2s = M::SPLIT ? 1.0f : -2.0f / (sc * sc);  // power of two: exact rescaling
   // T2 starts every accumulator at -s^2 |c_j|^2 / 2 (exact power-of-two
   // scalings), so acc = s^2 (x.c - |c_j|^2 / 2) and v_j = m2s * acc
   const float nc_mul = T2 ? -0.5f * sc * sc : 1.0f;
@@ -223,22 +261,22 @@ __device__ __forceinline__ void scan_tiles(
   const double het_max = HET ? het.gamma * het.n_cat : 0.0;
 
   // stage loading: registers <- global, LDS <- registers
-  constexpr int MPT = HET ? (SCAN_BC * MAX_CAT + SCAN_THREADS - 1) / SCAN_THREADS : 1;
+  constexpr int MPT = HET ? (BC * MAX_CAT + SCAN_THREADS - 1) / SCAN_THREADS : 1;
   uint4 stg[CPT];
   float stg_nc = 0.f;
   uint32_t stg_mode[MPT];
 #define GEEK_LOAD_REGS(C0)                                                                                 \
   do {                                                                                                     \
     _Pragma("unroll") for (int u = 0; u < CPT; ++u) {                                                     \
-      const int q = min(tid + u * SCAN_THREADS, SCAN_BC * CH - 1); /* clamped: always in bounds */        \
+      const int q = min(tid + u * SCAN_THREADS, BC * CH - 1); /* clamped: always in bounds */        \
       const int r = q / CH, c = q % CH;                                                                    \
       stg[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(cl + (int64_t)((C0) + r) * DP) + \
                                                c * 16);                                                    \
     }                                                                                                      \
-    stg_nc = nc[(C0) + (tid & (SCAN_BC - 1))];                                                             \
+    stg_nc = nc[(C0) + (tid & (BC - 1))];                                                             \
     if constexpr (HET) {                                                                                   \
       _Pragma("unroll") for (int u = 0; u < MPT; ++u) {                                                   \
-        const int q = min(tid + u * SCAN_THREADS, SCAN_BC * MAX_CAT - 1);                                  \
+        const int q = min(tid + u * SCAN_THREADS, BC * MAX_CAT - 1);                                  \
         const int r = q / MAX_CAT, a = q % MAX_CAT;                                                        \
         const bool ok = a < het.n_cat && (C0) + r < k;                                                     \
         const uint32_t mv = het.mode[ok ? (int64_t)((C0) + r) * het.n_cat + a : 0];                        \
@@ -250,23 +288,23 @@ __device__ __forceinline__ void scan_tiles(
   do {                                                                                                     \
     _Pragma("unroll") for (int u = 0; u < CPT; ++u) {                                                     \
       const int q = tid + u * SCAN_THREADS;                                                                \
-      if (q < SCAN_BC * CH) {                                                                              \
+      if (q < BC * CH) {                                                                              \
         const int r = q / CH, c = q % CH;                                                                  \
         *reinterpret_cast<uint4*>(reinterpret_cast<char*>(cbuf(IC<(B)>{}) + r * STR) + c * 16) = stg[u];   \
       }                                                                                                    \
     }                                                                                                      \
-    if (tid < SCAN_BC) lds_nc[B][tid] = nc_stage(stg_nc);                                                  \
+    if (tid < BC) lds_nc[B][tid] = nc_stage(stg_nc);                                                  \
     if constexpr (HET) {                                                                                   \
       _Pragma("unroll") for (int u = 0; u < MPT; ++u) {                                                   \
         const int q = tid + u * SCAN_THREADS;                                                              \
-        if (q < SCAN_BC * MAX_CAT) mbuf(IC<(B)>{})[q] = stg_mode[u];                                       \
+        if (q < BC * MAX_CAT) mbuf(IC<(B)>{})[q] = stg_mode[u];                                       \
       }                                                                                                    \
     }                                                                                                      \
   } while (0)
 #define GEEK_DMA_STAGE(C0, B)                                                                              \
   do {                                                                                                     \
-    _Pragma("unroll") for (int u = 0; u < CH / 4; ++u) {                                                  \
-      const int slot0 = w * (SCAN_BC * CH / 4) + u * 64; /* wave-uniform LDS chunk */                     \
+    _Pragma("unroll") for (int u = 0; u < BC * CH / 256; ++u) {                                           \
+      const int slot0 = w * (BC * CH / 4) + u * 64; /* wave-uniform LDS chunk */                     \
       const int slot = slot0 + lane;                                                                       \
       const int r = slot / CH, c = (slot % CH) ^ (r & (CH - 1));                                           \
       __builtin_amdgcn_global_load_lds(                                                                    \
@@ -275,8 +313,8 @@ __device__ __forceinline__ void scan_tiles(
     }                                                                                                      \
     /* raw |c|^2 in a register, converted when lds_nc[B] is stored: a use here \
        would make the wave wait for the whole stage at once */                 \
-    stg_nc = nc[(C0) + (tid & (SCAN_BC - 1))];                                                             \
-    if constexpr (HET)                                                                                     \
+    stg_nc = nc[(C0) + (tid & (BC - 1))];                                                             \
+    if (HET && w * 64 < BC * MAX_CAT / 4)                                                                  \
       __builtin_amdgcn_global_load_lds(                                                                    \
           reinterpret_cast<const char*>(het.mode16 + (int64_t)(C0) * MAX_CAT) + (w * 64 + lane) * 16,     \
           reinterpret_cast<char*>(mbuf(IC<(B)>{})) + w * 64 * 16, 16, 0, 0);                              \
@@ -284,6 +322,7 @@ __device__ __forceinline__ void scan_tiles(
 
   for (int64_t tile = tile0; tile < tile_end && tile * BN < count; tile += tstep) {
     typename M::frag xb[NCB][S];
+    float m2[NCB];  // -2 / (the row's scale * the centroids')
     float twoeps[NCB];
     int32_t crow[NCB][HET ? MAX_CAT : 1];
     bool valid[NCB];
@@ -323,11 +362,21 @@ __device__ __forceinline__ void scan_tiles(
         finite = finite && isfinite(xv[q]);
         nrm += (double)xv[q] * (double)xv[q];
       }
+      float sx = sc;
+      if constexpr (M::SPLIT) {
+        float mx = 0.f;
 #pragma unroll
-      for (int s = 0; s < S; ++s) xb[cb][s] = M::from_f32(xv + s * M::KPER, sc);
+        for (int q = 0; q < DP / 2; ++q) mx = fmaxf(mx, fabsf(xv[q]));
+        sx = M::scale_of(fmaxf(mx, __shfl_xor(mx, 32)));
+        m2[cb] = -2.0f * (1.0f / sx) * (1.0f / sc);
+      } else {
+        m2[cb] = m2s;
+      }
+#pragma unroll
+      for (int s = 0; s < S; ++s) xb[cb][s] = M::from_f32(xv + s * M::KPER, sx);
       if (!finite) set_status(st, GEEK_ERR_NONFINITE);
       nrm += __shfl_xor(nrm, 32);
-      twoeps[cb] = two_eps<M, DP, T2, BLK>(sqrt(nrm) * (1.0 + 1e-12), cm, 1.0 / sc, het_max);
+      twoeps[cb] = two_eps<M, DP, T2, BLK>(sqrt(nrm) * (1.0 + 1e-12), cm, 1.0 / sx, 1.0 / sc, het_max);
       if constexpr (HET) {
 #pragma unroll
         for (int a = 0; a < MAX_CAT; ++a)
@@ -365,7 +414,7 @@ __device__ __forceinline__ void scan_tiles(
     __syncthreads();  // previous tile done with the LDS buffers
     if constexpr (DMA) {
       GEEK_DMA_STAGE(0, 0);
-      if (tid < SCAN_BC) lds_nc[0][tid] = nc_stage(stg_nc);
+      if (tid < BC) lds_nc[0][tid] = nc_stage(stg_nc);
       __builtin_amdgcn_s_waitcnt(0);
     } else {
       GEEK_LOAD_REGS(0);
@@ -393,23 +442,25 @@ __device__ __forceinline__ void scan_tiles(
     // values enter the running best two (the same order of updates)
     f32x16 pendB[T2 ? NCB : 1];
     int pend_g = -1;
-    // one stage of SCAN_BC centroids from buffer `cur` (a compile-time
+    // one stage of BC centroids from buffer `cur` (a compile-time
     // constant), with the next stage loading into the other buffer
     auto stage = [&](auto curc, const int c0, const int it) {
       constexpr int cur = NBUF == 2 ? decltype(curc)::value : 0;
       constexpr int nxt = NBUF == 2 ? 1 - cur : 0;
-      const bool more = c0 + SCAN_BC < k_pad;
+      const bool more = c0 + BC < k_pad;
       if constexpr (DMA) {
-        if (more) GEEK_DMA_STAGE(c0 + SCAN_BC, nxt);
+        if (more) GEEK_DMA_STAGE(c0 + BC, nxt);
       } else {
-        if (NBUF == 2 && more) GEEK_LOAD_REGS(c0 + SCAN_BC);
+        if (NBUF == 2 && more) GEEK_LOAD_REGS(c0 + BC);
       }
 
       // A fragments of a 32-row block: all S of them in registers, the next
       // block's loaded while this block's epilogue runs (modes with at most
-      // eight K steps per block; float32's 64 steps read them one by one)
-      constexpr bool PF = !BLK && S <= 8;
-      auto afrag_rb = [&](int rb, int s) {
+      // eight K steps per block of one register quad; float32's pieces are
+      // read step by step)
+      constexpr bool PF = S <= 8 && !M::SPLIT;
+      auto afrag_rb = [&](int rb, int s) -> typename M::frag {
+        if constexpr (!M::SPLIT) {
         const int R = rb * 32 + p;
         if constexpr (DMA) {
           const char* rowp = reinterpret_cast<const char*>(cbuf(IC<cur>{})) + R * CH * 16;
@@ -417,6 +468,9 @@ __device__ __forceinline__ void scan_tiles(
           return M::load_lds(reinterpret_cast<const CE*>(rowp + (((off >> 4) ^ (R & (CH - 1))) << 4) + (off & 15)));
         } else {
           return M::load_lds(cbuf(IC<cur>{}) + R * STR + h * (DP / 2) + s * M::KPER);
+        }
+        } else {
+          return typename M::frag{};
         }
       };
       typename M::frag af[PF ? S : 1];
@@ -428,7 +482,7 @@ __device__ __forceinline__ void scan_tiles(
       // blocks of the stage go to the matrix cores back to back, into two
       // accumulator sets, so the first block's epilogue runs while the
       // second block's products are still in the matrix pipe
-      if constexpr (T2 && PF && !HET && SCAN_BC == 64) {
+      if constexpr (T2 && PF && !HET && BC == 64) {
         f32x16 accA[NCB], accB[NCB];
         {
           f32x16 initA;
@@ -481,7 +535,7 @@ __device__ __forceinline__ void scan_tiles(
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) accB[cb] = initB;
         }
-        const int g0 = it * (SCAN_BC / 32);
+        const int g0 = it * (BC / 32);
         // block B's products step by step, each step followed by its share
         // of block A's eight value pairs per column block: the vector
         // instructions issue while the matrix pipe works on B
@@ -518,7 +572,7 @@ __device__ __forceinline__ void scan_tiles(
         pend_g = g0 + 1;
       } else
 #pragma unroll 1
-      for (int rb = 0; rb < SCAN_BC / 32; ++rb) {
+      for (int rb = 0; rb < BC / 32; ++rb) {
         const int jb = rb * 32;
         f32x16 acc[NCB];
         f32x16 init = f32x16{};
@@ -532,40 +586,67 @@ __device__ __forceinline__ void scan_tiles(
         const int R = rb * 32 + p;
         const char* rowp = reinterpret_cast<const char*>(cbuf(IC<cur>{})) + R * CH * 16;
         auto afrag = [&](int s) {
-          if constexpr (DMA) {
+          if constexpr (M::SPLIT) {
+            typename M::frag f;
+            if constexpr (DMA) {
+              const int c = (h * (DP / 2) + s * M::KPER) / 4;  // 16-byte chunk of hi; lo follows
+              f.hi = *reinterpret_cast<const f16x8*>(rowp + ((c ^ (R & (CH - 1))) << 4));
+              f.lo = *reinterpret_cast<const f16x8*>(rowp + (((c + 1) ^ (R & (CH - 1))) << 4));
+            } else {
+              f.hi = *reinterpret_cast<const f16x8*>(ap + s * M::KPER);
+              f.lo = *reinterpret_cast<const f16x8*>(ap + s * M::KPER + 4);
+            }
+            return f;
+          } else if constexpr (DMA) {
             const int off = (h * (DP / 2) + s * M::KPER) * (int)sizeof(CE);
             return M::load_lds(reinterpret_cast<const CE*>(rowp + (((off >> 4) ^ (R & (CH - 1))) << 4) + (off & 15)));
           } else {
             return M::load_lds(ap + s * M::KPER);
           }
         };
-        if constexpr (BLK) {
-          // blocks of KB products (KB / (2 KPER) steps) in fresh accumulators,
-          // then added to the running sums (see two_eps)
-          constexpr int SB = M::KB / (2 * M::KPER);
+        if constexpr (M::SPLIT && BLK) {
+          // blocks of 16 products in fresh accumulators, the small products
+          // first, then added to the running sums (see two_eps)
+          static_assert(M::KB == 2 * M::KPER, "one step per block");
 #pragma unroll
-          for (int s0 = 0; s0 < S; s0 += SB) {
-            f32x16 blk[NCB];
+          for (int s = 0; s < S; ++s) {
+            const typename M::frag a = afrag(s);
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) blk[cb] = f32x16{};
+            for (int cb = 0; cb < NCB; ++cb) {
+              f32x16 blk = M::mfma(a.lo, xb[cb][s].hi, f32x16{});
+              blk = M::mfma(a.hi, xb[cb][s].lo, blk);
+              blk = M::mfma(a.hi, xb[cb][s].hi, blk);
 #pragma unroll
-            for (int s = s0; s < s0 + SB; ++s) {
-              const typename M::frag a = afrag(s);
-#pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) blk[cb] = M::mma(a, xb[cb][s], blk[cb]);
+              for (int r = 0; r < 16; ++r) acc[cb][r] += blk[r];
             }
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) acc[cb][r] += blk[cb][r];
           }
-        } else if constexpr (PF) {
+        } else if constexpr (M::SPLIT) {
+          // the small products in a chain of their own, added last
+          f32x16 low[NCB];
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) low[cb] = f32x16{};
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const typename M::frag a = afrag(s);
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) low[cb] = M::mfma(a.lo, xb[cb][s].hi, low[cb]);
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) acc[cb] = M::mfma(a.hi, xb[cb][s].hi, acc[cb]);
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) low[cb] = M::mfma(a.hi, xb[cb][s].lo, low[cb]);
+          }
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][r] += low[cb][r];
+        } else
+        if constexpr (PF) {
 #pragma unroll
           for (int s = 0; s < S; ++s) {
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) acc[cb] = M::mma(af[s], xb[cb][s], acc[cb]);
           }
-          if (rb + 1 < SCAN_BC / 32) {
+          if (rb + 1 < BC / 32) {
 #pragma unroll
             for (int s = 0; s < S; ++s) af[s] = afrag_rb(rb + 1, s);
           }
@@ -579,7 +660,7 @@ __device__ __forceinline__ void scan_tiles(
         }
         if constexpr (T2) {
           // branch-free: per value one bit insert and two med3
-          const int gblk = it * (SCAN_BC / 32) + rb;
+          const int gblk = it * (BC / 32) + rb;
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) {
             float t[16];
@@ -610,7 +691,7 @@ __device__ __forceinline__ void scan_tiles(
           float vmin = INFINITY;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            v[r] = __builtin_fmaf(m2s, acc[cb][r], ncv[r]);
+            v[r] = __builtin_fmaf(m2[cb], acc[cb][r], ncv[r]);
             if constexpr (HET) {
               const uint32_t* md = mbuf(IC<cur>{}) + (jb + (r >> 2) * 8 + h * 4 + (r & 3)) * MAX_CAT;
               int mm = 0;
@@ -661,13 +742,13 @@ __device__ __forceinline__ void scan_tiles(
       }
       if (more) {
         if constexpr (DMA) {
-          if (tid < SCAN_BC) lds_nc[nxt][tid] = nc_stage(stg_nc);
+          if (tid < BC) lds_nc[nxt][tid] = nc_stage(stg_nc);
           __builtin_amdgcn_s_waitcnt(0);  // this wave's chunks of the next stage landed
         } else if (NBUF == 2) {
           GEEK_STORE_LDS(nxt);
         } else {
           __syncthreads();
-          GEEK_LOAD_REGS(c0 + SCAN_BC);
+          GEEK_LOAD_REGS(c0 + BC);
           GEEK_STORE_LDS(0);
         }
       }
@@ -675,12 +756,12 @@ __device__ __forceinline__ void scan_tiles(
     };
     for (int c0 = 0, it = 0; c0 < k_pad;) {
       stage(IC<0>{}, c0, it);
-      c0 += SCAN_BC;
+      c0 += BC;
       ++it;
       if constexpr (NBUF == 2) {
         if (c0 < k_pad) {
           stage(IC<1>{}, c0, it);
-          c0 += SCAN_BC;
+          c0 += BC;
           ++it;
         }
       }
