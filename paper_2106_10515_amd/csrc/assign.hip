@@ -14,7 +14,7 @@
 //                 ambiguous rows).  The BF16 first pass keeps only the best
 //                 and second-best values (branch-free); a row is settled when
 //                 the runner-up lies beyond 2*eps_i, else it is rescanned in
-//                 float32.  FP8 keeps a TCAND window like float32.
+//                 float32.
 //   k_finalize    float64 distance (the reference formula, same operation
 //                 order) for each candidate; lowest index wins exact ties.
 //                 Rows whose candidate window overflowed are escalated.
@@ -199,43 +199,15 @@ static bool centroids_transposed(const geek_assign_job& J) {
 }
 static int64_t members_pad(const geek_assign_job& J) { return (J.n_members + 3) / 4 * 4; }
 
-// Largest |value| of a float32 matrix (FP8 scaling).
-__global__ void k_absmax_x(const float* __restrict__ X, int64_t ldx, int64_t n, int d, float* __restrict__ out) {
-  const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  float m = 0.f;
-  for (int64_t e = g; e < n * d; e += (int64_t)gridDim.x * blockDim.x) {
-    const float v = fabsf(X[(e / d) * ldx + (e % d)]);
-    if (v > m) m = v;  // NaN compares false and is ignored here
-  }
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) atomic_max_nonneg(out, m);
-}
-
-// scale = 2^floor(log2(224 / max)), so scaled values stay inside every
-// e4m3 variant's normal range; 1 when everything is zero.
-__global__ void k_fp8_scale(const float* __restrict__ mx, const float* __restrict__ mc, float* __restrict__ scale) {
-  if (blockIdx.x || threadIdx.x) return;
-  const float m = fmaxf(*mx, *mc);
-  // 2^e with max |value| * 2^e in [112, 224]; e is clamped at 60 for tiny
-  // data (the absolute error term covers it); data too large for a safe
-  // 2^e gets scale 0, which makes every row's bound infinite (escalation)
-  if (!(m > 0.f)) {
-    *scale = 1.0f;
-    return;
-  }
-  const float e = floorf(log2f(224.0f / m));
-  *scale = e < -60.f ? 0.0f : exp2f(fminf(e, 60.f));
-}
-
 // Matrix-core input copies of the centroids, zero-padded to [k_pad][DP];
 // padded rows get |c|^2 = +inf so they never enter a window.
 template <class M>
 __global__ void k_cprep(const double* __restrict__ C, int k, int d, int k_pad, int DP,
                         typename M::ce* __restrict__ cl, float* __restrict__ nc, float* __restrict__ cmax,
-                        const float* __restrict__ scale_p, const uint32_t* __restrict__ kdev) {
+                        const float* __restrict__ cabs_p, const uint32_t* __restrict__ kdev) {
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= k_pad) return;
-  const float sc = M::SCALED ? M::scale_of(*scale_p) : 1.0f;
+  const float sc = M::SPLIT ? M::scale_of(*cabs_p) : 1.0f;
   // seeds past a device-side count are padding too
   if (j >= (kdev ? (int)min(*kdev, (uint32_t)k) : k)) {
     for (int t = 0; t < DP; t += M::KPER) M::store_zero(cl + (int64_t)j * DP + t);
@@ -276,9 +248,9 @@ __global__ __launch_bounds__(SCAN_THREADS, (scan_min_blocks<M, DP, HET, NCB>()))
     const float* __restrict__ X, int64_t ldx, int d, int64_t n_rows,
     const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
     const typename M::ce* __restrict__ cl, const float* __restrict__ nc, int k_pad,
-    const float* __restrict__ cmax_p, const float* __restrict__ scale_p, Het het, int k,
+    const float* __restrict__ cmax_p, const float* __restrict__ cabs_p, Het het, int k,
     int32_t* __restrict__ rec, int32_t* st) {
-  scan_tiles<M, DP, HET, NCB, NBUF, T2, WIDE>(X, ldx, d, n_rows, rows, rows_count, cl, nc, k_pad, cmax_p, scale_p, het,
+  scan_tiles<M, DP, HET, NCB, NBUF, T2, WIDE>(X, ldx, d, n_rows, rows, rows_count, cl, nc, k_pad, cmax_p, cabs_p, het,
                                         k, rec, st, blockIdx.x, INT64_MAX, gridDim.x);
 }
 
@@ -369,8 +341,7 @@ __device__ void block_add_u64(unsigned long long* dst, unsigned long long v) {
   if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, v);
 }
 
-// Candidate windows (RECW records: the FP8 and float32 first passes, the
-// rescans): a lane per row, each lane walking its own row's candidates.
+// Candidate windows (RECW records: the float32 first pass, the rescans): a lane per row, each lane walking its own row's candidates.
 __global__ void k_finalize_win(const float* __restrict__ X, int64_t ldx, int d,
                            const double* __restrict__ C, int k, Het het, int64_t n_rows,
                            const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
@@ -847,11 +818,21 @@ size_t modes_ws(int64_t n_members, int F, int k);
 int32_t modes_compute(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32_t* so, const uint32_t* sm,
                       int k, int64_t NC, uint32_t* modes, void* ws, int32_t* st, hipStream_t s);
 
+// First passes on the bf16 matrix cores: GEEK_PREC_BF16 and GEEK_PREC_FP8.
+// e4m3 products run at the bf16 rate in the 32x32x16 form, and e4m3's error
+// window (2^-3) left most rows with more candidates than a lane's window holds,
+// so that a float32 rescan of nearly every row followed: 2 10^6 heterogeneous
+// rows, k = 1,000, hash and buckets included: 54.0 ms in e4m3, 10.4 ms now;
+// 805,748 x 115 rows, k = 1,312: 4.11 against 1.68 ms.
+static bool low_precision(const geek_assign_job& J) {
+  return J.precision == GEEK_PREC_BF16 || J.precision == GEEK_PREC_FP8;
+}
+
 struct AssignWs {
   uint32_t* cl32;  // float16 pieces (ModeF32)
-  void* cllow;  // bf16 / fp8 copy for the first pass
+  void* cllow;  // bf16 copy for the first pass
   float* nc;
-  float* cmax;   // [0] max |c|, [1] max |x_t| (FP8), [2] max |c_t|, [3] fp8 scale
+  float* cmax;   // [0] max |c|, [1] max |c_t|
   int32_t* rec;
   uint32_t* esc;
   uint32_t* fb;
@@ -872,7 +853,7 @@ static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
   const int DP = pick_dp(J.d);
   const int64_t k_pad = ((int64_t)J.k + SCAN_BC - 1) / SCAN_BC * SCAN_BC;
   out->cl32 = c.take<uint32_t>(k_pad * DP);
-  const size_t low = J.precision == GEEK_PREC_BF16 ? 2 : J.precision == GEEK_PREC_FP8 ? 1 : 0;
+  const size_t low = low_precision(J) ? 2 : 0;
   out->cllow = c.take<char>(low ? k_pad * DP * low : 16);
   out->nc = c.take<float>(k_pad);
   out->cmax = c.take<float>(4);
@@ -903,18 +884,14 @@ size_t assign_euclid_ws(const geek_assign_job& J) {
 // first pass 2.6 ms so, 1.6 ms with one block, 1.7 ms with one block and one
 // buffer; the rescan of 10^6 rows against 90,343 seeds 109 ms with two buffers,
 // 170 ms with one).
-// The BF16 first pass keeps the best two values per row (T2); FP8 and the
-// float32 pass, which also rescans rows with several candidates, keep the
-// full candidate window.
+// The BF16 first pass keeps the best two values per row (T2); the float32
+// pass, which also rescans rows with several candidates, keeps the full
+// candidate window.
 // Heterogeneous rows carry their categorical values in registers: one
 // column block.
 template <class M, bool HET> struct ScanShape {
-  // FP8's candidate window with two column blocks per wave runs 2-3x slower
-  // than with one (measured across depths); BF16 keeps two off HET
-  static constexpr int NCB = (HET || std::is_same<M, ModeFP8>::value) ? 1 : 2, NBUF = 2;
-  // e4m3's coarse rounding leaves most rows with a few candidates: FP8 keeps
-  // the full candidate window (float64 recheck of up to TCAND) instead
-  static constexpr bool T2 = std::is_same<M, ModeBF16>::value;
+  static constexpr int NCB = HET ? 1 : 2, NBUF = 2;
+  static constexpr bool T2 = true;
 };
 template <bool HET> struct ScanShape<ModeF32, HET> {
   static constexpr int NCB = 1, NBUF = 2;
@@ -938,7 +915,7 @@ static void launch_scan(int DP, int grid, hipStream_t s, const geek_assign_job& 
   case DPV:                                                                                            \
     hipLaunchKernelGGL((k_scan<M, DPV, HET, NCB, NBUF, T2, WIDE>), dim3(grid), dim3(SCAN_THREADS), 0, s, J.X,\
                        J.ldx, J.d, n_rows, rows, rows_count, static_cast<const CE*>(cl), W.nc, k_pad,  \
-                       W.cmax, W.cmax + (M::SPLIT ? 2 : 3), het, J.k, W.rec, st);                                     \
+                       W.cmax, W.cmax + 1, het, J.k, W.rec, st);                                     \
     break;
     GEEK_SCAN_CASE(32)
     GEEK_SCAN_CASE(64)
@@ -986,11 +963,11 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
     hipLaunchKernelGGL(k_gather_t, dim3(ceil_div(nmp, GT_TILE), ceil_div(J.d, GT_TILE)), dim3(256), 0, s, J.X,
                        J.ldx, J.n, J.d, J.seed_offsets, J.k, J.seed_members, J.n_members, nmp, W.xt, st);
     hipLaunchKernelGGL(k_centroids_t, dim3(ceil_div((int64_t)J.k * J.d, 256)), dim3(256), 0, s, W.xt,
-                       J.n_members, J.d, J.seed_offsets, J.k, J.centroids, W.cmax + 2, st);
+                       J.n_members, J.d, J.seed_offsets, J.k, J.centroids, W.cmax + 1, st);
   } else {
     hipLaunchKernelGGL(k_centroids, dim3(ceil_div((int64_t)J.k * J.d, 256)), dim3(256), 0, s, J.X,
                        J.ldx, J.n, J.d, J.seed_offsets, J.seed_members, J.k, J.k_dev, J.centroids,
-                       W.cmax + 2, st);
+                       W.cmax + 1, st);
   }
   if (C.het_on) {
     if (int32_t rc = modes_compute(reinterpret_cast<const uint32_t*>(J.cat), J.n_cat, J.n_cat, J.n,
@@ -1000,16 +977,10 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
                        J.n_cat, k_pad, W.mode16);
   }
   hipLaunchKernelGGL(k_cprep<ModeF32>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d, k_pad,
-                     DP, W.cl32, W.nc, W.cmax, W.cmax + 2, J.k_dev);
-  if (J.precision == GEEK_PREC_BF16) {
+                     DP, W.cl32, W.nc, W.cmax, W.cmax + 1, J.k_dev);
+  if (low_precision(J))
     hipLaunchKernelGGL(k_cprep<ModeBF16>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d,
-                       k_pad, DP, static_cast<__bf16*>(W.cllow), nullptr, nullptr, W.cmax + 3, J.k_dev);
-  } else if (J.precision == GEEK_PREC_FP8) {
-    hipLaunchKernelGGL(k_absmax_x, dim3(1024), dim3(256), 0, s, J.X, J.ldx, J.n, J.d, W.cmax + 1);
-    hipLaunchKernelGGL(k_fp8_scale, dim3(1), dim3(1), 0, s, W.cmax + 1, W.cmax + 2, W.cmax + 3);
-    hipLaunchKernelGGL(k_cprep<ModeFP8>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d,
-                       k_pad, DP, static_cast<uint8_t*>(W.cllow), nullptr, nullptr, W.cmax + 3, J.k_dev);
-  }
+                       k_pad, DP, static_cast<__bf16*>(W.cllow), nullptr, nullptr, W.cmax + 1, J.k_dev);
   GEEK_LAUNCH_CHECK();
   return GEEK_OK;
 }
@@ -1019,18 +990,11 @@ static int esc_grid(int64_t n, int rows_per_group) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(1024, ceil_div(n, rows_per_group)));
 }
 
-static bool low_precision(const geek_assign_job& J) {
-  return J.precision == GEEK_PREC_BF16 || J.precision == GEEK_PREC_FP8;
-}
-
 // The first pass of one job: every row gets a candidate record.
 static void assign_first_pass(const geek_assign_job& J, AssignCtx& C, int32_t* st, hipStream_t s) {
-  if (J.precision == GEEK_PREC_BF16) {
+  if (low_precision(J)) {
     const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeBF16>(C.het_on));
     scan_any<ModeBF16>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cllow, C.W, C.k_pad, C.het, st);
-  } else if (J.precision == GEEK_PREC_FP8) {
-    const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeFP8>(C.het_on));
-    scan_any<ModeFP8>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cllow, C.W, C.k_pad, C.het, st);
   } else {
     const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeF32>(C.het_on));
     scan_any<ModeF32>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl32, C.W, C.k_pad, C.het, st);
@@ -1043,7 +1007,7 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
   AssignWs& W = C.W;
   unsigned long long* ctr = W.ctr;
   const int fz_grid = (int)std::min<int64_t>(ceil_div(J.n, 4 * FZ_ROWS), 8192);
-  const int rstride = J.precision == GEEK_PREC_BF16 ? RECW_T2 : RECW;
+  const int rstride = low_precision(J) ? RECW_T2 : RECW;
   // eight lanes per row for the BF16 records of large jobs (10^7 rows at
   // d = 128: 3.3 against 4.0 ms); the batched workload's jobs (10^3 .. 10^6
   // rows on four streams) ran 36 ms slower in all with it than with a lane
@@ -1162,7 +1126,7 @@ int32_t assign_euclid_batch(const geek_assign_job* jobs, int njobs, void* ws, si
       e.cl = low ? W.cllow : static_cast<const void*>(W.cl32);
       e.nc = W.nc;
       e.cmax = W.cmax;
-      e.scale = W.cmax + (low ? 3 : 2);
+      e.cabs = W.cmax + 1;
       e.rec = W.rec;
       e.tile_begin = total;
       e.d = J.d;

@@ -14,7 +14,7 @@ namespace geek {
 template <int V>
 using IC = std::integral_constant<int, V>;
 
-constexpr int TCAND = 8;       // candidates per lane window, BF16/FP8 passes
+constexpr int TCAND = 8;       // candidates per lane window, float32 first pass
 constexpr int TCAND32 = 32;    // float32 pass (also the rescan of ambiguous rows)
 constexpr int RECW = TCAND32 + 1;  // candidate record per row: count, then ids
 constexpr int RECW_T2 = 2;         // the BF16 pass's record: 1 and the index, or -1
@@ -36,7 +36,7 @@ struct ModeF32 {
   };
   static constexpr int KPER = 8;
   static constexpr int KB = 16;   // products per fresh-accumulator block (0 = one chain)
-  static constexpr bool SCALED = true, SPLIT = true;
+  static constexpr bool SPLIT = true;
   using ce = uint32_t;            // 4 bytes per element: per 8, 16 bytes of hi then 16 of lo
   using frag = frag16;
   static constexpr double UX = 0x1p-22;
@@ -74,7 +74,7 @@ struct ModeF32 {
 struct ModeBF16 {
   static constexpr int KPER = 8;
   static constexpr int KB = 0;  // input rounding (2^-8) dominates the accumulation
-  static constexpr bool SCALED = false, SPLIT = false;
+  static constexpr bool SPLIT = false;
   using ce = __bf16;
   using frag = bf16x8;
   static constexpr double UX = 0x1p-8;  // conservative for any rounding to bf16
@@ -99,37 +99,6 @@ struct ModeBF16 {
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = (__bf16)0.0f;
   }
-};
-
-// e4m3 inputs, scaled by a power of two into the normal range; products are
-// exact in float32.  Relative rounding 2^-3 (conservative), absolute error
-// 2^-10 per element in scaled units (half the smallest subnormal spacing of
-// either e4m3 variant).
-struct ModeFP8 {
-  static constexpr int KPER = 8;
-  static constexpr int KB = 0;
-  static constexpr bool SCALED = true, SPLIT = false;
-  using ce = uint8_t;
-  using frag = long;
-  static constexpr double UX = 0x1p-3;
-  static constexpr double UC = 0x1p-3;
-  static constexpr double A0 = 0x1p-10, DROP = 0.0;
-  GEEK_HD static float scale_of(float scale) { return scale; }
-  GEEK_D static f32x16 mma(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a, b, c, 0, 0, 0);
-  }
-  GEEK_D static frag load_lds(const ce* p) { return *reinterpret_cast<const long*>(p); }
-  GEEK_D static frag from_f32(const float* v, float sc) {
-    int lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[0] * sc, v[1] * sc, 0, false);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[2] * sc, v[3] * sc, lo, true);
-    int hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[4] * sc, v[5] * sc, 0, false);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[6] * sc, v[7] * sc, hi, true);
-    return (long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
-  }
-  GEEK_D static void store(ce* p, const float* v, float sc) {
-    *reinterpret_cast<long*>(p) = from_f32(v, sc);
-  }
-  GEEK_D static void store_zero(ce* p) { *reinterpret_cast<long*>(p) = 0; }
 };
 
 // Categorical part of heterogeneous rows (cat == nullptr: Euclidean only).
@@ -197,7 +166,7 @@ __device__ __forceinline__ void scan_tiles(
     const float* __restrict__ X, int64_t ldx, int d, int64_t n_rows,
     const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
     const typename M::ce* __restrict__ cl, const float* __restrict__ nc, int k_pad,
-    const float* __restrict__ cmax_p, const float* __restrict__ scale_p, Het het, int k,
+    const float* __restrict__ cmax_p, const float* __restrict__ cabs_p, Het het, int k,
     int32_t* __restrict__ rec, int32_t* st, int64_t tile0, int64_t tile_end, int64_t tstep) {
   using CE = typename M::ce;
   // centroids per stage: half as many where an element takes four bytes and
@@ -247,11 +216,10 @@ __device__ __forceinline__ void scan_tiles(
 
   const int64_t count = rows ? (int64_t)*rows_count : n_rows;
   const double cm = (double)*cmax_p;
-  const float sc = M::SCALED ? M::scale_of(*scale_p) : 1.0f;
-  const float m2s = M::SPLIT ? 1.0f : -2.0f / (sc * sc);  // power of two: exact rescaling
-  // T2 starts every accumulator at -s^2 |c_j|^2 / 2 (exact power-of-two
-  // scalings), so acc = s^2 (x.c - |c_j|^2 / 2) and v_j = m2s * acc
-  const float nc_mul = T2 ? -0.5f * sc * sc : 1.0f;
+  const float sc = M::SPLIT ? M::scale_of(*cabs_p) : 1.0f;
+  // T2 starts every accumulator at -|c_j|^2 / 2, so acc = x.c - |c_j|^2 / 2
+  // and v_j = m2s * acc
+  const float m2s = -2.0f, nc_mul = T2 ? -0.5f : 1.0f;
   // padded centroids (|c|^2 = +inf) start T2 accumulators at -FLT_MAX / 4:
   // far below any real value, and finite even after the heterogeneous
   // epilogue doubles it (an infinity would turn into a NaN once the index
@@ -379,7 +347,7 @@ __device__ __forceinline__ void scan_tiles(
       twoeps[cb] = two_eps<M, DP, T2, BLK>(sqrt(nrm) * (1.0 + 1e-12), cm, 1.0 / sx, 1.0 / sc, het_max);
       if constexpr (HET) {
 #pragma unroll
-        for (int a = 0; a < MAX_CAT; ++a)
+        for (int a = 0; a < MAX_CAT; ++a)  // zero past n_cat, as mode16
           crow[cb][a] = (valid[cb] && a < het.n_cat) ? het.cat[i * het.n_cat + a] : 0;
       }
     }
@@ -478,6 +446,26 @@ __device__ __forceinline__ void scan_tiles(
 #pragma unroll
         for (int s = 0; s < S; ++s) af[s] = afrag_rb(0, s);
       }
+      // attributes of the lane's row that differ from the modes of the block's
+      // 16 seeds the lane holds, four attributes at a time (both sides are zero
+      // past n_cat).  With all attributes of a seed at once the compiler kept
+      // every seed's modes live: over 350 registers, one wavefront per SIMD.
+      [[maybe_unused]] auto count_mismatches = [&](int cb, int jb, int (&mm)[16]) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mm[r] = 0;
+#pragma unroll
+        for (int q = 0; q < MAX_CAT; q += 4) {
+          if (q < het.n_cat) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const uint4 md = *reinterpret_cast<const uint4*>(
+                  mbuf(IC<cur>{}) + (jb + (r >> 2) * 8 + h * 4 + (r & 3)) * MAX_CAT + q);
+              mm[r] += ((uint32_t)crow[cb][q] != md.x) + ((uint32_t)crow[cb][q + 1] != md.y) +
+                       ((uint32_t)crow[cb][q + 2] != md.z) + ((uint32_t)crow[cb][q + 3] != md.w);
+            }
+          }
+        }
+      };
       // first pass of point rows (top two, no categorical part): both 32-row
       // blocks of the stage go to the matrix cores back to back, into two
       // accumulator sets, so the first block's epilogue runs while the
@@ -663,22 +651,14 @@ __device__ __forceinline__ void scan_tiles(
           const int gblk = it * (BC / 32) + rb;
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) {
-            float t[16];
+            f32x16 tv = acc[cb];
+            if constexpr (HET) {
+              // -(v_num + gamma * mismatches), one rounding
+              int mm[16];
+              count_mismatches(cb, jb, mm);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              t[r] = acc[cb][r];
-              if constexpr (HET) {
-                // -(v_num + gamma * mismatches), one rounding
-                const uint32_t* md = mbuf(IC<cur>{}) + (jb + (r >> 2) * 8 + h * 4 + (r & 3)) * MAX_CAT;
-                int mm = 0;
-#pragma unroll
-                for (int q = 0; q < MAX_CAT; ++q) mm += (q < het.n_cat && (uint32_t)crow[cb][q] != md[q]) ? 1 : 0;
-                t[r] = __builtin_fmaf(-m2s, t[r], -het.gamma_f * (float)mm);
-              }
+              for (int r = 0; r < 16; ++r) tv[r] = __builtin_fmaf(-m2s, tv[r], -het.gamma_f * (float)mm[r]);
             }
-            f32x16 tv;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) tv[r] = t[r];
             t2_update(cb, tv, gblk);
           }
         } else {
@@ -690,17 +670,15 @@ __device__ __forceinline__ void scan_tiles(
           float v[16];
           float vmin = INFINITY;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            v[r] = __builtin_fmaf(m2[cb], acc[cb][r], ncv[r]);
-            if constexpr (HET) {
-              const uint32_t* md = mbuf(IC<cur>{}) + (jb + (r >> 2) * 8 + h * 4 + (r & 3)) * MAX_CAT;
-              int mm = 0;
+          for (int r = 0; r < 16; ++r) v[r] = __builtin_fmaf(m2[cb], acc[cb][r], ncv[r]);
+          if constexpr (HET) {
+            int mm[16];
+            count_mismatches(cb, jb, mm);
 #pragma unroll
-              for (int a = 0; a < MAX_CAT; ++a) mm += (a < het.n_cat && (uint32_t)crow[cb][a] != md[a]) ? 1 : 0;
-              v[r] = v[r] + het.gamma_f * (float)mm;
-            }
-            vmin = fminf(vmin, v[r]);
+            for (int r = 0; r < 16; ++r) v[r] = v[r] + het.gamma_f * (float)mm[r];
           }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) vmin = fminf(vmin, v[r]);
           if (vmin <= thr[cb]) {
             float* lv = lds_lv + (tid * NCB + cb) * TC;
             int* lj = lds_lj + (tid * NCB + cb) * TC;
@@ -847,7 +825,7 @@ struct ScanJob {
   const void* cl;
   const float* nc;
   const float* cmax;
-  const float* scale;
+  const float* cabs;
   int32_t* rec;
   int64_t tile_begin;  // first global tile of this job
   int d, k, k_pad, pad0;
@@ -884,7 +862,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_batch(const ScanJob* __re
     const int64_t tile = gt - J.tile_begin;
     scan_tiles<M, DP, false, NCB, NBUF, T2, false>(J.X, J.ldx, J.d, J.n, nullptr, nullptr,
                                             static_cast<const typename M::ce*>(J.cl), J.nc, J.k_pad, J.cmax,
-                                            J.scale, none, J.k, J.rec, st, tile, tile + 1, 1);
+                                            J.cabs, none, J.k, J.rec, st, tile, tile + 1, 1);
   }
 }
 
