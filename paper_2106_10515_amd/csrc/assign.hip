@@ -199,35 +199,38 @@ static bool centroids_transposed(const geek_assign_job& J) {
 }
 static int64_t members_pad(const geek_assign_job& J) { return (J.n_members + 3) / 4 * 4; }
 
-// Matrix-core input copies of the centroids, zero-padded to [k_pad][DP];
-// padded rows get |c|^2 = +inf so they never enter a window.
-template <class M>
-__global__ void k_cprep(const double* __restrict__ C, int k, int d, int k_pad, int DP,
-                        typename M::ce* __restrict__ cl, float* __restrict__ nc, float* __restrict__ cmax,
-                        const float* __restrict__ cabs_p, const uint32_t* __restrict__ kdev) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
+// Matrix-core input copies of the centroids, zero-padded to [k_pad][DP]: the
+// float32 pieces, and with `low` the bf16 copy of a bf16 first pass.  A thread
+// takes eight attributes of a centroid, the DP / 8 threads of a centroid are
+// neighbours in a wavefront (a thread per centroid, walking its row, took 7 us
+// at k = 10 and one launch per copy).  Padded rows get |c|^2 = +inf so they
+// never enter a window.  |c|^2 may be summed in any order (two_eps).
+__global__ __launch_bounds__(256) void k_cprep(const double* __restrict__ C, int k, int d, int k_pad, int DP,
+                                               uint32_t* __restrict__ cl32, __bf16* __restrict__ low,
+                                               float* __restrict__ nc, float* __restrict__ cmax,
+                                               const float* __restrict__ cabs_p, const uint32_t* __restrict__ kdev) {
+  const int G = DP / 8;  // 4, 8, 16 or 32: all threads of a centroid are in one wavefront
+  const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int j = (int)(gid / G), t = (int)(gid % G) * 8;
   if (j >= k_pad) return;
-  const float sc = M::SPLIT ? M::scale_of(*cabs_p) : 1.0f;
   // seeds past a device-side count are padding too
-  if (j >= (kdev ? (int)min(*kdev, (uint32_t)k) : k)) {
-    for (int t = 0; t < DP; t += M::KPER) M::store_zero(cl + (int64_t)j * DP + t);
-    if (nc) nc[j] = INFINITY;
-    return;
-  }
+  const bool real = j < (kdev ? (int)min(*kdev, (uint32_t)k) : k);
+  float v[8];
   double sq = 0.0;
-  float v[M::KPER];
-  for (int t = 0; t < DP; t += M::KPER) {
 #pragma unroll
-    for (int e = 0; e < M::KPER; ++e) {
-      const double c = t + e < d ? C[(int64_t)j * d + t + e] : 0.0;
-      sq = __dadd_rn(sq, __dmul_rn(c, c));
-      v[e] = (float)c;
-    }
-    M::store(cl + (int64_t)j * DP + t, v, sc);
+  for (int e = 0; e < 8; ++e) {
+    const double c = real && t + e < d ? C[(int64_t)j * d + t + e] : 0.0;
+    sq += c * c;
+    v[e] = (float)c;
   }
-  if (nc) {
-    nc[j] = (float)sq;
-    atomic_max_nonneg(cmax, (float)(sqrt(sq) * (1.0 + 0x1p-20)));
+  for (int o = 1; o < G; o <<= 1) sq += __shfl_xor(sq, o);
+  ModeF32::store(cl32 + (int64_t)j * DP + t, v, ModeF32::scale_of(*cabs_p));
+  if (low) ModeBF16::store(low + (int64_t)j * DP + t, v, 1.0f);
+  if (t == 0) {
+    nc[j] = real ? (float)sq : INFINITY;
+    const float norm = (float)(sqrt(sq) * (1.0 + 0x1p-20));
+    if (real && norm > __hip_atomic_load(cmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomic_max_nonneg(cmax, norm);
   }
 }
 
@@ -708,35 +711,68 @@ __global__ void k_fb_merge(const uint32_t* __restrict__ rows, const uint32_t* __
 }
 
 // ---------------------------------------------------------------- SSE, radius
-// One wavefront per 4096-row block: a coalesced copy into LDS, then one lane
-// adds the block's values in row order (the reference summation order).
-__global__ __launch_bounds__(64) void k_sse_blocks(const double* __restrict__ dist, int64_t n,
-                                                   double* __restrict__ blk) {
-  __shared__ double v[SSE_BLOCK];
+// acc + v[0] + ... + v[cnt - 1], one addition at a time (the reference order),
+// from LDS: the next sixteen values load while sixteen are added, so that the
+// chain waits for additions only (4,096 values: 48 us with a load per
+// addition, 37 us so; the addition itself takes about 9 ns in a chain).
+GEEK_D double chain_add(const double* v, int cnt, double acc) {
+  constexpr int G = 16;
+  double a[G], b[G];
+  int i = 0;
+  if (cnt >= G)
+#pragma unroll
+    for (int u = 0; u < G; ++u) a[u] = v[u];
+  for (; i + 2 * G <= cnt; i += 2 * G) {
+#pragma unroll
+    for (int u = 0; u < G; ++u) b[u] = v[i + G + u];
+#pragma unroll
+    for (int u = 0; u < G; ++u) acc = __dadd_rn(acc, a[u]);
+    if (i + 3 * G <= cnt)
+#pragma unroll
+      for (int u = 0; u < G; ++u) a[u] = v[i + 2 * G + u];
+#pragma unroll
+    for (int u = 0; u < G; ++u) acc = __dadd_rn(acc, b[u]);
+  }
+  for (; i < cnt; ++i) acc = __dadd_rn(acc, v[i]);
+  return acc;
+}
+
+// One workgroup per 4096-row block: a coalesced copy into LDS, then one lane
+// adds the block's values in row order.
+__global__ __launch_bounds__(256) void k_sse_blocks(const double* __restrict__ dist, int64_t n,
+                                                    double* __restrict__ blk) {
+  __shared__ __attribute__((aligned(16))) double v[SSE_BLOCK];
   const int64_t b = blockIdx.x;
   const int64_t s = b * SSE_BLOCK;
   const int cnt = (int)(n - s < SSE_BLOCK ? n - s : SSE_BLOCK);
-  for (int i = threadIdx.x; i < cnt; i += 64) v[i] = dist[s + i];
+  for (int i = threadIdx.x; i < cnt; i += 256) v[i] = dist[s + i];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double acc = 0.0;
-    for (int i = 0; i < cnt; ++i) acc = __dadd_rn(acc, v[i]);
-    blk[b] = acc;
-  }
+  if (threadIdx.x == 0) blk[b] = chain_add(v, cnt, 0.0);
 }
 
-__global__ void k_sse_total(const double* __restrict__ blk, int64_t nb, double* __restrict__ out) {
-  if (blockIdx.x || threadIdx.x) return;
+__global__ __launch_bounds__(256) void k_sse_total(const double* __restrict__ blk, int64_t nb, double* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) double v[SSE_BLOCK];
   double acc = 0.0;
-  for (int64_t b = 0; b < nb; ++b) acc = __dadd_rn(acc, blk[b]);
-  *out = acc;
+  for (int64_t s = 0; s < nb; s += SSE_BLOCK) {
+    const int cnt = (int)(nb - s < SSE_BLOCK ? nb - s : SSE_BLOCK);
+    __syncthreads();
+    for (int i = threadIdx.x; i < cnt; i += 256) v[i] = blk[s + i];
+    __syncthreads();
+    if (threadIdx.x == 0) acc = chain_add(v, cnt, acc);
+  }
+  if (threadIdx.x == 0) *out = acc;
 }
+
+// Radii start at zero (k_fill_f64 or k_assign_init).  The square root is
+// correctly rounded and monotone, so the largest root is the root of the
+// largest distance.
+GEEK_D double radius_of(double dist, int take_sqrt) { return take_sqrt ? sqrt(dist) : dist; }
 
 __global__ void k_radius(const int32_t* __restrict__ assign, const double* __restrict__ dist,
-                         int64_t n, int k, double* __restrict__ rad) {
+                         int64_t n, int k, int take_sqrt, double* __restrict__ rad) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= n || (unsigned)assign[i] >= (unsigned)k) return;
-  const double v = dist[i];
+  const double v = radius_of(dist[i], take_sqrt);
   double* slot = rad + assign[i];
   if (v > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
     atomic_max_nonneg(slot, v);
@@ -748,7 +784,7 @@ __global__ void k_radius(const int32_t* __restrict__ assign, const double* __res
 constexpr int RAD_LDS = 4096, RAD_LDS_BIG = 16384;
 template <int CAP>
 __global__ __launch_bounds__(256) void k_radius_lds(const int32_t* __restrict__ assign,
-                                                    const double* __restrict__ dist, int64_t n, int k,
+                                                    const double* __restrict__ dist, int64_t n, int k, int take_sqrt,
                                                     double* __restrict__ rad) {
   __shared__ unsigned long long m[CAP];
   for (int j = threadIdx.x; j < k; j += 256) m[j] = 0ull;
@@ -759,12 +795,40 @@ __global__ __launch_bounds__(256) void k_radius_lds(const int32_t* __restrict__ 
   }
   __syncthreads();
   for (int j = threadIdx.x; j < k; j += 256)
-    if (m[j]) atomic_max_nonneg(rad + j, __longlong_as_double((long long)m[j]));
+    if (m[j]) atomic_max_nonneg(rad + j, radius_of(__longlong_as_double((long long)m[j]), take_sqrt));
 }
 
-__global__ void k_sqrt_inplace(double* __restrict__ v, int k, int do_sqrt) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < k && do_sqrt) v[j] = sqrt(v[j]);
+// Both for one block of rows and at most SMALL_K clusters.
+constexpr int SMALL_K = 2048;
+__global__ __launch_bounds__(256) void k_sse_radius_small(const double* __restrict__ dist,
+                                                          const int32_t* __restrict__ assign, int n, int k,
+                                                          double* __restrict__ sse, double* __restrict__ radius,
+                                                          int take_sqrt) {
+  __shared__ __attribute__((aligned(16))) double v[SSE_BLOCK];
+  __shared__ unsigned long long m[SMALL_K];
+  for (int j = threadIdx.x; j < k; j += 256) m[j] = 0ull;
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += 256) {
+    const double x = dist[i];
+    const int a = assign[i];
+    v[i] = x;
+    if ((unsigned)a < (unsigned)k) atomicMax(&m[a], (unsigned long long)__double_as_longlong(x));
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *sse = 0.0 + chain_add(v, n, 0.0);
+  if (radius)
+    for (int j = threadIdx.x; j < k; j += 256) radius[j] = radius_of(__longlong_as_double((long long)m[j]), take_sqrt);
+}
+
+// Zeroes a job's counters, row counts, maxima and radii.
+__global__ void k_assign_init(uint32_t* counts, unsigned long long* ctr, float* cmax, double* radius, int k) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i < 4) {
+    counts[i] = 0u;
+    ctr[i] = 0ull;
+    cmax[i] = 0.f;
+  }
+  if (radius && i < k) radius[i] = 0.0;
 }
 
 __global__ void k_pad_modes(const uint32_t* __restrict__ mode, int k, int n_cat, int k_pad,
@@ -775,38 +839,33 @@ __global__ void k_pad_modes(const uint32_t* __restrict__ mode, int k, int n_cat,
   out[g] = (j < k && a < n_cat) ? mode[(int64_t)j * n_cat + a] : 0u;
 }
 
-__global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
 __global__ void k_fill_f64(double* p, int64_t n, double v) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
-__global__ void k_copy_u64(const unsigned long long* a, unsigned long long* b, int n) {
-  const int i = threadIdx.x;
-  if (i < n) b[i] = a[i];
-}
-
 // ---------------------------------------------------------------- host side
 // SSE over 4096-row blocks and the per-cluster radius (sqrt of the largest
-// member distance when `take_sqrt`), shared by every metric.
+// member distance when `take_sqrt`), shared by every metric.  `zeroed`: the
+// radii are already zero.
 void sse_and_radius(const double* dist, const int32_t* assign, int64_t n, int k, double* sse, double* radius,
-                    int take_sqrt, double* sse_blk, hipStream_t s) {
+                    int take_sqrt, double* sse_blk, bool zeroed, hipStream_t s) {
+  if (n <= SSE_BLOCK && k <= SMALL_K) {  // one launch instead of three or four
+    hipLaunchKernelGGL(k_sse_radius_small, dim3(1), dim3(256), 0, s, dist, assign, (int)n, k, sse, radius, take_sqrt);
+    return;
+  }
   const int64_t nblk = (n + SSE_BLOCK - 1) / SSE_BLOCK;
-  hipLaunchKernelGGL(k_sse_blocks, dim3(nblk), dim3(64), 0, s, dist, n, sse_blk);
-  hipLaunchKernelGGL(k_sse_total, dim3(1), dim3(1), 0, s, sse_blk, nblk, sse);
+  hipLaunchKernelGGL(k_sse_blocks, dim3(nblk), dim3(256), 0, s, dist, n, sse_blk);
+  hipLaunchKernelGGL(k_sse_total, dim3(1), dim3(256), 0, s, sse_blk, nblk, sse);
   if (radius) {
-    hipLaunchKernelGGL(k_fill_f64, dim3(ceil_div(k, 256)), dim3(256), 0, s, radius, k, 0.0);
+    if (!zeroed) hipLaunchKernelGGL(k_fill_f64, dim3(ceil_div(k, 256)), dim3(256), 0, s, radius, k, 0.0);
     if (k <= RAD_LDS)
       hipLaunchKernelGGL(k_radius_lds<RAD_LDS>, dim3((int)std::min<int64_t>(ceil_div(n, 4096), 512)), dim3(256), 0,
-                         s, assign, dist, n, k, radius);
+                         s, assign, dist, n, k, take_sqrt, radius);
     else if (k <= RAD_LDS_BIG)  // 128 KB of LDS: one workgroup per CU, fewer of them
       hipLaunchKernelGGL(k_radius_lds<RAD_LDS_BIG>, dim3((int)std::min<int64_t>(ceil_div(n, 16384), 128)), dim3(256),
-                         0, s, assign, dist, n, k, radius);
+                         0, s, assign, dist, n, k, take_sqrt, radius);
     else
-      hipLaunchKernelGGL(k_radius, dim3(ceil_div(n, 256)), dim3(256), 0, s, assign, dist, n, k, radius);
-    hipLaunchKernelGGL(k_sqrt_inplace, dim3(ceil_div(k, 256)), dim3(256), 0, s, radius, k, take_sqrt);
+      hipLaunchKernelGGL(k_radius, dim3(ceil_div(n, 256)), dim3(256), 0, s, assign, dist, n, k, take_sqrt, radius);
   }
 }
 
@@ -955,9 +1014,9 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
   C.het_on = J.metric == GEEK_METRIC_HETERO;
   if (C.het_on) C.het = Het{J.cat, J.modes, W.mode16, J.n_cat, (float)J.gamma, J.gamma};
   const int DP = C.DP, k_pad = C.k_pad;
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, W.counts, 4, 0u);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(W.ctr), 8, 0u);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(W.cmax), 4, 0u);
+  if (J.counters) W.ctr = J.counters;  // counted in place
+  hipLaunchKernelGGL(k_assign_init, dim3(J.radius ? ceil_div(J.k, 256) : 1), dim3(256), 0, s, W.counts, W.ctr, W.cmax,
+                     J.radius, J.k);
   if (centroids_transposed(J)) {
     const int64_t nmp = members_pad(J);
     hipLaunchKernelGGL(k_gather_t, dim3(ceil_div(nmp, GT_TILE), ceil_div(J.d, GT_TILE)), dim3(256), 0, s, J.X,
@@ -976,11 +1035,9 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
     hipLaunchKernelGGL(k_pad_modes, dim3(ceil_div((int64_t)k_pad * MAX_CAT, 256)), dim3(256), 0, s, J.modes, J.k,
                        J.n_cat, k_pad, W.mode16);
   }
-  hipLaunchKernelGGL(k_cprep<ModeF32>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d, k_pad,
-                     DP, W.cl32, W.nc, W.cmax, W.cmax + 1, J.k_dev);
-  if (low_precision(J))
-    hipLaunchKernelGGL(k_cprep<ModeBF16>, dim3(ceil_div(k_pad, 128)), dim3(128), 0, s, J.centroids, J.k, J.d,
-                       k_pad, DP, static_cast<__bf16*>(W.cllow), nullptr, nullptr, W.cmax + 1, J.k_dev);
+  hipLaunchKernelGGL(k_cprep, dim3(ceil_div((int64_t)k_pad * (DP / 8), 256)), dim3(256), 0, s, J.centroids, J.k, J.d,
+                     k_pad, DP, W.cl32, low_precision(J) ? static_cast<__bf16*>(W.cllow) : nullptr, W.nc, W.cmax,
+                     W.cmax + 1, J.k_dev);
   GEEK_LAUNCH_CHECK();
   return GEEK_OK;
 }
@@ -1040,8 +1097,7 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
   }
   hipLaunchKernelGGL(k_fb_merge, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, W.fb, W.counts + 1, J.k, W.part_d,
                      W.part_j, J.assign, C.dist, ctr);
-  sse_and_radius(C.dist, J.assign, J.n, J.k, J.sse, J.radius, C.het_on ? 0 : 1, W.sse_blk, s);
-  if (J.counters) hipLaunchKernelGGL(k_copy_u64, dim3(1), dim3(64), 0, s, ctr, J.counters, 4);
+  sse_and_radius(C.dist, J.assign, J.n, J.k, J.sse, J.radius, C.het_on ? 0 : 1, W.sse_blk, true, s);
   if (J.t_done) {
     if (t0) hipLaunchKernelGGL(k_clock_since, dim3(1), dim3(64), 0, s, t0, J.t_done);
     else hipLaunchKernelGGL(k_clock_now, dim3(1), dim3(64), 0, s, J.t_done);

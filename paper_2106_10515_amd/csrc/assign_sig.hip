@@ -25,7 +25,7 @@
 namespace geek {
 
 void sse_and_radius(const double* dist, const int32_t* assign, int64_t n, int k, double* sse, double* radius,
-                    int take_sqrt, double* sse_blk, hipStream_t s);
+                    int take_sqrt, double* sse_blk, bool zeroed, hipStream_t s);
 size_t sse_blk_words(int64_t n);
 
 constexpr int SG_CAP = 2048;  // matched seeds held in LDS per row
@@ -871,7 +871,7 @@ int32_t assign_sig(const geek_assign_job& J, void* ws, size_t ws_bytes, int32_t*
                        W.small, (int64_t)0, J.assign, dist, W.ctr);
   }
   prof_end(GEEK_PROF_ASSIGN_SCAN, s);
-  sse_and_radius(dist, J.assign, J.n, k, J.sse, J.radius, 0, W.sse_blk, s);
+  sse_and_radius(dist, J.assign, J.n, k, J.sse, J.radius, 0, W.sse_blk, false, s);
   if (J.counters) hipLaunchKernelGGL(k_copy_ctr, dim3(1), dim3(64), 0, s, W.ctr, J.counters);
   prof_end(GEEK_PROF_ASSIGN, s);
   GEEK_LAUNCH_CHECK();

@@ -1,0 +1,67 @@
+"""GPU parity at the sizes where small calls take a path of their own: tables
+bucketized by one workgroup (up to 2,048 objects), SSE and radii of one block
+of rows (up to 4,096 rows and 2,048 clusters), and the next sizes up."""
+
+import numpy as np
+import pytest
+
+import oracle
+
+from .gpu_util import announce, cuda, gpu_api, host_u32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 511, 513, 2047, 2048, 2049])
+@pytest.mark.parametrize("kw,alphabet", [(1, 1), (1, 40), (2, 3), (3, 2**31), (4, 7)])
+def test_small_tables(n, kw, alphabet):
+    api = gpu_api()
+    g = np.random.default_rng(n * 5 + kw)
+    T = 3
+    keys = g.integers(0, alphabet, size=(T, n, kw)).astype(np.uint32)
+    announce(f"bucketize small n={n} kw={kw} alphabet={alphabet}")
+    for want in (True, False):
+        mem, off, nb, bof = api.bucketize(cuda(keys), n, T, kw, n * kw, kw, want_bucket_of=want)
+        assert (bof is not None) == want
+        for t in range(T):
+            rm, ro, rb = oracle.bucketize(keys[t].astype(np.int64))
+            assert int(nb[t]) == len(ro) - 1
+            assert np.array_equal(host_u32(mem[t]), rm)
+            assert np.array_equal(host_u32(off[t])[:len(ro)], ro)
+            if want:
+                assert np.array_equal(host_u32(bof[t]), rb)
+
+
+def test_small_tables_rows_of_a_wider_matrix():
+    # band layout: all tables' words in one row, rows wider than the bands
+    api = gpu_api()
+    g = np.random.default_rng(3)
+    n, T, kw, ld = 1500, 5, 3, 19
+    sig = g.integers(0, 4, size=(n, ld)).astype(np.uint32)
+    announce("bucketize small bands")
+    mem, off, nb, bof = api.bucketize(cuda(sig), n, T, kw, kw, ld)
+    for t in range(T):
+        rm, ro, rb = oracle.bucketize(sig[:, t * kw:(t + 1) * kw].astype(np.int64))
+        assert int(nb[t]) == len(ro) - 1
+        assert np.array_equal(host_u32(mem[t]), rm) and np.array_equal(host_u32(off[t])[:len(ro)], ro)
+        assert np.array_equal(host_u32(bof[t]), rb)
+
+
+@pytest.mark.parametrize("n,k", [(1, 1), (31, 3), (33, 33), (4095, 5), (4096, 2048), (4096, 2049), (4097, 7),
+                                 (8191, 40), (8209, 4097)])
+def test_sse_and_radius_sizes(n, k):
+    api = gpu_api()
+    g = np.random.default_rng(n + k)
+    X = g.normal(size=(n, 3)).astype(np.float32)
+    ids = g.integers(0, n, size=k)
+    so, sm = np.arange(k + 1, dtype=np.uint32), ids.astype(np.uint32)
+    announce(f"sse n={n} k={k}")
+    C = oracle.centroids(X, so, sm)
+    a, dist = oracle.assign_euclid(X, C)
+    for prec in (0, 1):
+        out = api.assign_euclid(cuda(X), cuda(so), cuda(sm), k, prec)
+        assert np.array_equal(out["assign"].cpu().numpy(), a)
+        assert out["sse"].item() == oracle.sse(dist)
+        assert np.array_equal(out["radius"].cpu().numpy(), oracle.radius(dist, a, k))
+        again = api.assign_euclid(cuda(X), cuda(so), cuda(sm), k, prec, want_radius=False, want_dist=False)
+        assert again["sse"].item() == oracle.sse(dist)
