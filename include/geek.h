@@ -217,7 +217,9 @@ typedef struct geek_bucketize_job {
  * GEEK_ERR_NO_SEEDS.  The call never reads sizes back to the host.
  * Requires 1 <= T <= 128 (GEEK_ERR_UNSUPPORTED above), T * n < 2^31 and a C
  * capacity below 2^31.  The workspace grows with T * n (about 100 bytes per
- * (table, object)) and with the C capacity (about 50 bytes per member).
+ * (table, object); small jobs process several SILK tables at a time, about 70
+ * bytes per (table, object) and further SILK table up to T * n = 2^23 in all)
+ * and with the C capacity (about 50 bytes per member).
  */
 typedef struct geek_silk_job {
   int64_t n;                /* objects */

@@ -8,7 +8,9 @@
 //                     the open-addressing table, zeroed counters
 //   k_extent          start and size of every bucket in the member array
 //   k_mark_starts, scan, k_bucket_of   the global bucket of every (table, object)
-// For each SILK table:
+// For a batch of SILK tables at a time (blockIdx.y = the table in the batch; as
+// many tables as keep the batch's arrays below SILK_BATCH entries, so small
+// jobs take all tables in one batch and large ones one table per batch):
 //   k_sig / k_sig_big G(B) = (min_{x in B} pi_k(x))_k for every bucket, with the
 //                     hash evaluations counted as they are made
 //   k_ht_*            bins = buckets with identical G: an open-addressing table
@@ -19,13 +21,14 @@
 //                     in exactly one bucket per table and its count in a bin is
 //                     the number of those T buckets that the bin holds.
 //   k_emit_flags, scans, k_commit   C_shared sizes, delta, room left in C
-//   k_count_kept, scan, k_kept_pairs, radix sort by bin, k_c_write
-//                     the new sets of C, ids ascending
+//   k_count_kept, scan, k_kept_pairs, radix sort by set, k_c_write
+//                     the batch's new sets of C, ids ascending
 // De-duplication (one more table over the sets of C): sets sorted by their
 // K-tuple (radix sort) so that runs of equal tuples are the bins, in
 // ascending lexicographic order; a bin of one set passes it through, a bin of
 // several sets is majority-voted ((bin, id) pairs sorted and counted) and
 // delta-filtered; the seeds are written in bin order.
+#include <algorithm>
 #include <vector>
 
 #include "common.hpp"
@@ -37,21 +40,31 @@ constexpr int SK_BIG = 64;       // buckets larger than this are hashed by a wav
 constexpr int SG_GRID = 2048;    // blocks of the grid-stride kernels
 constexpr int SV_LDS = 8192;     // LDS entries (two words each) of a vote block
 constexpr int SILK_MAX_T = 128;  // transform tables the vote kernel holds in LDS
+// Entries (T n) of the tables processed together.  20,000 points, 16 tables:
+// one table at a time, the 900 launches of a call set its time (4.3 ms; 32
+// tables of 10^6 points, 32 10^6 entries, are bound by their memory accesses).
+constexpr int64_t SILK_BATCH = 1 << 23;
 
 // Device-side sizes and counters of one call.
 struct SilkState {
   unsigned long long hash_evals, pairs, multi, need_s, need_m;
   uint32_t nb;       // buckets of all tables
   uint32_t ht_mask;  // open-addressing table: mask + 1 slots in use
-  uint32_t big;      // buckets queued for k_sig_big
-  uint32_t es, em;   // this table's emitted sets / members
-  uint32_t kp;       // this table's kept (bin, id) pairs of emitted bins
+  uint32_t big;      // sets queued for k_sig_big (de-duplication)
+  uint32_t kp;       // the batch's kept (set, id) pairs of emitted bins
   uint32_t cs, cm;   // sets / members of C committed so far
   uint32_t over;     // C ran out of room
-  uint32_t fit;      // this table's sets are written to C
-  uint32_t base_s, base_m;
+  uint32_t cm0;      // members of C before the batch
   // de-duplication
   uint32_t nb2, P2, R2, kept2, k, tot_m, fit_out;
+};
+
+// One SILK table of a batch.
+struct SilkTable {
+  uint32_t big;             // buckets queued for k_sig_big
+  uint32_t fit;             // the table's sets are written to C
+  uint32_t base_s, base_m;  // its first set / member of C
+  uint32_t e0, m0;          // the scans' values at its first bucket
 };
 
 GEEK_D uint32_t gtid() { return blockIdx.x * blockDim.x + threadIdx.x; }
@@ -134,9 +147,14 @@ __global__ void k_bucket_of(const uint32_t* __restrict__ members, int64_t Tn, in
 __global__ __launch_bounds__(256) void k_sig(const uint32_t* __restrict__ mem, const uint32_t* __restrict__ gstart,
                                              const uint32_t* __restrict__ gsize, const uint32_t* __restrict__ count,
                                              const uint32_t* __restrict__ keys, int K, uint32_t* __restrict__ G,
-                                             uint32_t* __restrict__ big_list, uint32_t* big_count,
-                                             unsigned long long* evals) {
+                                             uint32_t* __restrict__ big_list, uint32_t* big_count, int big_stride,
+                                             int64_t stride, unsigned long long* evals) {
   const uint32_t ns = *count;
+  // table blockIdx.y of a batch: its keys, G, queue and queue length
+  keys += 2 * (int64_t)blockIdx.y * K;
+  G += (int64_t)blockIdx.y * stride * K;
+  big_list += (int64_t)blockIdx.y * stride;
+  big_count += (int64_t)blockIdx.y * big_stride;
   uint32_t a[4], b[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -175,8 +193,12 @@ __global__ __launch_bounds__(256) void k_sig_big(const uint32_t* __restrict__ me
                                                  const uint32_t* __restrict__ gsize,
                                                  const uint32_t* __restrict__ keys, int K,
                                                  uint32_t* __restrict__ G, const uint32_t* big_list,
-                                                 const uint32_t* big_count, unsigned long long* evals) {
-  const uint32_t nbig = *big_count;
+                                                 const uint32_t* big_count, int big_stride, int64_t stride,
+                                                 unsigned long long* evals) {
+  keys += 2 * (int64_t)blockIdx.y * K;
+  G += (int64_t)blockIdx.y * stride * K;
+  big_list += (int64_t)blockIdx.y * stride;
+  const uint32_t nbig = big_count[(int64_t)blockIdx.y * big_stride];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint32_t nwave = (gridDim.x * blockDim.x) >> 6;
@@ -239,7 +261,14 @@ GEEK_D bool g_eq(const uint32_t* __restrict__ G, uint32_t a, uint32_t b, int K) 
 }
 
 __global__ void k_ht_clear(const SilkState* S, uint32_t* __restrict__ ht, uint32_t* __restrict__ binmin,
-                           uint32_t* __restrict__ bcount, uint32_t* __restrict__ ksize) {
+                           uint32_t* __restrict__ bcount, uint32_t* __restrict__ ksize, int64_t ht_stride,
+                           int64_t stride, SilkTable* __restrict__ tabs) {
+  const int64_t o = (int64_t)blockIdx.y * stride;
+  ht += (int64_t)blockIdx.y * ht_stride;
+  binmin += o;
+  bcount += o;
+  ksize += o;
+  if (gtid() == 0) tabs[blockIdx.y] = SilkTable{};
   const uint32_t NB = S->nb, slots = S->ht_mask + 1u;
   const uint32_t top = slots > NB ? slots : NB;
   for (uint32_t i = gtid(); i < top; i += gstride()) {
@@ -257,7 +286,10 @@ __global__ void k_ht_clear(const SilkState* S, uint32_t* __restrict__ ht, uint32
 // claimant's G is complete before this kernel starts), so no slot is ever
 // read before its key exists.  rep[g] = the claimant of g's G.
 __global__ void k_ht_insert(const uint32_t* __restrict__ G, int K, const SilkState* S, uint32_t* __restrict__ ht,
-                            uint32_t* __restrict__ rep) {
+                            uint32_t* __restrict__ rep, int64_t ht_stride, int64_t stride) {
+  G += (int64_t)blockIdx.y * stride * K;
+  ht += (int64_t)blockIdx.y * ht_stride;
+  rep += (int64_t)blockIdx.y * stride;
   const uint32_t NB = S->nb, mask = S->ht_mask;
   for (uint32_t g = gtid(); g < NB; g += gstride()) {
     uint32_t h = g_hash(G, g, K) & mask;
@@ -276,7 +308,11 @@ __global__ void k_ht_insert(const uint32_t* __restrict__ G, int K, const SilkSta
 }
 
 __global__ void k_ht_min(const uint32_t* __restrict__ rep, const SilkState* S, uint32_t* __restrict__ binmin,
-                         uint32_t* __restrict__ bcount) {
+                         uint32_t* __restrict__ bcount, int64_t stride) {
+  const int64_t o = (int64_t)blockIdx.y * stride;
+  rep += o;
+  binmin += o;
+  bcount += o;
   const uint32_t NB = S->nb;
   for (uint32_t g = gtid(); g < NB; g += gstride()) {
     const uint32_t r = rep[g];
@@ -290,7 +326,12 @@ __global__ void k_ht_min(const uint32_t* __restrict__ rep, const SilkState* S, u
 __global__ __launch_bounds__(256) void k_bin_info(const uint32_t* __restrict__ rep,
                                                   const uint32_t* __restrict__ binmin,
                                                   const uint32_t* __restrict__ bcount, SilkState* S,
-                                                  uint2* __restrict__ info) {
+                                                  uint2* __restrict__ info, int64_t stride) {
+  const int64_t o = (int64_t)blockIdx.y * stride;
+  rep += o;
+  binmin += o;
+  bcount += o;
+  info += o;
   const uint32_t NB = S->nb;
   unsigned long long multi = 0;
   for (uint32_t g = gtid(); g < NB; g += gstride()) {
@@ -311,7 +352,11 @@ __global__ __launch_bounds__(256) void k_bin_info(const uint32_t* __restrict__ r
 __global__ __launch_bounds__(256) void k_vote(const uint32_t* __restrict__ bof, const uint2* __restrict__ info,
                                               int64_t n, int T, uint32_t* __restrict__ kbin,
                                               uint32_t* __restrict__ kc, uint32_t* __restrict__ ksize,
-                                              SilkState* S) {
+                                              SilkState* S, int64_t stride, int64_t kstride) {
+  info += (int64_t)blockIdx.y * stride;
+  ksize += (int64_t)blockIdx.y * stride;
+  kbin += (int64_t)blockIdx.y * kstride;
+  kc += (int64_t)blockIdx.y * n;
   extern __shared__ uint32_t vl[];  // [2][T][blockDim.x]: bin id, bin size
   const int VT = blockDim.x;
   uint32_t* lb = vl;
@@ -362,7 +407,11 @@ template <int TT>
 __global__ __launch_bounds__(256) void k_vote_reg(const uint32_t* __restrict__ bof, const uint2* __restrict__ info,
                                                   int64_t n, int T, uint32_t* __restrict__ kbin,
                                                   uint32_t* __restrict__ kc, uint32_t* __restrict__ ksize,
-                                                  SilkState* S) {
+                                                  SilkState* S, int64_t stride, int64_t kstride) {
+  info += (int64_t)blockIdx.y * stride;
+  ksize += (int64_t)blockIdx.y * stride;
+  kbin += (int64_t)blockIdx.y * kstride;
+  kc += (int64_t)blockIdx.y * n;
   constexpr uint32_t NONE = 0xFFFFFFFFu;
   const uint32_t NB = S->nb;
   unsigned long long pairs = 0;
@@ -416,45 +465,74 @@ __global__ __launch_bounds__(256) void k_vote_reg(const uint32_t* __restrict__ b
 }
 
 // Bins that join C: named by their smallest bucket, two or more buckets,
-// C_shared non-empty and of at least delta ids.
+// C_shared non-empty and of at least delta ids.  Entries of a batch's tables
+// past the bucket count are zero (the scans run over whole tables then).
 __global__ void k_emit_flags(const uint2* __restrict__ info, const uint32_t* __restrict__ ksize, int delta,
-                             const SilkState* S, uint32_t* __restrict__ eone, uint32_t* __restrict__ esz) {
+                             const SilkState* S, uint32_t* __restrict__ eone, uint32_t* __restrict__ esz,
+                             int64_t stride, uint32_t pad_to) {
+  const int64_t o = (int64_t)blockIdx.y * stride;
+  info += o;
+  ksize += o;
+  eone += o;
+  esz += o;
   const uint32_t NB = S->nb;
   const uint32_t dmin = delta > 1 ? (uint32_t)delta : 1u;
-  for (uint32_t g = gtid(); g < NB; g += gstride()) {
-    const uint2 e = info[g];
-    const uint32_t ks = ksize[g];
-    const bool on = e.x == g && e.y >= 2u && ks >= dmin;
+  for (uint32_t g = gtid(); g < (NB > pad_to ? NB : pad_to); g += gstride()) {
+    bool on = false;
+    uint32_t ks = 0u;
+    if (g < NB) {
+      const uint2 e = info[g];
+      ks = ksize[g];
+      on = e.x == g && e.y >= 2u && ks >= dmin;
+    }
     eone[g] = on ? 1u : 0u;
     esz[g] = on ? ks : 0u;
   }
 }
 
-// Room in C for this table's sets (C holds scap sets and mcap members); once
-// C has run out of room no later table writes to it, but the sizes needed are
-// still counted.
-__global__ void k_commit(SilkState* S, uint32_t scap, uint32_t mcap) {
+// Room in C for the tables of a batch in order (C holds scap sets and mcap
+// members; es and em: the scans' totals); once C has run out of room no later
+// table writes to it, but the sizes needed are still counted.
+__global__ void k_commit(SilkState* S, SilkTable* tabs, int B, const uint32_t* __restrict__ eidx,
+                         const uint32_t* __restrict__ eoff, const uint32_t* __restrict__ tot, int64_t stride,
+                         uint32_t scap, uint32_t mcap) {
   if (blockIdx.x || threadIdx.x) return;
-  const uint32_t es = S->es, em = S->em;
-  S->need_s += es;
-  S->need_m += em;
-  if (!S->over && (uint64_t)S->cs + es <= scap && (uint64_t)S->cm + em <= mcap) {
-    S->fit = 1u;
-    S->base_s = S->cs;
-    S->base_m = S->cm;
-    S->cs += es;
-    S->cm += em;
-  } else {
-    S->fit = 0u;
-    S->over = 1u;
+  S->cm0 = S->cm;
+  uint32_t e0 = 0u, m0 = 0u;
+  for (int t = 0; t < B; ++t) {
+    const uint32_t e1 = t + 1 < B ? eidx[(int64_t)(t + 1) * stride] : tot[0];
+    const uint32_t m1 = t + 1 < B ? eoff[(int64_t)(t + 1) * stride] : tot[1];
+    const uint32_t es = e1 - e0, em = m1 - m0;
+    SilkTable& t_ = tabs[t];
+    t_.e0 = e0;
+    t_.m0 = m0;
+    S->need_s += es;
+    S->need_m += em;
+    if (!S->over && (uint64_t)S->cs + es <= scap && (uint64_t)S->cm + em <= mcap) {
+      t_.fit = 1u;
+      t_.base_s = S->cs;
+      t_.base_m = S->cm;
+      S->cs += es;
+      S->cm += em;
+    } else {
+      t_.fit = 0u;
+      S->over = 1u;
+    }
+    e0 = e1;
+    m0 = m1;
   }
 }
 
 // Emitted bins per object (zero for every object when the table does not
 // fit in C, so the sort that follows has nothing to do).
 __global__ void k_count_kept(const uint32_t* __restrict__ kbin, const uint32_t* __restrict__ kc, int64_t n,
-                             const uint32_t* __restrict__ eone, const SilkState* S, uint32_t* __restrict__ kc2) {
-  const bool fit = S->fit != 0u;
+                             const uint32_t* __restrict__ eone, const SilkTable* __restrict__ tabs,
+                             uint32_t* __restrict__ kc2, int64_t stride, int64_t kstride) {
+  kbin += (int64_t)blockIdx.y * kstride;
+  kc += (int64_t)blockIdx.y * n;
+  eone += (int64_t)blockIdx.y * stride;
+  kc2 += (int64_t)blockIdx.y * n;
+  const bool fit = tabs[blockIdx.y].fit != 0u;
   for (int64_t i = gtid(); i < n; i += gstride()) {
     uint32_t m = 0;
     if (fit) {
@@ -465,20 +543,27 @@ __global__ void k_count_kept(const uint32_t* __restrict__ kbin, const uint32_t* 
   }
 }
 
-// (emitted bin index, id) pairs in id order: a stable sort by the bin index
-// then lists every C_shared with its ids ascending.
+// (set of C, id) pairs in (table, id) order: a stable sort by the set then
+// lists every C_shared with its ids ascending.
 __global__ void k_kept_pairs(const uint32_t* __restrict__ kbin, const uint32_t* __restrict__ kc, int64_t n,
                              const uint32_t* __restrict__ eone, const uint32_t* __restrict__ eidx,
-                             const uint32_t* __restrict__ kpos, const SilkState* S, uint32_t* __restrict__ phi,
-                             uint32_t* __restrict__ plo) {
-  if (!S->fit) return;
+                             const uint32_t* __restrict__ kpos, const SilkTable* __restrict__ tabs,
+                             uint32_t* __restrict__ phi, uint32_t* __restrict__ plo, int64_t stride,
+                             int64_t kstride) {
+  const SilkTable tab = tabs[blockIdx.y];
+  if (!tab.fit) return;
+  kbin += (int64_t)blockIdx.y * kstride;
+  kc += (int64_t)blockIdx.y * n;
+  eone += (int64_t)blockIdx.y * stride;
+  eidx += (int64_t)blockIdx.y * stride;
+  kpos += (int64_t)blockIdx.y * n;
   for (int64_t i = gtid(); i < n; i += gstride()) {
     const uint32_t c = kc[i];
     uint32_t p = kpos[i];
     for (uint32_t j = 0; j < c; ++j) {
       const uint32_t b = kbin[(int64_t)j * n + i];
       if (eone[b]) {
-        phi[p] = eidx[b];
+        phi[p] = tab.base_s + eidx[b] - tab.e0;
         plo[p] = (uint32_t)i;
         ++p;
       }
@@ -488,12 +573,16 @@ __global__ void k_kept_pairs(const uint32_t* __restrict__ kbin, const uint32_t* 
 
 __global__ void k_c_write(const uint32_t* __restrict__ sorted_ids, const uint32_t* __restrict__ eone,
                           const uint32_t* __restrict__ eidx, const uint32_t* __restrict__ eoff, const SilkState* S,
-                          uint32_t* __restrict__ cmem, uint32_t* __restrict__ coff) {
-  if (!S->fit) return;
-  const uint32_t em = S->em, NB = S->nb, bs = S->base_s, bm = S->base_m;
-  for (uint32_t q = gtid(); q < em; q += gstride()) cmem[bm + q] = sorted_ids[q];
+                          const SilkTable* __restrict__ tabs, uint32_t* __restrict__ cmem,
+                          uint32_t* __restrict__ coff, int64_t stride) {
+  const SilkTable tab = tabs[blockIdx.y];
+  const uint32_t NB = S->nb, kp = S->kp, cm0 = S->cm0;
+  if (blockIdx.y == 0)
+    for (uint32_t q = gtid(); q < kp; q += gstride()) cmem[cm0 + q] = sorted_ids[q];
+  if (!tab.fit) return;
+  const int64_t o = (int64_t)blockIdx.y * stride;
   for (uint32_t g = gtid(); g < NB; g += gstride())
-    if (eone[g]) coff[bs + eidx[g]] = bm + eoff[g];
+    if (eone[o + g]) coff[tab.base_s + eidx[o + g] - tab.e0] = tab.base_m + eoff[o + g] - tab.m0;
 }
 
 // ---- de-duplication ------------------------------------------------------------
@@ -729,7 +818,10 @@ __global__ void k_seed_copy(const uint32_t* __restrict__ soff, const uint32_t* _
 struct SilkWs {
   int64_t Tn, Ccap, Cs, KPmax, NS, NM;  // C's members / sets; NS, NM: sets, positions of either phase
   uint32_t ht_slots;
+  int B;            // SILK tables per batch
   SilkState* S;
+  SilkTable* tabs;  // [B]
+  uint32_t* tot;    // totals of the batch's two scans
   uint32_t *base, *gstart, *gsize, *G, *bof, *flag, *fscan, *ht, *rep, *binmin, *bcount, *ksize;
   uint2* info;
   uint32_t *eone, *esz, *eidx, *eoff, *kbin, *kc, *kc2, *kpos;
@@ -758,30 +850,34 @@ static size_t carve_silk(const geek_silk_job& J, void* ws, SilkWs& W) {
   uint64_t slots = 1024;
   while (slots < 2u * (uint64_t)W.Tn && slots < 0x80000000ull) slots <<= 1;
   W.ht_slots = (uint32_t)slots;
+  W.B = (int)std::max<int64_t>(1, std::min<int64_t>(J.L, SILK_BATCH / W.Tn));
   const int64_t NS = W.NS, Tn = W.Tn, Cc = W.Ccap, Cs = W.Cs;
-  const int64_t npairs = W.KPmax > Cc ? W.KPmax : Cc;
+  const int64_t B = W.B, BT = B * Tn, NBT = NS > BT ? NS : BT;
+  const int64_t npairs = B * W.KPmax > Cc ? B * W.KPmax : Cc;
   W.S = c.take<SilkState>(1);
+  W.tabs = c.take<SilkTable>(B);
+  W.tot = c.take<uint32_t>(2);
   W.base = c.take<uint32_t>(J.T + 1);
   W.gstart = c.take<uint32_t>(NS + 1);
   W.gsize = c.take<uint32_t>(NS + 1);
-  W.G = c.take<uint32_t>(NS * J.K);
+  W.G = c.take<uint32_t>(NBT * J.K);
   W.bof = c.take<uint32_t>(Tn);
   W.flag = c.take<uint32_t>(W.NM + 1);
   W.fscan = c.take<uint32_t>(W.NM + 1);
-  W.ht = c.take<uint32_t>(slots);
-  W.rep = c.take<uint32_t>(Tn);
-  W.binmin = c.take<uint32_t>(Tn);
-  W.bcount = c.take<uint32_t>(Tn);
-  W.ksize = c.take<uint32_t>(Tn);
-  W.info = c.take<uint2>(Tn);
-  W.eone = c.take<uint32_t>(Tn + 1);
-  W.esz = c.take<uint32_t>(Tn + 1);
-  W.eidx = c.take<uint32_t>(Tn + 1);
-  W.eoff = c.take<uint32_t>(Tn + 1);
-  W.kbin = c.take<uint32_t>(W.KPmax);
-  W.kc = c.take<uint32_t>(J.n + 1);
-  W.kc2 = c.take<uint32_t>(J.n + 1);
-  W.kpos = c.take<uint32_t>(J.n + 1);
+  W.ht = c.take<uint32_t>(B * slots);
+  W.rep = c.take<uint32_t>(BT);
+  W.binmin = c.take<uint32_t>(BT);
+  W.bcount = c.take<uint32_t>(BT);
+  W.ksize = c.take<uint32_t>(BT);
+  W.info = c.take<uint2>(BT);
+  W.eone = c.take<uint32_t>(BT + 1);
+  W.esz = c.take<uint32_t>(BT + 1);
+  W.eidx = c.take<uint32_t>(BT + 1);
+  W.eoff = c.take<uint32_t>(BT + 1);
+  W.kbin = c.take<uint32_t>(B * W.KPmax);
+  W.kc = c.take<uint32_t>(B * J.n + 1);
+  W.kc2 = c.take<uint32_t>(B * J.n + 1);
+  W.kpos = c.take<uint32_t>(B * J.n + 1);
   W.phi = c.take<uint32_t>(npairs);
   W.plo = c.take<uint32_t>(npairs);
   W.phi2 = c.take<uint32_t>(npairs);
@@ -811,10 +907,10 @@ static size_t carve_silk(const geek_silk_job& J, void* ws, SilkWs& W) {
   W.sone = c.take<uint32_t>(Cs + 1);
   W.soff = c.take<uint32_t>(Cs + 1);
   W.sidx = c.take<uint32_t>(Cs + 1);
-  W.big_list = c.take<uint32_t>(NS + 1);
+  W.big_list = c.take<uint32_t>(NBT + 1);
   const int64_t nsort = npairs > NS ? npairs : NS;
   W.radix_tmp = c.take<uint32_t>(radix_tmp_words(nsort));
-  W.scan_tmp = c.take<uint32_t>(exscan_tmp_words((W.NM > NS ? W.NM : NS) + 1) + 16);
+  W.scan_tmp = c.take<uint32_t>(exscan_tmp_words(std::max(std::max(W.NM, NS), BT) + 1) + 16);
   return c.used + 256;
 }
 
@@ -866,46 +962,54 @@ int32_t silk_run(const geek_silk_job& J, void* ws, size_t ws_bytes, int32_t* st,
   while (VT > 64 && VT * T > SV_LDS) VT >>= 1;
   const size_t vlds = sizeof(uint32_t) * 2 * (size_t)T * VT;
   const int vgrid = (int)std::min<int64_t>((n + VT - 1) / VT, 4096);
-  // kept pairs sorted by the emitted bin index (< number of buckets)
+  // kept pairs sorted by their set of C
   int kw[4], ksh[4], knp = 0;
-  for (int sh = 0; sh < bits_for((uint64_t)(Tn - 1)); sh += 8) {
+  for (int sh = 0; sh < bits_for((uint64_t)(W.Cs - 1)); sh += 8) {
     kw[knp] = 0;
     ksh[knp++] = sh;
   }
-  for (int t = 0; t < J.L; ++t) {
-    const uint32_t* keys = J.silk_keys + 2 * (int64_t)t * K;
-    hipLaunchKernelGGL(k_sk_fill, dim3(1), dim3(64), 0, s, &S->big, (int64_t)1, 0u);
-    hipLaunchKernelGGL(k_sig, dim3(ggrid(Tn)), dim3(256), 0, s, J.members, W.gstart, W.gsize, &S->nb, keys, K, W.G,
-                       W.big_list, &S->big, &S->hash_evals);
-    hipLaunchKernelGGL(k_sig_big, dim3(SG_GRID), dim3(256), 0, s, J.members, W.gstart, W.gsize, keys, K, W.G,
-                       W.big_list, &S->big, &S->hash_evals);
+  for (int t0 = 0; t0 < J.L; t0 += W.B) {
+    const int B = std::min(W.B, J.L - t0);
+    const int64_t hs = W.ht_slots, ks = W.KPmax;
+    const int bs = (int)(sizeof(SilkTable) / sizeof(uint32_t));
+    const uint32_t* keys = J.silk_keys + 2 * (int64_t)t0 * K;
+    const dim3 gT(ggrid(Tn), B), gn(ggrid(n), B), gall(B > 1 ? ggrid(2 * Tn) : SG_GRID, B), gbig(B > 1 ? 64 : SG_GRID, B);
+    // (clears the tables' queue lengths too)
+    hipLaunchKernelGGL(k_ht_clear, gall, dim3(256), 0, s, S, W.ht, W.binmin, W.bcount, W.ksize, hs, Tn, W.tabs);
+    hipLaunchKernelGGL(k_sig, gT, dim3(256), 0, s, J.members, W.gstart, W.gsize, &S->nb, keys, K, W.G, W.big_list,
+                       &W.tabs->big, bs, Tn, &S->hash_evals);
+    hipLaunchKernelGGL(k_sig_big, gbig, dim3(256), 0, s, J.members, W.gstart, W.gsize, keys, K, W.G, W.big_list,
+                       &W.tabs->big, bs, Tn, &S->hash_evals);
     // bins of identical G
-    hipLaunchKernelGGL(k_ht_clear, dim3(SG_GRID), dim3(256), 0, s, S, W.ht, W.binmin, W.bcount, W.ksize);
-    hipLaunchKernelGGL(k_ht_insert, dim3(ggrid(Tn)), dim3(256), 0, s, W.G, K, S, W.ht, W.rep);
-    hipLaunchKernelGGL(k_ht_min, dim3(ggrid(Tn)), dim3(256), 0, s, W.rep, S, W.binmin, W.bcount);
-    hipLaunchKernelGGL(k_bin_info, dim3(ggrid(Tn)), dim3(256), 0, s, W.rep, W.binmin, W.bcount, S, W.info);
+    hipLaunchKernelGGL(k_ht_insert, gT, dim3(256), 0, s, W.G, K, S, W.ht, W.rep, hs, Tn);
+    hipLaunchKernelGGL(k_ht_min, gT, dim3(256), 0, s, W.rep, S, W.binmin, W.bcount, Tn);
+    hipLaunchKernelGGL(k_bin_info, gT, dim3(256), 0, s, W.rep, W.binmin, W.bcount, S, W.info, Tn);
     // majority votes and the bins that join C
     if (T <= 16)
-      hipLaunchKernelGGL(k_vote_reg<16>, dim3(ggrid(n)), dim3(256), 0, s, W.bof, W.info, n, T, W.kbin, W.kc,
-                         W.ksize, S);
+      hipLaunchKernelGGL(k_vote_reg<16>, gn, dim3(256), 0, s, W.bof, W.info, n, T, W.kbin, W.kc, W.ksize, S, Tn, ks);
     else if (T <= 32)
-      hipLaunchKernelGGL(k_vote_reg<32>, dim3(ggrid(n)), dim3(256), 0, s, W.bof, W.info, n, T, W.kbin, W.kc,
-                         W.ksize, S);
+      hipLaunchKernelGGL(k_vote_reg<32>, gn, dim3(256), 0, s, W.bof, W.info, n, T, W.kbin, W.kc, W.ksize, S, Tn, ks);
     else
-      hipLaunchKernelGGL(k_vote, dim3(vgrid), dim3(VT), vlds, s, W.bof, W.info, n, T, W.kbin, W.kc, W.ksize, S);
-    hipLaunchKernelGGL(k_emit_flags, dim3(ggrid(Tn)), dim3(256), 0, s, W.info, W.ksize, J.delta, S, W.eone, W.esz);
-    exscan_u32_dn(W.eone, W.eidx, Tn, &S->nb, W.scan_tmp, &S->es, s);
-    exscan_u32_dn(W.esz, W.eoff, Tn, &S->nb, W.scan_tmp, &S->em, s);
-    hipLaunchKernelGGL(k_commit, dim3(1), dim3(1), 0, s, S, (uint32_t)W.Cs, (uint32_t)Cc);
-    // this table's sets of C, ids ascending
-    hipLaunchKernelGGL(k_count_kept, dim3(ggrid(n)), dim3(256), 0, s, W.kbin, W.kc, n, W.eone, S, W.kc2);
-    exscan_u32(W.kc2, W.kpos, n, W.scan_tmp, &S->kp, s);
-    hipLaunchKernelGGL(k_kept_pairs, dim3(ggrid(n)), dim3(256), 0, s, W.kbin, W.kc, n, W.eone, W.eidx, W.kpos, S,
-                       W.phi, W.plo);
-    RsView A{{W.phi, nullptr, nullptr, nullptr}, W.plo}, B{{W.phi2, nullptr, nullptr, nullptr}, W.plo2};
-    const int alt = radix_sort_dn(A, B, 1, W.KPmax, &S->kp, kw, ksh, knp, W.radix_tmp, s);
-    hipLaunchKernelGGL(k_c_write, dim3(ggrid(Tn)), dim3(256), 0, s, alt ? W.plo2 : W.plo, W.eone, W.eidx, W.eoff, S,
-                       W.cmem, W.coff);
+      hipLaunchKernelGGL(k_vote, dim3(vgrid, B), dim3(VT), vlds, s, W.bof, W.info, n, T, W.kbin, W.kc, W.ksize, S, Tn,
+                         ks);
+    // scans over the batch's tables one after another (one table: its buckets)
+    hipLaunchKernelGGL(k_emit_flags, gT, dim3(256), 0, s, W.info, W.ksize, J.delta, S, W.eone, W.esz, Tn,
+                       B > 1 ? (uint32_t)Tn : 0u);
+    const uint32_t* cnt = B > 1 ? nullptr : &S->nb;
+    exscan_u32_dn(W.eone, W.eidx, B * Tn, cnt, W.scan_tmp, W.tot, s);
+    exscan_u32_dn(W.esz, W.eoff, B * Tn, cnt, W.scan_tmp, W.tot + 1, s);
+    hipLaunchKernelGGL(k_commit, dim3(1), dim3(1), 0, s, S, W.tabs, B, W.eidx, W.eoff, W.tot, Tn, (uint32_t)W.Cs,
+                       (uint32_t)Cc);
+    // the batch's sets of C, ids ascending
+    hipLaunchKernelGGL(k_count_kept, gn, dim3(256), 0, s, W.kbin, W.kc, n, W.eone, W.tabs, W.kc2, Tn, ks);
+    exscan_u32(W.kc2, W.kpos, B * n, W.scan_tmp, &S->kp, s);
+    hipLaunchKernelGGL(k_kept_pairs, gn, dim3(256), 0, s, W.kbin, W.kc, n, W.eone, W.eidx, W.kpos, W.tabs, W.phi, W.plo,
+                       Tn, ks);
+    RsView A{{W.phi, nullptr, nullptr, nullptr}, W.plo}, Bv{{W.phi2, nullptr, nullptr, nullptr}, W.plo2};
+    // (a set of C holds a table's pairs, so the pairs that fit number at most Cc)
+    const int alt = radix_sort_dn(A, Bv, 1, std::min<int64_t>(B * W.KPmax, Cc), &S->kp, kw, ksh, knp, W.radix_tmp, s);
+    hipLaunchKernelGGL(k_c_write, gT, dim3(256), 0, s, alt ? W.plo2 : W.plo, W.eone, W.eidx, W.eoff, S, W.tabs, W.cmem,
+                       W.coff, Tn);
   }
   // ---- de-duplication: one more table over the sets of C (Cs bounds its
   // sets and bins, Cc its members and voting pairs)
@@ -915,9 +1019,9 @@ int32_t silk_run(const geek_silk_job& J, void* ws, size_t ws_bytes, int32_t* st,
   hipLaunchKernelGGL(k_set_extent, dim3(ggrid(Cs)), dim3(256), 0, s, W.coff, S, W.gstart, W.gsize);
   hipLaunchKernelGGL(k_sk_fill, dim3(1), dim3(64), 0, s, &S->big, (int64_t)1, 0u);
   hipLaunchKernelGGL(k_sig, dim3(ggrid(Cs)), dim3(256), 0, s, W.cmem, W.gstart, W.gsize, &S->cs, dkeys, K, W.G,
-                     W.big_list, &S->big, (unsigned long long*)nullptr);
+                     W.big_list, &S->big, 0, (int64_t)0, (unsigned long long*)nullptr);
   hipLaunchKernelGGL(k_sig_big, dim3(SG_GRID), dim3(256), 0, s, W.cmem, W.gstart, W.gsize, dkeys, K, W.G, W.big_list,
-                     &S->big, (unsigned long long*)nullptr);
+                     &S->big, 0, (int64_t)0, (unsigned long long*)nullptr);
   hipLaunchKernelGGL(k_dd_tuples, dim3(ggrid(Cs)), dim3(256), 0, s, W.G, K, S, W.tw[0], W.tw[1], W.tw[2], W.tw[3],
                      W.tv);
   int tw[16], tsh[16], tnp = 0;
