@@ -151,9 +151,12 @@ __global__ __launch_bounds__(256) void k_gather_t(const float* __restrict__ X, i
 }
 
 // Centroids from the grouped copy: the same ascending chain of float64
-// additions as k_centroids.
-constexpr int CT_B = 16;  // 16-byte loads in flight per batch (64 members)
-__global__ void k_centroids_t(const float* __restrict__ Xt, int64_t nm, int d,
+// additions as k_centroids.  The longest seed's chain is the kernel's time:
+// 244,500 members 3.56 ms with every batch of 64 members' loads waited for,
+// 3.15 ms with 144 members' loads in flight ahead of the additions (12.9 ns per
+// member; widening four members ahead of their additions changed nothing).
+constexpr int CT_B = 6, CT_R = 7;  // 16-byte loads per batch, batches in the ring
+__global__ __launch_bounds__(256) void k_centroids_t(const float* __restrict__ Xt, int64_t nm, int d,
                               const uint32_t* __restrict__ offs, int k, double* __restrict__ C,
                               float* __restrict__ cabs, int32_t* st) {
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -172,17 +175,34 @@ __global__ void k_centroids_t(const float* __restrict__ Xt, int64_t nm, int d,
       double acc = 0.0;
       int64_t q = s;
       for (; q < e && (q & 3); ++q) acc = __dadd_rn(acc, (double)at(q));
-      for (; q + 4 * CT_B <= e; q += 4 * CT_B) {
-        float4 v[CT_B];
+      // a ring of CT_R batches: one is added while the others load
+      float4 v[CT_R][CT_B];
+      auto load = [&](float4 (&to)[CT_B], int64_t q0) {
 #pragma unroll
-        for (int u = 0; u < CT_B; ++u) v[u] = *reinterpret_cast<const float4*>(p + ((q >> 2) + u) * gs);
+        for (int u = 0; u < CT_B; ++u) to[u] = *reinterpret_cast<const float4*>(p + ((q0 >> 2) + u) * gs);
+      };
+      auto add = [&](const float4 (&x)[CT_B]) {
 #pragma unroll
         for (int u = 0; u < CT_B; ++u) {
-          acc = __dadd_rn(acc, (double)v[u].x);
-          acc = __dadd_rn(acc, (double)v[u].y);
-          acc = __dadd_rn(acc, (double)v[u].z);
-          acc = __dadd_rn(acc, (double)v[u].w);
+          acc = __dadd_rn(acc, (double)x[u].x);
+          acc = __dadd_rn(acc, (double)x[u].y);
+          acc = __dadd_rn(acc, (double)x[u].z);
+          acc = __dadd_rn(acc, (double)x[u].w);
         }
+      };
+      constexpr int64_t NB = 4 * CT_B;
+      if (q + CT_R * NB <= e) {
+#pragma unroll
+        for (int z = 0; z < CT_R - 1; ++z) load(v[z], q + z * NB);
+        for (; q + (2 * CT_R - 1) * NB <= e; q += CT_R * NB)
+#pragma unroll
+          for (int z = 0; z < CT_R; ++z) {
+            load(v[(z + CT_R - 1) % CT_R], q + (z + CT_R - 1) * NB);
+            add(v[z]);
+          }
+#pragma unroll
+        for (int z = 0; z < CT_R - 1; ++z) add(v[z]);
+        q += (CT_R - 1) * NB;
       }
       for (; q < e; ++q) acc = __dadd_rn(acc, (double)at(q));
       c = acc / (double)(e - s);
