@@ -161,13 +161,22 @@ GEEK_D float two_eps(double xn, double cm, double inv_x, double inv_c, double he
 // from LDS feeds NCB MFMAs.  With NBUF = 2 the next stage of centroids is
 // in flight while the current one is consumed (LDS DMA where rows are at
 // least 64 bytes, else through registers).
-template <class M, int DP, bool HET, int NCB, int NBUF, bool T2, bool WIDE>
+// What a scan restricted to some groups of seeds reads, and what a first pass
+// leaves for it (see "blocked rescan" in assign.hip); all null otherwise.
+struct ScanBlocks {
+  const uint32_t* flags;  // per tile of 128 rows a bit per 64 (permuted) seeds
+  int words;              // 32-bit words per tile
+  const uint32_t* perm;   // seed of a permuted position
+  float* thr;             // out: per unsettled row the largest candidate value
+};
+
+template <class M, int DP, bool HET, int NCB, int NBUF, bool T2, bool WIDE, bool MARK = false>
 __device__ __forceinline__ void scan_tiles(
     const float* __restrict__ X, int64_t ldx, int d, int64_t n_rows,
     const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
     const typename M::ce* __restrict__ cl, const float* __restrict__ nc, int k_pad,
     const float* __restrict__ cmax_p, const float* __restrict__ cabs_p, Het het, int k,
-    int32_t* __restrict__ rec, int32_t* st, int64_t tile0, int64_t tile_end, int64_t tstep) {
+    int32_t* __restrict__ rec, int32_t* st, int64_t tile0, int64_t tile_end, int64_t tstep, ScanBlocks sb = {}) {
   using CE = typename M::ce;
   // centroids per stage: half as many where an element takes four bytes and
   // two stages are in LDS (three workgroups per CU at d = 128 then)
@@ -379,13 +388,37 @@ __device__ __forceinline__ void scan_tiles(
       blk[cb] = 0;
     }
 
+    // the stage after the one at c0 (k_pad: none): with flags, the next stage
+    // of a flagged group of 64 seeds
+    [[maybe_unused]] const uint32_t* frow = nullptr;
+    if constexpr (WIDE) frow = sb.flags ? sb.flags + tile * sb.words : nullptr;
+    auto group_from = [&](int g) {
+      int w = g >> 5;
+      uint32_t bits = w < sb.words ? frow[w] & (~0u << (g & 31)) : 0u;
+      while (bits == 0u) {
+        if (++w >= sb.words) return k_pad;
+        bits = frow[w];
+      }
+      return (w * 32 + __ffs(bits) - 1) * 64;
+    };
+    auto next_c0 = [&](int c0) {
+      if constexpr (WIDE) {
+        if (frow) return ((c0 + BC) & 63) ? c0 + BC : group_from((c0 + BC) >> 6);
+      }
+      return c0 + BC;
+    };
+    int first = 0;
+    if constexpr (WIDE) {
+      if (frow) first = group_from(0);
+    }
+    const int load0 = first < k_pad ? first : 0;
     __syncthreads();  // previous tile done with the LDS buffers
     if constexpr (DMA) {
-      GEEK_DMA_STAGE(0, 0);
+      GEEK_DMA_STAGE(load0, 0);
       if (tid < BC) lds_nc[0][tid] = nc_stage(stg_nc);
       __builtin_amdgcn_s_waitcnt(0);
     } else {
-      GEEK_LOAD_REGS(0);
+      GEEK_LOAD_REGS(load0);
       GEEK_STORE_LDS(0);
     }
     __syncthreads();
@@ -412,14 +445,14 @@ __device__ __forceinline__ void scan_tiles(
     int pend_g = -1;
     // one stage of BC centroids from buffer `cur` (a compile-time
     // constant), with the next stage loading into the other buffer
-    auto stage = [&](auto curc, const int c0, const int it) {
+    auto stage = [&](auto curc, const int c0, const int it, const int cn) {
       constexpr int cur = NBUF == 2 ? decltype(curc)::value : 0;
       constexpr int nxt = NBUF == 2 ? 1 - cur : 0;
-      const bool more = c0 + BC < k_pad;
+      const bool more = cn < k_pad;
       if constexpr (DMA) {
-        if (more) GEEK_DMA_STAGE(c0 + BC, nxt);
+        if (more) GEEK_DMA_STAGE(cn, nxt);
       } else {
-        if (NBUF == 2 && more) GEEK_LOAD_REGS(c0 + BC);
+        if (NBUF == 2 && more) GEEK_LOAD_REGS(cn);
       }
 
       // A fragments of a 32-row block: all S of them in registers, the next
@@ -726,20 +759,22 @@ __device__ __forceinline__ void scan_tiles(
           GEEK_STORE_LDS(nxt);
         } else {
           __syncthreads();
-          GEEK_LOAD_REGS(c0 + BC);
+          GEEK_LOAD_REGS(cn);
           GEEK_STORE_LDS(0);
         }
       }
       __syncthreads();
     };
-    for (int c0 = 0, it = 0; c0 < k_pad;) {
-      stage(IC<0>{}, c0, it);
-      c0 += BC;
+    for (int c0 = first, it = 0; c0 < k_pad;) {
+      int cn = next_c0(c0);
+      stage(IC<0>{}, c0, it, cn);
+      c0 = cn;
       ++it;
       if constexpr (NBUF == 2) {
         if (c0 < k_pad) {
-          stage(IC<1>{}, c0, it);
-          c0 += BC;
+          cn = next_c0(c0);
+          stage(IC<1>{}, c0, it, cn);
+          c0 = cn;
           ++it;
         }
       }
@@ -774,6 +809,16 @@ __device__ __forceinline__ void scan_tiles(
           int32_t* rr = rec + posv[cb] * RECW_T2;
           rr[0] = unique ? 1 : -1;
           if (unique) rr[1] = jbest;
+          if constexpr (MARK) {
+            // any seed near the best will do to order the rows by; a value or
+            // window that says nothing lets every seed pass
+            if (!unique) {
+              rr[1] = (unsigned)jbest < (unsigned)k ? jbest : 0;
+              const float t = v1 + twoeps[cb];
+              const bool good = best > -1e37f && best < 1e37f && fabsf(best) >= 0x1p-126f && t < INFINITY;
+              sb.thr[posv[cb]] = good ? t : INFINITY;
+            }
+          }
         }
       }
     } else {
@@ -805,7 +850,7 @@ __device__ __forceinline__ void scan_tiles(
         } else {
           if (h == 0) rr[0] = kept + kept_o;
           const int off = h ? kept_o : 0;
-          for (int q = 0; q < kept; ++q) rr[1 + off + q] = lj[q];
+          for (int q = 0; q < kept; ++q) rr[1 + off + q] = WIDE && sb.perm ? (int)sb.perm[lj[q]] : lj[q];
         }
       }
     }
