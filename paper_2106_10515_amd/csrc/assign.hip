@@ -42,8 +42,9 @@ constexpr int SSE_BLOCK = 4096;
 // ---------------------------------------------------------------- centroids
 // The sum over a seed's members is one chain of float64 additions (the
 // reference order), so a seed with many members is bound by memory latency:
-// members are taken CB at a time, their values loaded together (the next
-// batch's ids already in flight), then added in order.
+// members are taken CB at a time, their values loaded together, and added in
+// order while the next batch's values load (the ids of the batch after it are
+// already in flight).
 constexpr int CB = 32;
 
 // Largest magnitude seen by a wavefront into *out (skipped while *out is not
@@ -59,7 +60,7 @@ GEEK_D void wave_absmax(float v, float* out) {
 GEEK_D double centroid_of(const float* __restrict__ X, int64_t ldx, int64_t n, int t,
                           const uint32_t* __restrict__ mem, uint32_t s, uint32_t e, int32_t* st);
 
-__global__ void k_centroids(const float* __restrict__ X, int64_t ldx, int64_t n, int d,
+__global__ __launch_bounds__(256) void k_centroids(const float* __restrict__ X, int64_t ldx, int64_t n, int d,
                             const uint32_t* __restrict__ offs, const uint32_t* __restrict__ mem,
                             int k, const uint32_t* __restrict__ kdev, double* __restrict__ C,
                             float* __restrict__ cabs, int32_t* st) {
@@ -89,22 +90,32 @@ GEEK_D double centroid_of(const float* __restrict__ X, int64_t ldx, int64_t n, i
   // repeated ids whose values are not added)
   auto id_at = [&](uint32_t q) { return mem[q < e ? q : e - 1]; };
   uint32_t ids[CB];
-#pragma unroll
-  for (int u = 0; u < CB; ++u) ids[u] = id_at(s + u);
-  for (uint32_t q = s; q < e; q += CB) {
-    float v[CB];
+  float v[CB], w[CB];
+  auto load = [&](float (&to)[CB], uint32_t next) {  // values of `ids`, then the ids from `next` on
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
       const bool ok = (int64_t)ids[u] < n;
       bad |= !ok;
-      v[u] = X[(int64_t)(ok ? ids[u] : 0u) * ldx + t];
+      to[u] = X[(int64_t)(ok ? ids[u] : 0u) * ldx + t];
     }
 #pragma unroll
-    for (int u = 0; u < CB; ++u) ids[u] = id_at(q + CB + u);
+    for (int u = 0; u < CB; ++u) ids[u] = id_at(next + u);
+  };
+  auto add = [&](const float (&x)[CB], uint32_t q) {
     const uint32_t cnt = e - q < (uint32_t)CB ? e - q : (uint32_t)CB;
 #pragma unroll
     for (int u = 0; u < CB; ++u)
-      if ((uint32_t)u < cnt) acc = __dadd_rn(acc, (double)v[u]);
+      if ((uint32_t)u < cnt) acc = __dadd_rn(acc, (double)x[u]);
+  };
+#pragma unroll
+  for (int u = 0; u < CB; ++u) ids[u] = id_at(s + u);
+  load(v, s + CB);
+  for (uint32_t q = s; q < e; q += 2 * CB) {
+    if (q + CB < e) load(w, q + 2 * CB);
+    add(v, q);
+    if (q + CB >= e) break;
+    if (q + 2 * CB < e) load(v, q + 3 * CB);
+    add(w, q + CB);
   }
   if (bad) set_status(st, GEEK_ERR_ARG);
   return acc / (double)(e - s);
@@ -529,6 +540,7 @@ __global__ __launch_bounds__(256) void k_finalize(const float* __restrict__ X, i
 // the seed tiles of a group are split over up to FB_SPLIT workgroups, whose
 // per-row (D, j) minima k_fb_merge combines.
 constexpr int FB_R = 64, FB_C = 64, FB_TK = 16, FB_GRID = 1024, FB_SPLIT = 16;
+constexpr int FB_GROUPS = 4096;  // marked groups of seeds a workgroup lists
 constexpr int FB_XS = FB_R + 4;  // LDS row stride (floats) of the staged rows
 constexpr int FB_CS = FB_C + 2;  // LDS row stride (doubles) of a seed chunk
 
@@ -557,7 +569,11 @@ __global__ __launch_bounds__(256) void k_fallback64(
     const uint32_t* __restrict__ kdev, Het het,
     const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count, int32_t* __restrict__ assign,
     double* __restrict__ dist, double* __restrict__ part_d, int32_t* __restrict__ part_j,
-    unsigned long long* __restrict__ ctr) {
+    unsigned long long* __restrict__ ctr, const uint32_t* __restrict__ fpos, ScanBlocks sb) {
+  // with marks (fpos: the rows' places in the marked order, ascending): the
+  // groups of 64 seeds marked for some row of the workgroup's 64
+  __shared__ uint32_t glist[FB_GROUPS];
+  __shared__ uint32_t gsum[4];
   constexpr int XS_WORDS = DP * FB_XS > FB_R * 16 * 3 ? DP * FB_XS : FB_R * 16 * 3;
   __shared__ __attribute__((aligned(16))) float xs[XS_WORDS];  // [t][row]; later the reduction
   __shared__ __attribute__((aligned(16))) double cs[FB_TK * FB_CS];  // [t][seed]
@@ -575,8 +591,39 @@ __global__ __launch_bounds__(256) void k_fallback64(
   for (int64_t q = blockIdx.x; q < R * S; q += gridDim.x) {
     const int64_t g = q / S;
     const int sp = (int)(q % S);
-    const int tile0 = (int)((int64_t)sp * T / S), tile1 = (int)((int64_t)(sp + 1) * T / S);
     __syncthreads();  // the previous item's reduction has read xs and rid
+    int groups = T;
+    bool listed = false;
+    if (sb.flags && sb.words <= 256) {
+      const int64_t p0 = g * FB_R, p1 = p0 + FB_R < (int64_t)count ? p0 + FB_R - 1 : (int64_t)count - 1;
+      const int64_t t0 = fpos[p0] / 128, t1 = fpos[p1] / 128;
+      uint32_t bits = 0u;
+      if (tid < sb.words)
+        for (int64_t z = t0; z <= t1; ++z) bits |= sb.flags[z * sb.words + tid];
+      const uint32_t mine = __popc(bits);
+      uint32_t incl = mine;
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o);
+        if ((tid & 63) >= o) incl += y;
+      }
+      if ((tid & 63) == 63) gsum[tid >> 6] = incl;
+      __syncthreads();
+      uint32_t at = incl - mine;
+      for (int z = 0; z < tid >> 6; ++z) at += gsum[z];
+      const uint32_t all = gsum[0] + gsum[1] + gsum[2] + gsum[3];
+      listed = all <= (uint32_t)FB_GROUPS;  // uniform
+      if (listed) {
+        groups = (int)all;
+        for (; bits; bits &= bits - 1u) glist[at++] = (uint32_t)(tid * 32 + __ffs(bits) - 1);
+      }
+    }
+    const int tile0 = (int)((int64_t)sp * groups / S), tile1 = (int)((int64_t)(sp + 1) * groups / S);
+    // seed of column `c` of the z-th tile: in order, or through the marked order
+    auto seed_at = [&](int z, int c) {
+      if (!listed) return z * FB_C + c;
+      const int r = (int)glist[z] * FB_C + c;
+      return r < k ? (int)sb.perm[r] : k;
+    };
     if (tid < FB_R) {
       const int64_t pos = g * FB_R + tid;
       rid[tid] = pos < count ? (int64_t)rows[pos] : -1;
@@ -601,11 +648,11 @@ __global__ __launch_bounds__(256) void k_fallback64(
       for (int u = 0; u < 4; ++u) {
         const int idx = tid + u * 256;
         const int jj = idx >> 4, tt = idx & 15;
-        const int j = tile * FB_C + jj, t = ch * FB_TK + tt;
+        const int j = seed_at(tile, jj), t = ch * FB_TK + tt;
         pre[u] = (j < kv && t < d) ? C[(int64_t)j * d + t] : 0.0;
       }
     };
-    if (tile0 < tile1) fetch(tile0, 0);
+    if (tile0 < tile1) fetch(tile0, 0);  // (glist is complete since the barrier before rid was read)
     for (int tile = tile0; tile < tile1; ++tile) {
       double acc[4][4];
 #pragma unroll
@@ -640,17 +687,16 @@ __global__ __launch_bounds__(256) void k_fallback64(
             }
         }
       }
-      // j increases along this thread's sequence: strict < keeps the lowest
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const int64_t i = rid[tr * 4 + a];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-          const int j = tile * FB_C + tc * 4 + b;
+          const int j = seed_at(tile, tc * 4 + b);
           if (j >= kv) continue;
           double D = acc[a][b];
           if (het.cat && i >= 0) D = __dadd_rn(D, __dmul_rn(het.gamma, (double)mismatches(het, i, j)));
-          if (D < best[a]) {
+          if (D < best[a] || (D == best[a] && j < bj[a])) {
             best[a] = D;
             bj[a] = j;
           }
@@ -695,8 +741,8 @@ __global__ __launch_bounds__(256) void k_fallback64(
   }
 }
 
-// Per-row minimum over the seed-tile splits of k_fallback64 (split order is
-// seed order, so (D, j) comparison keeps the lowest index on ties).
+// Per-row minimum over the seed-tile splits of k_fallback64 (lowest index on
+// ties).
 __global__ void k_fb_merge(const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count, int k,
                            const double* __restrict__ part_d, const int32_t* __restrict__ part_j,
                            int32_t* __restrict__ assign, double* __restrict__ dist,
@@ -741,7 +787,7 @@ __global__ void k_fb_merge(const uint32_t* __restrict__ rows, const uint32_t* __
 // every 128 of them the groups of 64 seeds that hold a value within some row's
 // window (k_mark), and the float32 rescan visits the marked groups only.  The
 // marks are exact bounds; the orders decide how few there are.
-// 10^6 points, 90,343 seeds of 1,000 clusters: rescan 111 ms against 19 ms for
+// 10^6 points, 90,343 seeds of 1,000 clusters: rescan and float64 scan 137 ms against 21 ms for
 // ordering, marking and rescanning.  Below BLOCKED_K seeds the rescan itself is
 // short, and the dozens of launches that order rows and seeds are not worth it.
 constexpr int BLOCKED_K = 16384;
@@ -927,6 +973,25 @@ __global__ __launch_bounds__(SCAN_THREADS, 2) void k_mark(const float* __restric
     stage(buf0, 0, buf1, c0);
     if (c0 + SCAN_BC < k_pad) stage(buf1, 1, buf0, c0 + SCAN_BC);
   }
+}
+
+// Rows the rescan left (an overflowed window), in the marked order: their
+// flags, then, after a scan, the rows and their places.
+__global__ void k_left_flags(const uint32_t* __restrict__ count, const int32_t* __restrict__ rec,
+                             uint32_t* __restrict__ flag) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, c = *count;
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < c; q += stride)
+    flag[q] = rec[q * RECW] <= 0 ? 1u : 0u;
+}
+__global__ void k_left_list(const uint32_t* __restrict__ count, const uint32_t* __restrict__ rows,
+                            const uint32_t* __restrict__ flag, const uint32_t* __restrict__ at,
+                            uint32_t* __restrict__ left, uint32_t* __restrict__ pos) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, c = *count;
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < c; q += stride)
+    if (flag[q]) {
+      left[at[q]] = rows[q];
+      pos[at[q]] = (uint32_t)q;
+    }
 }
 
 __global__ void k_clear_words(uint32_t* __restrict__ p, int64_t n) {
@@ -1390,12 +1455,22 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
   hipLaunchKernelGGL(k_finalize_win, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids,
                      J.k, C.het, (int64_t)0, esc, W.counts + 0, W.rec, RECW, J.assign, C.dist, W.fb, W.counts + 1,
                      ctr, 1);
+  const uint32_t* fpos = nullptr;
+  if (blocked) {
+    // the float64 scan visits marked groups too: its rows in the marked order
+    // (k_finalize_win listed the same rows in any order)
+    uint32_t *flag = W.rkey, *at = W.rkey2, *pos = esc == W.rid ? W.rid2 : W.rid;
+    hipLaunchKernelGGL(k_left_flags, dim3(1024), dim3(256), 0, s, W.counts + 0, W.rec, flag);
+    exscan_u32_dn(flag, at, J.n, W.counts + 0, W.rtmp, nullptr, s);
+    hipLaunchKernelGGL(k_left_list, dim3(1024), dim3(256), 0, s, W.counts + 0, esc, flag, at, W.fb, pos);
+    fpos = pos;
+  }
   const int fb_grid = (int)std::min<int64_t>(FB_GRID, ceil_div(J.n, FB_R) * FB_SPLIT);
   switch (C.DP) {
 #define GEEK_FB_CASE(DPV)                                                                                  \
   case DPV:                                                                                                \
     hipLaunchKernelGGL(k_fallback64<DPV>, dim3(fb_grid), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k, \
-                       J.k_dev, C.het, W.fb, W.counts + 1, J.assign, C.dist, W.part_d, W.part_j, ctr);               \
+                       J.k_dev, C.het, W.fb, W.counts + 1, J.assign, C.dist, W.part_d, W.part_j, ctr, fpos, sb);\
     break;
     GEEK_FB_CASE(32)
     GEEK_FB_CASE(64)
