@@ -72,3 +72,18 @@ def test_sig_bits_values_no_hash_spreads():
     sig[:k, 3] = np.resize(values, k)
     so, sm = np.arange(k + 1, dtype=np.uint32), np.arange(k, dtype=np.uint32)  # one member each
     _run(api, sig, so, sm, "search")
+
+
+@pytest.mark.parametrize("F", [7, 256, 300])
+def test_sig_modes_of_small_and_large_seeds(F):
+    # modes counted in LDS (up to 48 members) beside ones found by sorting,
+    # with ties between values
+    api = gpu_api()
+    g = np.random.default_rng(F)
+    n = 500
+    sig = (g.integers(0, 4, size=(n, F)) * 1_000_003).astype(np.uint32)
+    sig[3] = 0xFFFFFFFF
+    sizes = np.array([1, 48, 49, 2, 300, 47, 64, 1, 1, 500, 3])
+    so = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
+    sm = np.concatenate([np.sort(g.choice(n, size=s, replace=False)) for s in sizes]).astype(np.uint32)
+    _run(api, sig, so, sm, "modes")
