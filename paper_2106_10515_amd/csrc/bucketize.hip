@@ -76,7 +76,11 @@ GEEK_D bool key_eq(const uint4& a, const uint4& b) {
 // ---------------------------------------------------------------- partition
 // Fingerprint of every (table, id) and the per-chunk histogram of its top nb
 // bits.  With `given` (the caller's fingerprints of these keys) the keys are
-// not read and nothing is written but the histogram.
+// not read and nothing is written but the histogram.  A thread's loads of
+// FC_B ids are issued together: a short launch is a chain of load latencies
+// otherwise, one per id (64 jobs of 10^3 .. 3 10^5 ids x 16 tables: 54 us a
+// job, 9 us with this and pt_chunk).
+constexpr int FC_B = 8;
 __global__ __launch_bounds__(BZ_THREADS) void k_fp_count(BzArgs a, int nblk, int chunk, uint32_t* counts,
                                                          uint32_t* fp, const uint32_t* given) {
   extern __shared__ uint32_t hist[];
@@ -86,15 +90,42 @@ __global__ __launch_bounds__(BZ_THREADS) void k_fp_count(BzArgs a, int nblk, int
   __syncthreads();
   const int64_t s = (int64_t)blk * chunk;
   const int64_t e = s + chunk < a.n ? s + chunk : a.n;
-  for (int64_t i = s + threadIdx.x; i < e; i += BZ_THREADS) {
-    uint32_t f;
+  const int64_t tn = (int64_t)t * a.n;
+  for (int64_t i0 = s + threadIdx.x; i0 < e; i0 += FC_B * BZ_THREADS) {
+    uint32_t f[FC_B];
     if (given) {
-      f = given[(int64_t)t * a.n + i];
+#pragma unroll
+      for (int u = 0; u < FC_B; ++u) {
+        const int64_t i = i0 + u * BZ_THREADS;
+        f[u] = given[tn + (i < e ? i : i0)];
+      }
     } else {
-      f = fp_of(load_key(a, t, i));
-      fp[(int64_t)t * a.n + i] = f;
+      uint4 key[FC_B];
+      if (a.kw == 4) {  // the branch outside the loads: they are not split by it
+#pragma unroll
+        for (int u = 0; u < FC_B; ++u) {
+          const int64_t i = i0 + u * BZ_THREADS;
+          const uint32_t* k = a.keys + (int64_t)t * a.tstride + (i < e ? i : i0) * a.rstride;
+          key[u] = make_uint4(k[0], k[1], k[2], k[3]);
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < FC_B; ++u) {
+          const int64_t i = i0 + u * BZ_THREADS;
+          key[u] = load_key(a, t, i < e ? i : i0);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < FC_B; ++u) f[u] = fp_of(key[u]);
+#pragma unroll
+      for (int u = 0; u < FC_B; ++u) {
+        const int64_t i = i0 + u * BZ_THREADS;
+        if (i < e) fp[tn + i] = f[u];
+      }
     }
-    atomicAdd(&hist[bin_bits_of(f, a.nb)], 1u);
+#pragma unroll
+    for (int u = 0; u < FC_B; ++u)
+      if (i0 + u * BZ_THREADS < e) atomicAdd(&hist[bin_bits_of(f[u], a.nb)], 1u);
   }
   __syncthreads();
   uint32_t* out = counts + ((int64_t)t * nblk + blk) * nbins;
@@ -299,18 +330,18 @@ __device__ void part_rounds(PartLds& L, int nbins, int nbits, int shift, int64_t
   }
 }
 
-// First pass: block (chunk of PT_SUPER ids, table) -> 2^nb1 bins by the top
-// nb1 bits of the fingerprint (nb1 <= PT_B1).
-__global__ __launch_bounds__(BZ_THREADS) void k_p1_scatter(BzArgs a, int nb1, int nblk, const uint32_t* counts,
-                                                           const uint32_t* binstart, const uint32_t* fp,
+// First pass: block (chunk of ids, table) -> 2^nb1 bins by the top nb1 bits of
+// the fingerprint (nb1 <= PT_B1).
+__global__ __launch_bounds__(BZ_THREADS) void k_p1_scatter(BzArgs a, int nb1, int nblk, int chunk,
+                                                           const uint32_t* counts, const uint32_t* binstart, const uint32_t* fp,
                                                            BzRec* out) {
   __shared__ PartLds L;
   const int t = blockIdx.y, blk = blockIdx.x;
   const int nbins = 1 << nb1;
   for (int b = threadIdx.x; b < nbins; b += BZ_THREADS)
     L.cur[b] = binstart[(int64_t)t * nbins + b] + counts[((int64_t)t * nblk + blk) * nbins + b];
-  const int64_t s = (int64_t)blk * PT_SUPER;
-  const int64_t e = s + PT_SUPER < a.n ? s + PT_SUPER : a.n;
+  const int64_t s = (int64_t)blk * chunk;
+  const int64_t e = s + chunk < a.n ? s + chunk : a.n;
   const uint32_t* fpt = fp + (int64_t)t * a.n;
   part_rounds(L, nbins, nb1, 32 - nb1, e - s,
               [&](int64_t q, uint32_t& f, uint32_t& id) {
@@ -1215,6 +1246,17 @@ static int bin_bits(int64_t n) {
   return nb;
 }
 
+// Ids per workgroup of the fingerprint count and the first partition pass:
+// PT_SUPER, or less (down to one round) where that leaves the chip without two
+// workgroups per CU: a workgroup takes its rounds one after the other (64 jobs
+// of 10^3 .. 3 10^5 ids x 16 tables: the scatter 30 us a job with 16,384 ids
+// per workgroup, 12 us now; 10^7 x 32: the same chunks and time as before).
+static int pt_chunk(int64_t n, int T) {
+  int c = PT_SUPER;
+  while (c > PT_ROUND && (int64_t)ceil_div(n, c) * T < 512) c >>= 1;
+  return c;
+}
+
 struct BzWs {
   uint32_t *counts, *bintot, *binstart, *fp;
   BzRec *st, *alt;  // partitioned records: final bins, first-pass bins
@@ -1228,7 +1270,7 @@ static size_t carve_bz(const geek_bucketize_job& J, void* ws, BzWs& W) {
   Carver c(ws);
   const int nb = bin_bits(J.n);
   const int nbins = 1 << nb;
-  const int nblk = ceil_div(J.n, PT_SUPER);
+  const int chunk = pt_chunk(J.n, J.T), nblk = ceil_div(J.n, chunk);
   const int nch = ceil_div(J.n, SC_CHUNK);
   const size_t Tn = (size_t)J.T * J.n;
   const int64_t fw = ceil_div(J.n, 16) * 16;
@@ -1270,7 +1312,7 @@ int32_t bucketize_run(const geek_bucketize_job& J, void* ws, size_t ws_bytes, in
   if (ws_bytes < carve_bz(J, ws, W)) return GEEK_ERR_WORKSPACE;
   const int nb = bin_bits(J.n);
   const int nbins = 1 << nb;
-  const int nblk = ceil_div(J.n, PT_SUPER);
+  const int chunk = pt_chunk(J.n, J.T), nblk = ceil_div(J.n, chunk);
   const int nch = ceil_div(J.n, SC_CHUNK);
   const int64_t fw = ceil_div(J.n, 16) * 16;
   BzArgs a{J.keys, J.n, J.T, J.key_words, J.table_stride, J.row_stride, nb};
@@ -1295,12 +1337,12 @@ int32_t bucketize_run(const geek_bucketize_job& J, void* ws, size_t ws_bytes, in
                      reinterpret_cast<uint4*>(W.flag8), (int64_t)J.T * fw / 16 + 1);
   uint32_t* nhard = reinterpret_cast<uint32_t*>(W.flag8 + (size_t)J.T * fw);
   if (nb <= PT_B1) {
-    hipLaunchKernelGGL(k_fp_count, dim3(nblk, J.T), dim3(BZ_THREADS), (size_t)nbins * 4, s, a, nblk, PT_SUPER,
+    hipLaunchKernelGGL(k_fp_count, dim3(nblk, J.T), dim3(BZ_THREADS), (size_t)nbins * 4, s, a, nblk, chunk,
                        W.counts, W.fp, given);
     hipLaunchKernelGGL(k_bin_colscan, dim3(ceil_div((int64_t)J.T * nbins, 256)), dim3(256), 0, s, J.T,
                        nblk, nbins, W.counts, W.bintot);
     hipLaunchKernelGGL(k_bin_rowscan, dim3(J.T), dim3(1024), 0, s, nbins, W.bintot, W.binstart);
-    hipLaunchKernelGGL(k_p1_scatter, dim3(nblk, J.T), dim3(BZ_THREADS), 0, s, a, nb, nblk, W.counts, W.binstart,
+    hipLaunchKernelGGL(k_p1_scatter, dim3(nblk, J.T), dim3(BZ_THREADS), 0, s, a, nb, nblk, chunk, W.counts, W.binstart,
                        fps, W.st);
   } else {
     // first pass into the alternate buffers by the top PT_B1 bits, second
@@ -1310,12 +1352,12 @@ int32_t bucketize_run(const geek_bucketize_job& J, void* ws, size_t ws_bytes, in
     const int nb1bins = J.T << PT_B1;
     const int F = 1 << (nb - PT_B1);
     const int maxchunks = (int)p2_max_chunks(J.n, J.T);
-    hipLaunchKernelGGL(k_fp_count, dim3(nblk, J.T), dim3(BZ_THREADS), (size_t)4 << PT_B1, s, a1, nblk, PT_SUPER,
+    hipLaunchKernelGGL(k_fp_count, dim3(nblk, J.T), dim3(BZ_THREADS), (size_t)4 << PT_B1, s, a1, nblk, chunk,
                        W.counts, W.fp, given);
     hipLaunchKernelGGL(k_bin_colscan, dim3(ceil_div(nb1bins, 256)), dim3(256), 0, s, J.T, nblk, 1 << PT_B1,
                        W.counts, W.bintot1);
     hipLaunchKernelGGL(k_bin_rowscan, dim3(J.T), dim3(1024), 0, s, 1 << PT_B1, W.bintot1, W.binstart1);
-    hipLaunchKernelGGL(k_p1_scatter, dim3(nblk, J.T), dim3(BZ_THREADS), 0, s, a1, PT_B1, nblk, W.counts,
+    hipLaunchKernelGGL(k_p1_scatter, dim3(nblk, J.T), dim3(BZ_THREADS), 0, s, a1, PT_B1, nblk, chunk, W.counts,
                        W.binstart1, fps, W.alt);
     hipLaunchKernelGGL(k_p2_chunks, dim3(1), dim3(1024), 0, s, nb1bins, W.bintot1, W.cbase, W.cbin);
     hipLaunchKernelGGL(k_p2_count, dim3(maxchunks), dim3(BZ_THREADS), 0, s, J.n, nb, W.cbase, W.cbin, nb1bins,

@@ -65,3 +65,19 @@ def test_sse_and_radius_sizes(n, k):
         assert np.array_equal(out["radius"].cpu().numpy(), oracle.radius(dist, a, k))
         again = api.assign_euclid(cuda(X), cuda(so), cuda(sm), k, prec, want_radius=False, want_dist=False)
         assert again["sse"].item() == oracle.sse(dist)
+
+
+@pytest.mark.parametrize("n,T", [(2049, 1), (4096, 2), (4097, 2), (12289, 40), (20001, 128), (40000, 128), (33000, 256)])
+def test_partition_chunk_sizes(n, T):
+    # workgroups of the first partition pass take 4,096, 8,192 or 16,384 ids
+    api = gpu_api()
+    g = np.random.default_rng(n + T)
+    keys = g.integers(0, 90, size=(T, n, 4)).astype(np.uint32)
+    keys[:, :, 2:] = 0
+    announce(f"bucketize chunks n={n} T={T}")
+    mem, off, nb, bof = api.bucketize(cuda(keys), n, T, 4, n * 4, 4)
+    for t in {0, T // 2, T - 1}:
+        rm, ro, rb = oracle.bucketize(keys[t].astype(np.int64))
+        assert int(nb[t]) == len(ro) - 1
+        assert np.array_equal(host_u32(mem[t]), rm) and np.array_equal(host_u32(off[t])[:len(ro)], ro)
+        assert np.array_equal(host_u32(bof[t]), rb)
