@@ -1028,15 +1028,17 @@ GEEK_D double chain_add(const double* v, int cnt, double acc) {
 
 // One workgroup per 4096-row block: a coalesced copy into LDS, then one lane
 // adds the block's values in row order.
-__global__ __launch_bounds__(256) void k_sse_blocks(const double* __restrict__ dist, int64_t n,
-                                                    double* __restrict__ blk) {
-  __shared__ __attribute__((aligned(16))) double v[SSE_BLOCK];
-  const int64_t b = blockIdx.x;
+GEEK_D void sse_block(double* v, int64_t b, const double* __restrict__ dist, int64_t n, double* __restrict__ blk) {
   const int64_t s = b * SSE_BLOCK;
   const int cnt = (int)(n - s < SSE_BLOCK ? n - s : SSE_BLOCK);
   for (int i = threadIdx.x; i < cnt; i += 256) v[i] = dist[s + i];
   __syncthreads();
   if (threadIdx.x == 0) blk[b] = chain_add(v, cnt, 0.0);
+}
+__global__ __launch_bounds__(256) void k_sse_blocks(const double* __restrict__ dist, int64_t n,
+                                                    double* __restrict__ blk) {
+  __shared__ __attribute__((aligned(16))) double v[SSE_BLOCK];
+  sse_block(v, blockIdx.x, dist, n, blk);
 }
 
 __global__ __launch_bounds__(256) void k_sse_total(const double* __restrict__ blk, int64_t nb, double* __restrict__ out) {
@@ -1071,20 +1073,39 @@ __global__ void k_radius(const int32_t* __restrict__ assign, const double* __res
 // non-negative doubles order like the values), then one global atomic per
 // touched slot.
 constexpr int RAD_LDS = 4096, RAD_LDS_BIG = 16384;
-template <int CAP>
-__global__ __launch_bounds__(256) void k_radius_lds(const int32_t* __restrict__ assign,
-                                                    const double* __restrict__ dist, int64_t n, int k, int take_sqrt,
-                                                    double* __restrict__ rad) {
-  __shared__ unsigned long long m[CAP];
+GEEK_D void radius_lds(unsigned long long* m, int64_t b, int64_t nb, const int32_t* __restrict__ assign,
+                       const double* __restrict__ dist, int64_t n, int k, int take_sqrt, double* __restrict__ rad) {
   for (int j = threadIdx.x; j < k; j += 256) m[j] = 0ull;
   __syncthreads();
-  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = b * 256 + threadIdx.x; i < n; i += nb * 256) {
     const int a = assign[i];
     if ((unsigned)a < (unsigned)k) atomicMax(&m[a], (unsigned long long)__double_as_longlong(dist[i]));
   }
   __syncthreads();
   for (int j = threadIdx.x; j < k; j += 256)
     if (m[j]) atomic_max_nonneg(rad + j, radius_of(__longlong_as_double((long long)m[j]), take_sqrt));
+}
+template <int CAP>
+__global__ __launch_bounds__(256) void k_radius_lds(const int32_t* __restrict__ assign,
+                                                    const double* __restrict__ dist, int64_t n, int k, int take_sqrt,
+                                                    double* __restrict__ rad) {
+  __shared__ unsigned long long m[CAP];
+  radius_lds(m, blockIdx.x, gridDim.x, assign, dist, n, k, take_sqrt, rad);
+}
+
+// Up to RAD_LDS clusters: workgroups 0 .. nblk - 1 take one block of the SSE
+// each, the others the radii, which are done while the SSE's chains (37 us
+// each) run; two launches one after the other before.
+static_assert(RAD_LDS == SSE_BLOCK, "one array serves both");
+__global__ __launch_bounds__(256) void k_sse_radius(const double* __restrict__ dist, const int32_t* __restrict__ assign,
+                                                    int64_t n, int k, int nblk, double* __restrict__ blk,
+                                                    double* __restrict__ rad, int take_sqrt) {
+  __shared__ __attribute__((aligned(16))) double v[SSE_BLOCK];
+  if ((int)blockIdx.x < nblk)
+    sse_block(v, blockIdx.x, dist, n, blk);
+  else
+    radius_lds(reinterpret_cast<unsigned long long*>(v), (int)blockIdx.x - nblk, (int)gridDim.x - nblk, assign, dist, n,
+               k, take_sqrt, rad);
 }
 
 // Both for one block of rows and at most SMALL_K clusters.
@@ -1143,14 +1164,16 @@ void sse_and_radius(const double* dist, const int32_t* assign, int64_t n, int k,
     return;
   }
   const int64_t nblk = (n + SSE_BLOCK - 1) / SSE_BLOCK;
-  hipLaunchKernelGGL(k_sse_blocks, dim3(nblk), dim3(256), 0, s, dist, n, sse_blk);
+  if (radius && !zeroed) hipLaunchKernelGGL(k_fill_f64, dim3(ceil_div(k, 256)), dim3(256), 0, s, radius, k, 0.0);
+  const bool both = radius && k <= RAD_LDS;
+  if (both)
+    hipLaunchKernelGGL(k_sse_radius, dim3((int)nblk + (int)std::min<int64_t>(ceil_div(n, 4096), 512)), dim3(256), 0, s,
+                       dist, assign, n, k, (int)nblk, sse_blk, radius, take_sqrt);
+  else
+    hipLaunchKernelGGL(k_sse_blocks, dim3(nblk), dim3(256), 0, s, dist, n, sse_blk);
   hipLaunchKernelGGL(k_sse_total, dim3(1), dim3(256), 0, s, sse_blk, nblk, sse);
-  if (radius) {
-    if (!zeroed) hipLaunchKernelGGL(k_fill_f64, dim3(ceil_div(k, 256)), dim3(256), 0, s, radius, k, 0.0);
-    if (k <= RAD_LDS)
-      hipLaunchKernelGGL(k_radius_lds<RAD_LDS>, dim3((int)std::min<int64_t>(ceil_div(n, 4096), 512)), dim3(256), 0,
-                         s, assign, dist, n, k, take_sqrt, radius);
-    else if (k <= RAD_LDS_BIG)  // 128 KB of LDS: one workgroup per CU, fewer of them
+  if (radius && !both) {
+    if (k <= RAD_LDS_BIG)  // 128 KB of LDS: one workgroup per CU, fewer of them
       hipLaunchKernelGGL(k_radius_lds<RAD_LDS_BIG>, dim3((int)std::min<int64_t>(ceil_div(n, 16384), 128)), dim3(256),
                          0, s, assign, dist, n, k, take_sqrt, radius);
     else

@@ -81,3 +81,17 @@ def test_partition_chunk_sizes(n, T):
         assert int(nb[t]) == len(ro) - 1
         assert np.array_equal(host_u32(mem[t]), rm) and np.array_equal(host_u32(off[t])[:len(ro)], ro)
         assert np.array_equal(host_u32(bof[t]), rb)
+
+
+@pytest.mark.parametrize("n,k", [(4097, 4096), (12288, 4096), (12289, 4097), (20011, 1)])
+def test_sse_beside_radii(n, k):
+    api = gpu_api()
+    g = np.random.default_rng(n + k)
+    X = g.normal(size=(n, 3)).astype(np.float32)
+    so, sm = np.arange(k + 1, dtype=np.uint32), g.integers(0, n, size=k).astype(np.uint32)
+    announce(f"sse beside radii n={n} k={k}")
+    a, dist = oracle.assign_euclid(X, oracle.centroids(X, so, sm))
+    out = api.assign_euclid(cuda(X), cuda(so), cuda(sm), k, 1)
+    assert np.array_equal(out["assign"].cpu().numpy(), a)
+    assert out["sse"].item() == oracle.sse(dist)
+    assert np.array_equal(out["radius"].cpu().numpy(), oracle.radius(dist, a, k))
