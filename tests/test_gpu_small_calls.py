@@ -95,3 +95,21 @@ def test_sse_beside_radii(n, k):
     assert np.array_equal(out["assign"].cpu().numpy(), a)
     assert out["sse"].item() == oracle.sse(dist)
     assert np.array_equal(out["radius"].cpu().numpy(), oracle.radius(dist, a, k))
+
+
+@pytest.mark.parametrize("d", [1, 7, 31, 33, 64, 65, 127, 129, 255, 256])
+def test_hash_norms_of_ragged_depths(d):
+    # eight lanes share a projection row's norm: depths that leave some of them short
+    api = gpu_api()
+    g = np.random.default_rng(d)
+    n, m, L, w = 300, 5, 13, 3.0
+    X = g.normal(size=(n, d)).astype(np.float32)
+    A, b = g.normal(size=(m * L, d)).astype(np.float32), (g.random(m * L) * w).astype(np.float32)
+    announce(f"hash norms d={d}")
+    codes = oracle.e2lsh_codes(X, A, b, w)
+    keys, _ = api.hash_dense(cuda(X), cuda(A), cuda(b), m, L, w)
+    mem, off, nb, bof = api.bucketize(keys, n, L, 4, n * 4, 4)
+    for t in range(L):
+        rm, ro, rb = oracle.bucketize(codes[:, t * m:(t + 1) * m])
+        assert int(nb[t]) == len(ro) - 1
+        assert np.array_equal(host_u32(mem[t]), rm) and np.array_equal(host_u32(off[t])[:len(ro)], ro)
