@@ -375,9 +375,31 @@ __device__ void block_add_u64(unsigned long long* dst, unsigned long long v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, v);
 }
+// Both sums of a workgroup of 256, one atomic each: atomics of one address take
+// about 10 ns each over the whole chip, so a count per wavefront was most of
+// the float64 distances' time for some 10^5 rows (246 us of 256 with eight
+// lanes per row).
+__device__ void block_add2_u64(unsigned long long* dst0, unsigned long long* dst1, unsigned long long v0,
+                               unsigned long long v1) {
+  __shared__ unsigned long long part[2][4];
+  for (int o = 32; o > 0; o >>= 1) {
+    v0 += __shfl_xor(v0, o);
+    v1 += __shfl_xor(v1, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    part[0][threadIdx.x >> 6] = v0;
+    part[1][threadIdx.x >> 6] = v1;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const unsigned long long* q = part[threadIdx.x];
+    const unsigned long long v = q[0] + q[1] + q[2] + q[3];
+    if (v) atomicAdd(threadIdx.x ? dst1 : dst0, v);
+  }
+}
 
 // Candidate windows (RECW records: the float32 first pass, the rescans): a lane per row, each lane walking its own row's candidates.
-__global__ void k_finalize_win(const float* __restrict__ X, int64_t ldx, int d,
+__global__ __launch_bounds__(256) void k_finalize_win(const float* __restrict__ X, int64_t ldx, int d,
                            const double* __restrict__ C, int k, Het het, int64_t n_rows,
                            const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
                            const int32_t* __restrict__ rec, int rstride, int32_t* __restrict__ assign,
@@ -419,8 +441,7 @@ __global__ void k_finalize_win(const float* __restrict__ X, int64_t ldx, int d,
     ncand += (unsigned long long)c;
   }
   if (ctr) {
-    block_add_u64(ctr + ctr_rows, nrow);
-    block_add_u64(ctr + 3, ncand);
+    block_add2_u64(ctr + ctr_rows, ctr + 3, nrow, ncand);
   }
 }
 
@@ -446,6 +467,10 @@ __global__ __launch_bounds__(256) void k_finalize(const float* __restrict__ X, i
                                                   uint32_t* __restrict__ esc, uint32_t* __restrict__ esc_count,
                                                   unsigned long long* __restrict__ ctr, int ctr_rows) {
   __shared__ double sq[4][FZ_ROWS][FZ_STEP + 2];  // + 2: the eight row leaders read distinct banks
+  // escalated rows wait here, and leave with one atomic per 57 or more (with
+  // one per eight rows, 10^6 escalated rows took 1.4 ms)
+  __shared__ uint32_t left[4][64];
+  int nleft = 0;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int g = lane >> 3, e = lane & 7;  // row slot, lane within the row
   const int64_t count = rows ? (int64_t)*rows_count : n_rows;
@@ -453,15 +478,29 @@ __global__ __launch_bounds__(256) void k_finalize(const float* __restrict__ X, i
   const bool xal = ((reinterpret_cast<uintptr_t>(X) | (uintptr_t)(ldx * 4)) & 15) == 0;
   const bool cal = ((reinterpret_cast<uintptr_t>(C) | (uintptr_t)(d * 8)) & 15) == 0;
   unsigned long long nrow = 0, ncand = 0;
+  auto flush = [&]() {
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(esc_count, (uint32_t)nleft);
+    at = (uint32_t)__shfl((int)at, 0);
+    if (lane < nleft) esc[at + lane] = left[wv][lane];
+    nleft = 0;
+    __builtin_amdgcn_wave_barrier();
+  };
   for (int64_t base = ((int64_t)blockIdx.x * 4 + wv) * FZ_ROWS; base < count; base += stride) {
     const int64_t pos = base + g;
     const bool live = pos < count;
     const int64_t i = live ? (rows ? (int64_t)rows[pos] : pos) : 0;
     const int32_t* rr = rec + (live ? pos : 0) * rstride;
     int c = live ? rr[0] : 0;
-    if (live && c <= 0) {  // window overflow (or no finite candidate): escalate
-      if (e == 0) esc[atomicAdd(esc_count, 1u)] = (uint32_t)i;
-      c = 0;
+    const bool over = live && c <= 0;  // window overflow (or no finite candidate): escalate
+    const uint64_t om = __ballot(over && e == 0);
+    if (over) c = 0;
+    if (om) {  // nleft is at most 64 - FZ_ROWS here
+      if (over && e == 0) left[wv][nleft + __popcll(om & ((1ull << lane) - 1ull))] = (uint32_t)i;
+      nleft += __popcll(om);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (nleft > 64 - FZ_ROWS) flush();
     }
     int maxc = c;  // the wavefront walks the largest candidate count of its rows
 #pragma unroll
@@ -524,9 +563,9 @@ __global__ __launch_bounds__(256) void k_finalize(const float* __restrict__ X, i
       ncand += (unsigned long long)c;
     }
   }
+  if (nleft) flush();
   if (ctr) {
-    block_add_u64(ctr + ctr_rows, nrow);
-    block_add_u64(ctr + 3, ncand);
+    block_add2_u64(ctr + ctr_rows, ctr + 3, nrow, ncand);
   }
 }
 
@@ -1455,17 +1494,19 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
                           const unsigned long long* t0) {
   AssignWs& W = C.W;
   unsigned long long* ctr = W.ctr;
-  const int fz_grid = (int)std::min<int64_t>(ceil_div(J.n, 4 * FZ_ROWS), 8192);
+  const int fz_grid = (int)std::min<int64_t>(
+      8192, std::max<int64_t>(ceil_div(J.n, 1024), std::min<int64_t>(ceil_div(J.n, 8 * FZ_ROWS), 2048)));
   const int rstride = low_precision(J) ? RECW_T2 : RECW;
-  // eight lanes per row for the BF16 records of large jobs (10^7 rows at
-  // d = 128: 3.3 against 4.0 ms); the batched workload's jobs (10^3 .. 10^6
-  // rows on four streams) ran 36 ms slower in all with it than with a lane
-  // per row, for reasons not yet found, so smaller jobs keep a lane per row
-  if (rstride == RECW_T2 && J.n >= ((int64_t)1 << 20))
+  // Eight lanes per row for the BF16 records of many wide rows, whose lines do
+  // not stay in the caches between a lane's steps (whole assignment, k = 500,
+  // eight lanes against one: 10^6 x 256 1.20 / 1.26 ms, 1.5 10^6 x 128 0.82 /
+  // 0.84, 5 10^5 x 128 0.33 / 0.33; but 2 10^5 x 128 0.213 / 0.206, 1.5 10^6 x
+  // 64 0.48 / 0.47, x 20 0.28 / 0.23).
+  if (rstride == RECW_T2 && J.d > 64 && J.n * J.d >= ((int64_t)1 << 26))
     hipLaunchKernelGGL(k_finalize, dim3(fz_grid), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k, C.het, J.n,
                        nullptr, nullptr, W.rec, rstride, J.assign, C.dist, W.esc, W.counts + 0, ctr, 0);
   else
-    hipLaunchKernelGGL(k_finalize_win, dim3(ceil_div(J.n, 256)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k,
+    hipLaunchKernelGGL(k_finalize_win, dim3((int)std::min<int64_t>(ceil_div(J.n, 256), 1024)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k,
                        C.het, J.n, nullptr, nullptr, W.rec, rstride, J.assign, C.dist, W.esc, W.counts + 0, ctr, 0);
   // rows with several first-pass candidates: float32 rescan of those rows with
   // a wider window (persistent grids, at most one row tile / block per group)

@@ -567,7 +567,6 @@ __global__ __launch_bounds__(SB_THREADS) void k_sig_bits(const uint32_t* __restr
   const int g = lane / GL, sub = lane % GL;
   const uint32_t row_bytes = GL * SB_VW * 4;
   const int64_t tiles = (n + R - 1) / R, waves = (int64_t)gridDim.x * (SB_THREADS / 64);
-  unsigned long long rows_done = 0;
   for (int64_t t = (int64_t)blockIdx.x * (SB_THREADS / 64) + wave; t < tiles; t += waves) {
     const int64_t i0 = t * R;
     // mask rows of the positions that share a value with some mode: the words
@@ -698,10 +697,9 @@ __global__ __launch_bounds__(SB_THREADS) void k_sig_bits(const uint32_t* __restr
       assign[i0 + g] = (sub * SB_VW + w) * 32 + __ffs(cw) - 1;
       dist[i0 + g] = 1.0 - (double)best / (double)F;
     }
-    rows_done += (unsigned long long)(n - i0 < R ? n - i0 : R);
     __builtin_amdgcn_wave_barrier();
   }
-  if (lane == 0 && rows_done) atomicAdd(ctr + 2, rows_done);
+  if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(ctr + 2, (unsigned long long)n);  // every row, counted once
 }
 
 __global__ void k_zero_words(uint32_t* p, int n) {

@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void k_sig_big(const uint32_t* __restrict__ me
       if (lane == k && k < K) G[(int64_t)g * K + k] = mn[k];
     done += (unsigned long long)sz * K;
   }
-  if (evals && lane == 0 && done) atomicAdd(evals, done);
+  if (evals) block_add(lane == 0 ? done : 0ull, evals);
 }
 
 // ---- bins of identical G (SILK tables) ---------------------------------------
