@@ -4,7 +4,7 @@
 //   k_centroids   float64 centroids, one thread per (seed, dim), members summed
 //                 in ascending order one rounding at a time (exact parity),
 //                 their values loaded 32 at a time.
-//   k_cprep       centroid copies in the matrix-core input type (fp32 / bf16),
+//   k_cprep       centroid copies for the matrix cores (bf16; two float16 pieces),
 //                 |c|^2 and max |c| for the error bound.
 //   k_scan<M,DP>  matrix-core tile |x|^2 - 2 x.c + |c|^2 over all centroids for
 //                 a block of rows.  Float32: per row it keeps every centroid
@@ -1232,7 +1232,7 @@ int32_t modes_compute(const uint32_t* V, int64_t ldv, int F, int64_t n, const ui
 // e4m3 products run at the bf16 rate in the 32x32x16 form, and e4m3's error
 // window (2^-3) left most rows with more candidates than a lane's window holds,
 // so that a float32 rescan of nearly every row followed: 2 10^6 heterogeneous
-// rows, k = 1,000, hash and buckets included: 54.0 ms in e4m3, 10.4 ms now;
+// rows, k = 1,000, hash and buckets included: 54.0 ms in e4m3, 9.5 ms now;
 // 805,748 x 115 rows, k = 1,312: 4.11 against 1.68 ms.
 static bool low_precision(const geek_assign_job& J) {
   return J.precision == GEEK_PREC_BF16 || J.precision == GEEK_PREC_FP8;
