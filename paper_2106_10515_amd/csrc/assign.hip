@@ -912,7 +912,8 @@ __global__ void k_row_keys(const uint32_t* __restrict__ rows, const uint32_t* __
 }
 
 // Marks for every tile of 128 rows the groups of 64 seeds in which some row has
-// a bf16 value within its window.  A block takes 256 rows (64 per wavefront)
+// a bf16 value within its window, and every group where some row has no bound
+// (thr = +inf).  A block takes 256 rows (64 per wavefront)
 // and streams the seeds through two LDS stages as the first pass does; a
 // value's test is one max and, per 16 of them, one comparison.
 template <int DP>
@@ -934,12 +935,16 @@ __global__ __launch_bounds__(SCAN_THREADS, 2) void k_mark(const float* __restric
   if (tile * 256 >= count) return;
   M::frag xb[NCB][S];
   float least[NCB];  // accumulator value from which a seed counts: v = -2 acc <= thr
+  bool every = false;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
     const int64_t pos = tile * 256 + w * 64 + cb * 32 + p;
     const bool valid = pos < count;
     const int64_t i = valid ? (int64_t)rows[pos] : 0;
     least[cb] = valid ? -0.5f * thr[i] : INFINITY;
+    // a row without a bound: its values may overflow with both signs, and no
+    // comparison holds for the NaN of such a sum
+    every = every || least[cb] == -INFINITY;
     const float* xr = X + i * ldx + h * (DP / 2);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -971,7 +976,7 @@ __global__ __launch_bounds__(SCAN_THREADS, 2) void k_mark(const float* __restric
   uint32_t bits = 0u;
   auto stage = [&](const __bf16* cur, int b, __bf16* nxt, int c0) {
     if (c0 + SCAN_BC < k_pad) dma(c0 + SCAN_BC, nxt);
-    bool hit = false;
+    bool hit = every;
 #pragma unroll
     for (int rb = 0; rb < SCAN_BC / 32; ++rb) {
       const int R = rb * 32 + p;
