@@ -84,8 +84,8 @@ __global__ __launch_bounds__(MODE_THREADS) void k_mode_small(const uint32_t* __r
   modes[j * F + f] = best;
 }
 
-// Members of the seeds the sort takes (0 for the others), and their items:
-// (position's segment, value) at boff[j] F + f s_j + q.
+// Members of the seeds the sort takes (0 for the others), and the items of
+// positions f0 .. f0 + F - 1: (position's segment, value) at boff[j] F + f s_j + q.
 __global__ void k_mode_sizes(const uint32_t* __restrict__ so, int k, uint32_t* __restrict__ size) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= k) return;
@@ -95,7 +95,7 @@ __global__ void k_mode_sizes(const uint32_t* __restrict__ so, int k, uint32_t* _
 __global__ void k_mode_total(const uint32_t* __restrict__ members, int F, uint32_t* __restrict__ items) {
   if (threadIdx.x == 0) *items = *members * (uint32_t)F;
 }
-__global__ void k_mode_items(const uint32_t* __restrict__ V, int64_t ldv, int F, int64_t n,
+__global__ void k_mode_items(const uint32_t* __restrict__ V, int64_t ldv, int f0, int F, int64_t n,
                              const uint32_t* __restrict__ so, const uint32_t* __restrict__ sm, int k,
                              const uint32_t* __restrict__ boff, const uint32_t* __restrict__ items,
                              uint32_t* __restrict__ val, uint32_t* __restrict__ seg, int32_t* st) {
@@ -115,13 +115,14 @@ __global__ void k_mode_items(const uint32_t* __restrict__ V, int64_t ldv, int F,
     const int64_t at = (int64_t)boff[j] * F + (int64_t)f * sj + q;
     const bool ok = (int64_t)id < n;
     if (!ok) set_status(st, GEEK_ERR_ARG);
-    val[at] = ok ? V[(int64_t)id * ldv + f] : 0u;
+    val[at] = ok ? V[(int64_t)id * ldv + f0 + f] : 0u;
     seg[at] = (uint32_t)j * (uint32_t)F + (uint32_t)f;
   }
 }
 
 __global__ void k_mode_pick(const uint32_t* __restrict__ val, const uint32_t* __restrict__ so,
-                            const uint32_t* __restrict__ boff, int k, int F, uint32_t* __restrict__ modes) {
+                            const uint32_t* __restrict__ boff, int k, int f0, int F, int ldm,
+                            uint32_t* __restrict__ modes) {
   const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (g >= (int64_t)k * F) return;
   const int j = (int)(g / F), f = (int)(g % F);
@@ -142,7 +143,7 @@ __global__ void k_mode_pick(const uint32_t* __restrict__ val, const uint32_t* __
     }
   }
   if (ccnt > bcnt) best = cur;
-  modes[g] = best;
+  modes[(int64_t)j * ldm + f0 + f] = best;
 }
 
 // (f, value, j) triples of the modes for the inverted index
@@ -732,7 +733,7 @@ static bool sig_use_bits(const geek_assign_job& J) {
 }
 
 struct SigWs {
-  int64_t NI;  // mode items: members * F
+  int64_t NI;  // mode items sorted together: members * positions of a slice
   uint32_t *val, *seg, *val2, *seg2;
   uint32_t *boff, *bcount;  // modes by sorting: first member of each seed; members, items
   uint32_t *wj, *wv, *wf, *wj2, *wv2, *wf2;
@@ -759,10 +760,16 @@ static int bits_of(uint64_t v) {
   return b;
 }
 
+// Positions whose items are sorted together: as many as keep the sort's 32-bit
+// item count (and segment number: k <= NC) below 2^31.
+static int mode_slice(int64_t NC, int F) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(F, ((int64_t)1 << 31) / std::max<int64_t>(NC, 1)));
+}
+
 static size_t carve_sig(const geek_assign_job& J, void* ws, SigWs& W) {
   Carver c(ws);
   const int64_t F = J.F;
-  const int64_t NI = J.n_members * F;
+  const int64_t NI = J.n_members * mode_slice(J.n_members, J.F);
   const int64_t KI = (int64_t)J.k * F;
   const int64_t NR = NI > KI ? NI : KI;
   W.NI = NI;
@@ -816,23 +823,27 @@ int32_t modes_run(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32
   if (NC <= MODE_SMALL) return GEEK_OK;  // no seed can be larger
   hipLaunchKernelGGL(k_mode_sizes, dim3(ceil_div(k, 256)), dim3(256), 0, s, so, k, W.boff);
   exscan_u32(W.boff, W.boff, k, W.rtmp, W.bcount, s);
-  hipLaunchKernelGGL(k_mode_total, dim3(1), dim3(64), 0, s, W.bcount, F, W.bcount + 1);
-  hipLaunchKernelGGL(k_mode_items, dim3((int)std::min<int64_t>(4096, ceil_div(NI, 256))), dim3(256), 0, s, V, ldv, F, n,
-                     so, sm, k, W.boff, W.bcount + 1, W.val, W.seg, st);
-  int words[8], shifts[8], np = 0;
-  for (int sh = 0; sh < 32; sh += 8) {
-    words[np] = 0;
-    shifts[np++] = sh;
+  const int slice = mode_slice(NC, F);
+  for (int f0 = 0; f0 < F; f0 += slice) {
+    const int Fs = std::min(slice, F - f0);
+    hipLaunchKernelGGL(k_mode_total, dim3(1), dim3(64), 0, s, W.bcount, Fs, W.bcount + 1);
+    hipLaunchKernelGGL(k_mode_items, dim3((int)std::min<int64_t>(4096, ceil_div(NC * Fs, 256))), dim3(256), 0, s, V,
+                       ldv, f0, Fs, n, so, sm, k, W.boff, W.bcount + 1, W.val, W.seg, st);
+    int words[8], shifts[8], np = 0;
+    for (int sh = 0; sh < 32; sh += 8) {
+      words[np] = 0;
+      shifts[np++] = sh;
+    }
+    const int sb = bits_of((uint64_t)k * Fs - 1);
+    for (int sh = 0; sh < sb; sh += 8) {
+      words[np] = 1;
+      shifts[np++] = sh;
+    }
+    RsView A{{W.val, W.seg, nullptr, nullptr}, nullptr}, B{{W.val2, W.seg2, nullptr, nullptr}, nullptr};
+    const int alt = radix_sort_dn(A, B, 2, NC * Fs, W.bcount + 1, words, shifts, np, W.rtmp, s);
+    hipLaunchKernelGGL(k_mode_pick, dim3(ceil_div((int64_t)k * Fs, 256)), dim3(256), 0, s, alt ? W.val2 : W.val, so,
+                       W.boff, k, f0, Fs, F, modes);
   }
-  const int sb = bits_of((uint64_t)k * F - 1);
-  for (int sh = 0; sh < sb; sh += 8) {
-    words[np] = 1;
-    shifts[np++] = sh;
-  }
-  RsView A{{W.val, W.seg, nullptr, nullptr}, nullptr}, B{{W.val2, W.seg2, nullptr, nullptr}, nullptr};
-  const int alt = radix_sort_dn(A, B, 2, NI, W.bcount + 1, words, shifts, np, W.rtmp, s);
-  hipLaunchKernelGGL(k_mode_pick, dim3(ceil_div((int64_t)k * F, 256)), dim3(256), 0, s, alt ? W.val2 : W.val, so, W.boff,
-                     k, F, modes);
   return GEEK_OK;
 }
 
@@ -840,7 +851,7 @@ int32_t modes_run(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32
 // heterogeneous rows), with its own workspace.
 size_t modes_ws(int64_t n_members, int F, int k) {
   Carver c(nullptr);
-  const int64_t NI = n_members * F, KI = (int64_t)k * F;
+  const int64_t NI = n_members * mode_slice(n_members, F), KI = (int64_t)k * F;
   const int64_t NR = NI > KI ? NI : KI;
   for (int q = 0; q < 4; ++q) c.take<uint32_t>(NR + 1);
   c.take<uint32_t>(k + 1);
@@ -852,7 +863,7 @@ size_t modes_ws(int64_t n_members, int F, int k) {
 int32_t modes_compute(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32_t* so, const uint32_t* sm,
                       int k, int64_t NC, uint32_t* modes, void* ws, int32_t* st, hipStream_t s) {
   Carver c(ws);
-  const int64_t NI = NC * F, KI = (int64_t)k * F;
+  const int64_t NI = NC * mode_slice(NC, F), KI = (int64_t)k * F;
   const int64_t NR = NI > KI ? NI : KI;
   SigWs W{};
   W.val = c.take<uint32_t>(NR + 1);

@@ -1,0 +1,37 @@
+"""GPU parity of the signature assignment's modes with numpy, bit for bit, at
+member counts past what one 32-bit sort can hold."""
+
+import numpy as np
+import pytest
+
+from .gpu_util import announce, cuda, gpu_api, host_u32
+
+pytestmark = pytest.mark.gpu
+
+
+def _modes(sig, so, sm, values):
+    """Most frequent value per seed and position (the smallest on ties) of
+    members that repeat, by counts per object; values lie in 0 .. values - 1."""
+    out = []
+    for j in range(len(so) - 1):
+        times = np.bincount(sm[so[j]:so[j + 1]], minlength=len(sig)).astype(np.float64)
+        out.append(np.argmax([times @ (sig == v) for v in range(values)], axis=0))
+    return np.array(out, np.uint32)
+
+
+def test_more_than_2_to_32_items():
+    # 64 seeds of 65,700 members and 1,024 positions: 4.3 10^9 items
+    api = gpu_api()
+    g = np.random.default_rng(0)
+    n, F, k, per, values = 500, 1024, 64, 65_700, 5
+    sig = g.integers(0, values, size=(n, F)).astype(np.uint32)
+    so = (np.arange(k + 1) * per).astype(np.uint32)
+    sm = g.integers(0, n, size=k * per).astype(np.uint32)
+    assert len(sm) * F > 2**32
+    announce(f"modes n={n} F={F} k={k} members={len(sm)}")
+    out = api.assign_sig(cuda(sig), cuda(so), cuda(sm), k)
+    api.release_workspace()
+    modes = _modes(sig, so, sm, values)
+    assert np.array_equal(host_u32(out["modes"]), modes)
+    match = (sig[:, None, :] == modes[None]).sum(axis=2)
+    assert np.array_equal(out["assign"].cpu().numpy(), np.argmax(match, axis=1))
