@@ -36,6 +36,15 @@ constexpr int64_t SIG_DENSE_MAX = 1 << 20;
 // ... by bit planes up to this k (masks of k * F rows of k bits)
 constexpr int SIG_BITS_K = 4096;
 
+// Members of seed j, or 0 and a status: none, or some past the job's member
+// count NC, which the member ids and the sort's buffers are sized by.
+GEEK_D uint32_t mode_members(const uint32_t* __restrict__ so, int64_t j, int64_t NC, int32_t* st) {
+  const uint32_t s0 = so[j], s1 = so[j + 1];
+  if (s1 > s0 && (int64_t)s1 <= NC) return s1 - s0;
+  set_status(st, s1 > s0 ? GEEK_ERR_ARG : GEEK_ERR_EMPTY_SET);
+  return 0u;
+}
+
 // Seeds of at most MODE_SMALL members: thread f of a workgroup copies its
 // position's values of the seed's members (a row's positions are contiguous)
 // into a column of LDS and compares them with each other.  64,000 members in
@@ -43,15 +52,14 @@ constexpr int SIG_BITS_K = 4096;
 constexpr int MODE_SMALL = 48, MODE_THREADS = 256;
 __global__ __launch_bounds__(MODE_THREADS) void k_mode_small(const uint32_t* __restrict__ V, int64_t ldv, int F,
                                                              int64_t n, const uint32_t* __restrict__ so,
-                                                             const uint32_t* __restrict__ sm, uint32_t* __restrict__ modes,
-                                                             int32_t* st) {
+                                                             const uint32_t* __restrict__ sm, int64_t NC,
+                                                             uint32_t* __restrict__ modes, int32_t* st) {
   __shared__ uint32_t v[MODE_SMALL][MODE_THREADS];
   const int64_t j = blockIdx.x;
   const int f = blockIdx.y * MODE_THREADS + threadIdx.x;
-  const uint32_t s0 = so[j], sj = so[j + 1] - s0;
+  const uint32_t s0 = so[j], sj = mode_members(so, j, NC, st);
   if (sj > (uint32_t)MODE_SMALL || f >= F) return;
   if (sj == 0u) {
-    set_status(st, GEEK_ERR_EMPTY_SET);
     modes[j * F + f] = 0u;
     return;
   }
@@ -86,14 +94,14 @@ __global__ __launch_bounds__(MODE_THREADS) void k_mode_small(const uint32_t* __r
 
 // Members of the seeds the sort takes (0 for the others), and the items of
 // positions f0 .. f0 + F - 1: (position's segment, value) at boff[j] F + f s_j + q.
-__global__ void k_mode_sizes(const uint32_t* __restrict__ so, int k, uint32_t* __restrict__ size) {
+__global__ void k_mode_sizes(const uint32_t* __restrict__ so, int k, int64_t NC, uint32_t* __restrict__ size) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= k) return;
-  const uint32_t sj = so[j + 1] - so[j];
+  const uint32_t sj = mode_members(so, j, NC, nullptr);
   size[j] = sj > (uint32_t)MODE_SMALL ? sj : 0u;
 }
-__global__ void k_mode_total(const uint32_t* __restrict__ members, int F, uint32_t* __restrict__ items) {
-  if (threadIdx.x == 0) *items = *members * (uint32_t)F;
+__global__ void k_mode_total(const uint32_t* __restrict__ members, int F, int64_t NC, uint32_t* __restrict__ items) {
+  if (threadIdx.x == 0) *items = (int64_t)*members <= NC ? *members * (uint32_t)F : 0u;
 }
 __global__ void k_mode_items(const uint32_t* __restrict__ V, int64_t ldv, int f0, int F, int64_t n,
                              const uint32_t* __restrict__ so, const uint32_t* __restrict__ sm, int k,
@@ -121,13 +129,13 @@ __global__ void k_mode_items(const uint32_t* __restrict__ V, int64_t ldv, int f0
 }
 
 __global__ void k_mode_pick(const uint32_t* __restrict__ val, const uint32_t* __restrict__ so,
-                            const uint32_t* __restrict__ boff, int k, int f0, int F, int ldm,
+                            const uint32_t* __restrict__ boff, int k, int f0, int F, int ldm, int64_t NC,
                             uint32_t* __restrict__ modes) {
   const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (g >= (int64_t)k * F) return;
   const int j = (int)(g / F), f = (int)(g % F);
-  const uint32_t sj = so[j + 1] - so[j];
-  if (sj <= (uint32_t)MODE_SMALL) return;
+  const uint32_t sj = mode_members(so, j, NC, nullptr);
+  if (sj <= (uint32_t)MODE_SMALL || (int64_t)boff[j] + sj > NC) return;
   const uint32_t* p = val + (int64_t)boff[j] * F + (int64_t)f * sj;
   uint32_t best = p[0], bcnt = 0, cur = p[0], ccnt = 0;
   for (uint32_t q = 0; q < sj; ++q) {
@@ -819,14 +827,14 @@ int32_t modes_run(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32
   const int64_t NI = NC * F;
   if (NI <= 0) return GEEK_OK;
   hipLaunchKernelGGL(k_mode_small, dim3(k, ceil_div(F, MODE_THREADS)), dim3(MODE_THREADS), 0, s, V, ldv, F, n, so, sm,
-                     modes, st);
+                     NC, modes, st);
   if (NC <= MODE_SMALL) return GEEK_OK;  // no seed can be larger
-  hipLaunchKernelGGL(k_mode_sizes, dim3(ceil_div(k, 256)), dim3(256), 0, s, so, k, W.boff);
+  hipLaunchKernelGGL(k_mode_sizes, dim3(ceil_div(k, 256)), dim3(256), 0, s, so, k, NC, W.boff);
   exscan_u32(W.boff, W.boff, k, W.rtmp, W.bcount, s);
   const int slice = mode_slice(NC, F);
   for (int f0 = 0; f0 < F; f0 += slice) {
     const int Fs = std::min(slice, F - f0);
-    hipLaunchKernelGGL(k_mode_total, dim3(1), dim3(64), 0, s, W.bcount, Fs, W.bcount + 1);
+    hipLaunchKernelGGL(k_mode_total, dim3(1), dim3(64), 0, s, W.bcount, Fs, NC, W.bcount + 1);
     hipLaunchKernelGGL(k_mode_items, dim3((int)std::min<int64_t>(4096, ceil_div(NC * Fs, 256))), dim3(256), 0, s, V,
                        ldv, f0, Fs, n, so, sm, k, W.boff, W.bcount + 1, W.val, W.seg, st);
     int words[8], shifts[8], np = 0;
@@ -842,7 +850,7 @@ int32_t modes_run(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32
     RsView A{{W.val, W.seg, nullptr, nullptr}, nullptr}, B{{W.val2, W.seg2, nullptr, nullptr}, nullptr};
     const int alt = radix_sort_dn(A, B, 2, NC * Fs, W.bcount + 1, words, shifts, np, W.rtmp, s);
     hipLaunchKernelGGL(k_mode_pick, dim3(ceil_div((int64_t)k * Fs, 256)), dim3(256), 0, s, alt ? W.val2 : W.val, so,
-                       W.boff, k, f0, Fs, F, modes);
+                       W.boff, k, f0, Fs, F, NC, modes);
   }
   return GEEK_OK;
 }

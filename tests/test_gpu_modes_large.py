@@ -35,3 +35,22 @@ def test_more_than_2_to_32_items():
     assert np.array_equal(host_u32(out["modes"]), modes)
     match = (sig[:, None, :] == modes[None]).sum(axis=2)
     assert np.array_equal(out["assign"].cpu().numpy(), np.argmax(match, axis=1))
+
+
+@pytest.mark.parametrize("per,given", [(4, 7), (60, 100), (60, 61)])
+def test_seeds_past_the_member_count_are_refused(per, given):
+    # seed_offsets that claim more members than the job has ids for
+    api = gpu_api()
+    g = np.random.default_rng(1)
+    n, F, k = 200, 12, 3
+    sig, cat = g.integers(0, 9, size=(n, F)).astype(np.uint32), g.integers(0, 9, size=(n, 5)).astype(np.uint32)
+    X = g.normal(size=(n, 3)).astype(np.float32)
+    so = (np.arange(k + 1) * per).astype(np.uint32)
+    sm = g.integers(0, n, size=k * per).astype(np.uint32)
+    announce(f"modes past the member count per={per} given={given}")
+    whole, ids = cuda(sm), cuda(sm)[:given]
+    for call in (lambda m: api.assign_sig(cuda(sig), cuda(so), m, k),
+                 lambda m: api.assign_hetero(cuda(X), cuda(cat), cuda(so), m, k, 1.0, 1)):
+        with pytest.raises(api.GeekError, match="invalid argument"):
+            call(ids)
+        call(whole)
