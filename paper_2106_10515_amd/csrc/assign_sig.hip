@@ -52,44 +52,45 @@ GEEK_D uint32_t mode_members(const uint32_t* __restrict__ so, int64_t j, int64_t
 constexpr int MODE_SMALL = 48, MODE_THREADS = 256;
 __global__ __launch_bounds__(MODE_THREADS) void k_mode_small(const uint32_t* __restrict__ V, int64_t ldv, int F,
                                                              int64_t n, const uint32_t* __restrict__ so,
-                                                             const uint32_t* __restrict__ sm, int64_t NC,
+                                                             const uint32_t* __restrict__ sm, int k, int64_t NC,
                                                              uint32_t* __restrict__ modes, int32_t* st) {
-  __shared__ uint32_t v[MODE_SMALL][MODE_THREADS];
-  const int64_t j = blockIdx.x;
+  __shared__ uint32_t v[MODE_SMALL][MODE_THREADS];  // a thread reads its own column only
   const int f = blockIdx.y * MODE_THREADS + threadIdx.x;
-  const uint32_t s0 = so[j], sj = mode_members(so, j, NC, st);
-  if (sj > (uint32_t)MODE_SMALL || f >= F) return;
-  if (sj == 0u) {
-    modes[j * F + f] = 0u;
-    return;
-  }
-  for (uint32_t q0 = 0; q0 < sj; q0 += 8) {  // eight members' loads in flight
-    uint32_t x[8];
+  for (int64_t j = blockIdx.x; j < k; j += gridDim.x) {
+    const uint32_t s0 = so[j], sj = mode_members(so, j, NC, st);
+    if (sj > (uint32_t)MODE_SMALL || f >= F) continue;
+    if (sj == 0u) {
+      modes[j * F + f] = 0u;
+      continue;
+    }
+    for (uint32_t q0 = 0; q0 < sj; q0 += 8) {  // eight members' loads in flight
+      uint32_t x[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const uint32_t id = sm[s0 + (q0 + u < sj ? q0 + u : sj - 1u)];
-      if ((int64_t)id >= n) {
-        set_status(st, GEEK_ERR_ARG);
-        x[u] = 0u;
-      } else {
-        x[u] = V[(int64_t)id * ldv + f];
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t id = sm[s0 + (q0 + u < sj ? q0 + u : sj - 1u)];
+        if ((int64_t)id >= n) {
+          set_status(st, GEEK_ERR_ARG);
+          x[u] = 0u;
+        } else {
+          x[u] = V[(int64_t)id * ldv + f];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (q0 + u < sj) v[q0 + u][threadIdx.x] = x[u];
+    }
+    uint32_t best = 0u, most = 0u;
+    for (uint32_t q = 0; q < sj; ++q) {
+      const uint32_t x = v[q][threadIdx.x];
+      uint32_t c = 0u;
+      for (uint32_t r = q; r < sj; ++r) c += v[r][threadIdx.x] == x ? 1u : 0u;  // full count at the first occurrence
+      if (c > most || (c == most && x < best)) {
+        most = c;
+        best = x;
       }
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (q0 + u < sj) v[q0 + u][threadIdx.x] = x[u];
+    modes[j * F + f] = best;
   }
-  uint32_t best = 0u, most = 0u;
-  for (uint32_t q = 0; q < sj; ++q) {
-    const uint32_t x = v[q][threadIdx.x];
-    uint32_t c = 0u;
-    for (uint32_t r = q; r < sj; ++r) c += v[r][threadIdx.x] == x ? 1u : 0u;  // full count at the first occurrence
-    if (c > most || (c == most && x < best)) {
-      most = c;
-      best = x;
-    }
-  }
-  modes[j * F + f] = best;
 }
 
 // Members of the seeds the sort takes (0 for the others), and the items of
@@ -826,8 +827,9 @@ int32_t modes_run(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32
                   int64_t NC, uint32_t* modes, SigWs& W, int32_t* st, hipStream_t s) {
   const int64_t NI = NC * F;
   if (NI <= 0) return GEEK_OK;
-  hipLaunchKernelGGL(k_mode_small, dim3(k, ceil_div(F, MODE_THREADS)), dim3(MODE_THREADS), 0, s, V, ldv, F, n, so, sm,
-                     NC, modes, st);
+  // (a launch holds less than 2^32 threads per dimension)
+  hipLaunchKernelGGL(k_mode_small, dim3(std::min(k, 1 << 22), ceil_div(F, MODE_THREADS)), dim3(MODE_THREADS), 0, s, V,
+                     ldv, F, n, so, sm, k, NC, modes, st);
   if (NC <= MODE_SMALL) return GEEK_OK;  // no seed can be larger
   hipLaunchKernelGGL(k_mode_sizes, dim3(ceil_div(k, 256)), dim3(256), 0, s, so, k, NC, W.boff);
   exscan_u32(W.boff, W.boff, k, W.rtmp, W.bcount, s);

@@ -54,3 +54,18 @@ def test_seeds_past_the_member_count_are_refused(per, given):
         with pytest.raises(api.GeekError, match="invalid argument"):
             call(ids)
         call(whole)
+
+
+def test_more_seeds_than_one_launch_of_workgroups():
+    # 2^24 seeds: a workgroup of 256 threads each would be 2^32 threads
+    api = gpu_api()
+    g = np.random.default_rng(2)
+    n, F, k = 40, 2, 2**24 + 3
+    sig = g.integers(0, 6, size=(n, F)).astype(np.uint32)
+    sm = g.integers(0, n, size=k).astype(np.uint32)
+    announce(f"modes n={n} F={F} k={k}")
+    out = api.assign_sig(cuda(sig), cuda(np.arange(k + 1, dtype=np.uint32)), cuda(sm), k)
+    api.release_workspace()
+    assert np.array_equal(host_u32(out["modes"]), sig[sm])
+    first = [int(np.flatnonzero((sig[sm[:4000]] == row).all(axis=1))[0]) for row in sig]
+    assert out["assign"].cpu().numpy().tolist() == first
