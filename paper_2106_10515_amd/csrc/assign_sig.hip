@@ -726,7 +726,7 @@ __global__ void k_copy_ctr(const unsigned long long* a, unsigned long long* b) {
 // match lists of a wavefront's rows fit in LDS).
 static int sig_lanes(int F, int k) {
   int gl = F > 512 ? 16 : 8;
-  while (gl * 32 * SB_VW < k) gl *= 2;
+  while ((int64_t)gl * 32 * SB_VW < k) gl *= 2;
   return gl;
 }
 
