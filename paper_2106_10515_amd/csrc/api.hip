@@ -185,6 +185,7 @@ static int32_t check_assign(const geek_assign_job& J) {
   } else if (J.metric == GEEK_METRIC_SIG) {
     if (!J.sig || J.F < 1 || !J.modes || J.n_members < J.k) return GEEK_ERR_ARG;
     if (J.F > 1024) return GEEK_ERR_UNSUPPORTED;
+    if ((int64_t)J.k * J.F >= (1ll << 32)) return GEEK_ERR_UNSUPPORTED;  // index entries have 32-bit positions
   } else {
     return GEEK_ERR_ARG;
   }

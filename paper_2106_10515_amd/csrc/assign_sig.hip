@@ -757,9 +757,9 @@ struct SigWs {
   int row_words, bits_cap;
 };
 
-static uint32_t pow2_at_least(uint64_t v) {
-  uint32_t p = 1;
-  while (p < v && p < (1u << 31)) p <<= 1;
+static uint64_t pow2_at_least(uint64_t v) {
+  uint64_t p = 1;
+  while (p < v && p < (1ull << 32)) p <<= 1;
   return p;
 }
 
@@ -794,8 +794,10 @@ static size_t carve_sig(const geek_assign_job& J, void* ws, SigWs& W) {
   W.wj2 = c.take<uint32_t>(KI + 1);
   W.wv2 = c.take<uint32_t>(KI + 1);
   W.wf2 = c.take<uint32_t>(KI + 1);
-  const uint32_t HS = pow2_at_least(2 * (uint64_t)KI + 2);
-  W.hmask = HS - 1;
+  // at most half full, or (KI < 2^32 from 2^31 on) with slots left empty: a
+  // probe ends at one
+  const uint64_t HS = pow2_at_least(2 * (uint64_t)KI + 2);
+  W.hmask = (uint32_t)(HS - 1);
   const bool bits = sig_use_bits(J), index = KI > SIG_DENSE_MAX;
   W.hkey = c.take<unsigned long long>(index ? HS : 0);
   W.hval = c.take<unsigned long long>(index ? HS : 0);
