@@ -252,7 +252,7 @@ typedef struct geek_silk_job {
  *   in float64 as: for t = 0..d-1, delta = x_it - c_jt, acc += delta*delta
  *   (each operation rounded, no fused multiply-add); lowest j on ties.
  *   The matrix cores compute an approximate D~ = |x|^2 - 2 x.c + |c|^2 in
- *   `precision` (FP32: from two float16 pieces per value; FP8 runs the bf16
+ *   `precision` (FP32: from three bf16 pieces per value, exact; FP8 runs the bf16
  *   pass, which is as fast and settles more rows); every j whose D~ lies within a rigorous per-row error bound
  *   of the row minimum is a candidate.  Rows with one candidate (BF16, FP8) or
  *   at most 8 (FP32) have their candidates re-evaluated with the float64

@@ -4,7 +4,7 @@
 //   k_centroids   float64 centroids, one thread per (seed, dim), members summed
 //                 in ascending order one rounding at a time (exact parity),
 //                 their values loaded 32 at a time.
-//   k_cprep       centroid copies for the matrix cores (bf16; two float16 pieces),
+//   k_cprep       centroid copies for the matrix cores (three bf16 pieces),
 //                 |c|^2 and max |c| for the error bound.
 //   k_scan<M,DP>  matrix-core tile |x|^2 - 2 x.c + |c|^2 over all centroids for
 //                 a block of rows.  Float32: per row it keeps every centroid
@@ -47,14 +47,6 @@ constexpr int SSE_BLOCK = 4096;
 // already in flight).
 constexpr int CB = 32;
 
-// Largest magnitude seen by a wavefront into *out (skipped while *out is not
-// below it).
-GEEK_D void wave_absmax(float v, float* out) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  if ((threadIdx.x & 63) == 0 && v > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    atomic_max_nonneg(out, v);
-}
-
 // Centroid of dimension t over the members [s, e) of mem (ids below n), one
 // ordered chain.
 GEEK_D double centroid_of(const float* __restrict__ X, int64_t ldx, int64_t n, int t,
@@ -62,24 +54,21 @@ GEEK_D double centroid_of(const float* __restrict__ X, int64_t ldx, int64_t n, i
 
 __global__ __launch_bounds__(256) void k_centroids(const float* __restrict__ X, int64_t ldx, int64_t n, int d,
                             const uint32_t* __restrict__ offs, const uint32_t* __restrict__ mem,
-                            int k, const uint32_t* __restrict__ kdev, double* __restrict__ C,
-                            float* __restrict__ cabs, int32_t* st) {
+                            int k, const uint32_t* __restrict__ kdev, double* __restrict__ C, int32_t* st) {
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (gid >= (int64_t)k * d) return;
+  const int j = (int)(gid / d), t = (int)(gid % d);
   double c = 0.0;
-  if (gid < (int64_t)k * d) {
-    const int j = (int)(gid / d), t = (int)(gid % d);
-    // seeds counted on the device: those past the count take no part
-    const int kv = kdev ? (int)min(*kdev, (uint32_t)k) : k;
-    if (j < kv) {
-      const uint32_t s = offs[j], e = offs[j + 1];
-      if (e <= s) set_status(st, GEEK_ERR_EMPTY_SET);
-      else c = centroid_of(X, ldx, n, t, mem, s, e, st);
-    } else if (kv == 0 && gid == 0) {
-      set_status(st, GEEK_ERR_NO_SEEDS);
-    }
-    C[gid] = c;
+  // seeds counted on the device: those past the count take no part
+  const int kv = kdev ? (int)min(*kdev, (uint32_t)k) : k;
+  if (j < kv) {
+    const uint32_t s = offs[j], e = offs[j + 1];
+    if (e <= s) set_status(st, GEEK_ERR_EMPTY_SET);
+    else c = centroid_of(X, ldx, n, t, mem, s, e, st);
+  } else if (kv == 0 && gid == 0) {
+    set_status(st, GEEK_ERR_NO_SEEDS);
   }
-  wave_absmax((float)fabs(c), cabs);
+  C[gid] = c;
 }
 
 GEEK_D double centroid_of(const float* __restrict__ X, int64_t ldx, int64_t n, int t,
@@ -169,8 +158,7 @@ __global__ __launch_bounds__(256) void k_gather_t(const float* __restrict__ X, i
 // member; widening four members ahead of their additions changed nothing).
 constexpr int CT_B = 6, CT_R = 7;  // 16-byte loads per batch, batches in the ring
 __global__ __launch_bounds__(256) void k_centroids_t(const float* __restrict__ Xt, int64_t nm, int d,
-                              const uint32_t* __restrict__ offs, int k, double* __restrict__ C,
-                              float* __restrict__ cabs, int32_t* st) {
+                              const uint32_t* __restrict__ offs, int k, double* __restrict__ C, int32_t* st) {
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   double c = 0.0;
   if (gid < (int64_t)k * d) {
@@ -221,7 +209,6 @@ __global__ __launch_bounds__(256) void k_centroids_t(const float* __restrict__ X
     }
     C[gid] = c;
   }
-  wave_absmax((float)fabs(c), cabs);
 }
 
 // Whether the centroids go through the dimension-major copy: seeds of 64
@@ -232,15 +219,15 @@ static bool centroids_transposed(const geek_assign_job& J) {
 static int64_t members_pad(const geek_assign_job& J) { return (J.n_members + 3) / 4 * 4; }
 
 // Matrix-core input copies of the centroids, zero-padded to [k_pad][DP]: the
-// float32 pieces, and with `low` the bf16 copy of a bf16 first pass.  A thread
+// three float32 pieces in planes, the first of which is the bf16 copy of a bf16
+// first pass.  A thread
 // takes eight attributes of a centroid, the DP / 8 threads of a centroid are
 // neighbours in a wavefront (a thread per centroid, walking its row, took 7 us
 // at k = 10 and one launch per copy).  Padded rows get |c|^2 = +inf so they
 // never enter a window.  |c|^2 may be summed in any order (two_eps).
 __global__ __launch_bounds__(256) void k_cprep(const double* __restrict__ C, int k, int d, int k_pad, int DP,
-                                               uint32_t* __restrict__ cl32, __bf16* __restrict__ low,
-                                               float* __restrict__ nc, float* __restrict__ cmax,
-                                               const float* __restrict__ cabs_p, const uint32_t* __restrict__ kdev) {
+                                               __bf16* __restrict__ cl, float* __restrict__ nc,
+                                               float* __restrict__ cmax, const uint32_t* __restrict__ kdev) {
   const int G = DP / 8;  // 4, 8, 16 or 32: all threads of a centroid are in one wavefront
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int j = (int)(gid / G), t = (int)(gid % G) * 8;
@@ -256,8 +243,10 @@ __global__ __launch_bounds__(256) void k_cprep(const double* __restrict__ C, int
     v[e] = (float)c;
   }
   for (int o = 1; o < G; o <<= 1) sq += __shfl_xor(sq, o);
-  ModeF32::store(cl32 + (int64_t)j * DP + t, v, ModeF32::scale_of(*cabs_p));
-  if (low) ModeBF16::store(low + (int64_t)j * DP + t, v, 1.0f);
+  const ModeF32::frag f = ModeF32::from_f32(v, 1.0f);
+#pragma unroll
+  for (int z = 0; z < ModeF32::PIECES; ++z)
+    *reinterpret_cast<bf16x8*>(cl + ((int64_t)z * k_pad + j) * DP + t) = f.p[z];
   if (t == 0) {
     nc[j] = real ? (float)sq : INFINITY;
     const float norm = (float)(sqrt(sq) * (1.0 + 0x1p-20));
@@ -266,26 +255,25 @@ __global__ __launch_bounds__(256) void k_cprep(const double* __restrict__ C, int
   }
 }
 
-// Three workgroups per CU for the float32 pieces up to 128 attributes (at most
-// 168 registers a wavefront, a few spilled while x is split: 1.88 -> 1.69 ms on
-// 500,009 x 100 rows, 3,001 seeds).  Two workgroups per CU (at most 256 registers a wavefront) for the BF16
+// Two workgroups per CU (at most 256 registers a wavefront) for the BF16
 // first pass of point rows up to 128 attributes, whose stage pipeline keeps
-// two blocks' accumulators live; the compiler would otherwise go just past
-// 256 and halve the occupancy.
-template <class M, int DP, bool HET, int NCB>
+// two blocks' accumulators live (the compiler would otherwise go just past
+// 256 and halve the occupancy), and for the first pass of the float32 pieces,
+// whose LDS allows as many.
+template <class M, int DP, bool HET, int NCB, bool WIDE>
 constexpr int scan_min_blocks() {
-  if (M::SPLIT && !HET && NCB == 1 && DP <= 128) return 3;
+  if (M::PIECES > 1) return !HET && !WIDE && NCB == 1 && DP <= 128 ? 2 : 1;
   return (std::is_same<M, ModeBF16>::value && !HET && NCB == 2 && DP <= 128) ? 2 : 1;
 }
 
 template <class M, int DP, bool HET, int NCB, int NBUF, bool T2, bool WIDE, bool MARK>
-__global__ __launch_bounds__(SCAN_THREADS, (scan_min_blocks<M, DP, HET, NCB>())) void k_scan(
+__global__ __launch_bounds__(SCAN_THREADS, (scan_min_blocks<M, DP, HET, NCB, WIDE>())) void k_scan(
     const float* __restrict__ X, int64_t ldx, int d, int64_t n_rows,
     const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
     const typename M::ce* __restrict__ cl, const float* __restrict__ nc, int k_pad,
-    const float* __restrict__ cmax_p, const float* __restrict__ cabs_p, Het het, int k,
+    const float* __restrict__ cmax_p, const float* __restrict__ scale_p, Het het, int k,
     int32_t* __restrict__ rec, int32_t* st, ScanBlocks sb) {
-  scan_tiles<M, DP, HET, NCB, NBUF, T2, WIDE, MARK>(X, ldx, d, n_rows, rows, rows_count, cl, nc, k_pad, cmax_p, cabs_p, het,
+  scan_tiles<M, DP, HET, NCB, NBUF, T2, WIDE, MARK>(X, ldx, d, n_rows, rows, rows_count, cl, nc, k_pad, cmax_p, scale_p, het,
                                         k, rec, st, blockIdx.x, INT64_MAX, gridDim.x, sb);
 }
 
@@ -877,9 +865,8 @@ __global__ __launch_bounds__(256) void k_seed_code(const double* __restrict__ C,
 // Matrix-core copies in seed order `sid` (padding rows stay last), and the
 // place of every seed.  One thread per eight attributes.
 __global__ __launch_bounds__(256) void k_seed_permute(const uint32_t* __restrict__ sid, int k, int k_pad, int DP,
-                                                      const uint32_t* __restrict__ cl32, const __bf16* __restrict__ low,
-                                                      const float* __restrict__ nc, uint32_t* __restrict__ cl32p,
-                                                      __bf16* __restrict__ lowp, float* __restrict__ ncp,
+                                                      const __bf16* __restrict__ cl, const float* __restrict__ nc,
+                                                      __bf16* __restrict__ clp, float* __restrict__ ncp,
                                                       uint32_t* __restrict__ spos) {
   const int G = DP / 8;
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -887,11 +874,10 @@ __global__ __launch_bounds__(256) void k_seed_permute(const uint32_t* __restrict
   const int t = (int)(gid % G) * 8;
   if (r >= k_pad) return;
   const int64_t j = r < k ? (int64_t)sid[r] : r;
-  const uint4* a = reinterpret_cast<const uint4*>(cl32 + j * DP + t);
-  uint4* b = reinterpret_cast<uint4*>(cl32p + r * DP + t);
-  b[0] = a[0];
-  b[1] = a[1];
-  *reinterpret_cast<uint4*>(lowp + r * DP + t) = *reinterpret_cast<const uint4*>(low + j * DP + t);
+#pragma unroll
+  for (int64_t z = 0; z < ModeF32::PIECES; ++z)
+    *reinterpret_cast<uint4*>(clp + (z * k_pad + r) * DP + t) =
+        *reinterpret_cast<const uint4*>(cl + (z * k_pad + j) * DP + t);
   if (t == 0) {
     ncp[r] = nc[j];
     if (r < k) spos[j] = (uint32_t)r;
@@ -1244,10 +1230,9 @@ static bool low_precision(const geek_assign_job& J) {
 }
 
 struct AssignWs {
-  uint32_t* cl32;  // float16 pieces (ModeF32)
-  void* cllow;  // bf16 copy for the first pass
+  __bf16* cl;  // the centroids' pieces (ModeF32), the first also the bf16 first pass's copy
   float* nc;
-  float* cmax;   // [0] max |c|, [1] max |c_t|
+  float* cmax;   // [0] max |c|
   int32_t* rec;
   uint32_t* esc;
   uint32_t* fb;
@@ -1266,8 +1251,8 @@ struct AssignWs {
   double* mean;
   uint32_t *skey, *sid, *skey2, *sid2, *spos;  // seeds by code
   uint32_t *rkey, *rid, *rkey2, *rid2;         // unsettled rows by their best seed's place
-  uint32_t *cl32p, *flags, *rtmp;
-  __bf16* clowp;
+  __bf16* clp;  // the pieces in seed order
+  uint32_t *flags, *rtmp;
   int fwords;
 };
 
@@ -1281,9 +1266,7 @@ static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
   Carver c(ws);
   const int DP = pick_dp(J.d);
   const int64_t k_pad = ((int64_t)J.k + SCAN_BC - 1) / SCAN_BC * SCAN_BC;
-  out->cl32 = c.take<uint32_t>(k_pad * DP);
-  const size_t low = low_precision(J) ? 2 : 0;
-  out->cllow = c.take<char>(low ? k_pad * DP * low : 16);
+  out->cl = c.take<__bf16>(ModeF32::PIECES * k_pad * DP);
   out->nc = c.take<float>(k_pad);
   out->cmax = c.take<float>(4);
   out->rec = c.take<int32_t>(J.n * RECW);
@@ -1313,8 +1296,7 @@ static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
     out->rid = c.take<uint32_t>(n);
     out->rkey2 = c.take<uint32_t>(n);
     out->rid2 = c.take<uint32_t>(n);
-    out->cl32p = c.take<uint32_t>(k_pad * DP);
-    out->clowp = c.take<__bf16>(k_pad * DP);
+    out->clp = c.take<__bf16>(ModeF32::PIECES * k_pad * DP);
     out->flags = c.take<uint32_t>((size_t)(ceil_div(n, 256) * 2) * out->fwords);
     out->rtmp = c.take<uint32_t>(radix_tmp_words(std::max(n, k)));
   }
@@ -1328,11 +1310,10 @@ size_t assign_euclid_ws(const geek_assign_job& J) {
 }
 
 // Column blocks per wave and LDS buffering per mode: the low-precision modes
-// reuse every LDS fragment for two column blocks; float32's pieces of two
+// reuse every LDS fragment for two column blocks; float32's three pieces of two
 // blocks would leave one wavefront per SIMD (500,009 x 100 rows, 3,001 seeds:
-// first pass 2.6 ms so, 1.6 ms with one block, 1.7 ms with one block and one
-// buffer; the rescan of 10^6 rows against 90,343 seeds 109 ms with two buffers,
-// 170 ms with one).
+// whole call 2.20 ms with one block and two stages; 4.12 ms with float32 matrix
+// instructions).
 // The BF16 first pass keeps the best two values per row (T2); the float32
 // pass, which also rescans rows with several candidates, keeps the full
 // candidate window.
@@ -1357,12 +1338,14 @@ static void launch_scan(int DP, int grid, hipStream_t s, const geek_assign_job& 
                         const uint32_t* rows, const uint32_t* rows_count, const void* cl, const AssignWs& W,
                         int k_pad, const Het& het, int32_t* st, const ScanBlocks& sb, const float* nc) {
   using CE = typename M::ce;
-  constexpr int NCB = ScanShape<M, HET>::NCB, NBUF = ScanShape<M, HET>::NBUF;
+  constexpr int NCB = ScanShape<M, HET>::NCB;
   constexpr bool T2 = ScanShape<M, HET>::T2;
+  // (two stages of 256 attributes in three pieces and wide windows exceed the LDS)
+  constexpr int NBUF = ScanShape<M, HET>::NBUF, NBUF256 = M::PIECES > 1 && WIDE ? 1 : NBUF;
   switch (DP) {
 #define GEEK_SCAN_CASE(DPV)                                                                            \
   case DPV:                                                                                            \
-    hipLaunchKernelGGL((k_scan<M, DPV, HET, NCB, NBUF, T2, WIDE, MARK>), dim3(grid), dim3(SCAN_THREADS), 0, s, J.X,\
+    hipLaunchKernelGGL((k_scan<M, DPV, HET, NCB, DPV == 256 ? NBUF256 : NBUF, T2, WIDE, MARK>), dim3(grid), dim3(SCAN_THREADS), 0, s, J.X,\
                        J.ldx, J.d, n_rows, rows, rows_count, static_cast<const CE*>(cl), nc, k_pad,  \
                        W.cmax, W.cmax + 1, het, J.k, W.rec, st, sb);                                     \
     break;
@@ -1417,11 +1400,10 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
     hipLaunchKernelGGL(k_gather_t, dim3(ceil_div(nmp, GT_TILE), ceil_div(J.d, GT_TILE)), dim3(256), 0, s, J.X,
                        J.ldx, J.n, J.d, J.seed_offsets, J.k, J.seed_members, J.n_members, nmp, W.xt, st);
     hipLaunchKernelGGL(k_centroids_t, dim3(ceil_div((int64_t)J.k * J.d, 256)), dim3(256), 0, s, W.xt,
-                       J.n_members, J.d, J.seed_offsets, J.k, J.centroids, W.cmax + 1, st);
+                       J.n_members, J.d, J.seed_offsets, J.k, J.centroids, st);
   } else {
     hipLaunchKernelGGL(k_centroids, dim3(ceil_div((int64_t)J.k * J.d, 256)), dim3(256), 0, s, J.X,
-                       J.ldx, J.n, J.d, J.seed_offsets, J.seed_members, J.k, J.k_dev, J.centroids,
-                       W.cmax + 1, st);
+                       J.ldx, J.n, J.d, J.seed_offsets, J.seed_members, J.k, J.k_dev, J.centroids, st);
   }
   if (C.het_on) {
     if (int32_t rc = modes_compute(reinterpret_cast<const uint32_t*>(J.cat), J.n_cat, J.n_cat, J.n,
@@ -1431,8 +1413,7 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
                        J.n_cat, k_pad, W.mode16);
   }
   hipLaunchKernelGGL(k_cprep, dim3(ceil_div((int64_t)k_pad * (DP / 8), 256)), dim3(256), 0, s, J.centroids, J.k, J.d,
-                     k_pad, DP, W.cl32, low_precision(J) ? static_cast<__bf16*>(W.cllow) : nullptr, W.nc, W.cmax,
-                     W.cmax + 1, J.k_dev);
+                     k_pad, DP, W.cl, W.nc, W.cmax, J.k_dev);
   GEEK_LAUNCH_CHECK();
   return GEEK_OK;
 }
@@ -1448,13 +1429,13 @@ static void assign_first_pass(const geek_assign_job& J, AssignCtx& C, int32_t* s
     const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeBF16>(C.het_on));
     C.marked = blocked_rescan(J);
     if (C.marked)
-      scan_any<ModeBF16, false, true>(false, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cllow, C.W, C.k_pad, C.het,
+      scan_any<ModeBF16, false, true>(false, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl, C.W, C.k_pad, C.het,
                                       st, ScanBlocks{nullptr, 0, nullptr, C.W.thr});
     else
-      scan_any<ModeBF16>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cllow, C.W, C.k_pad, C.het, st);
+      scan_any<ModeBF16>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl, C.W, C.k_pad, C.het, st);
   } else {
     const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeF32>(C.het_on));
-    scan_any<ModeF32>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl32, C.W, C.k_pad, C.het, st);
+    scan_any<ModeF32>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl, C.W, C.k_pad, C.het, st);
   }
 }
 
@@ -1469,7 +1450,7 @@ static const uint32_t* blocked_marks(const geek_assign_job& J, const AssignCtx& 
   RsView A{{W.skey, nullptr, nullptr, nullptr}, W.sid}, B{{W.skey2, nullptr, nullptr, nullptr}, W.sid2};
   const uint32_t* sid = radix_sort(A, B, 1, k, zero, shifts, CODE_BITS / 8, W.rtmp, s) ? W.sid2 : W.sid;
   hipLaunchKernelGGL(k_seed_permute, dim3(ceil_div((int64_t)k_pad * (C.DP / 8), 256)), dim3(256), 0, s, sid, k, k_pad,
-                     C.DP, W.cl32, static_cast<const __bf16*>(W.cllow), W.nc, W.cl32p, W.clowp, W.ncp, W.spos);
+                     C.DP, W.cl, W.nc, W.clp, W.ncp, W.spos);
   hipLaunchKernelGGL(k_row_keys, dim3(1024), dim3(256), 0, s, W.esc, W.counts + 0, W.rec, W.spos, W.rkey, W.rid);
   int np = 1;
   while (np < 4 && (uint32_t)(k - 1) >> (8 * np)) ++np;
@@ -1482,7 +1463,7 @@ static const uint32_t* blocked_marks(const geek_assign_job& J, const AssignCtx& 
 #define GEEK_MARK_CASE(DPV)                                                                                          \
   case DPV:                                                                                                          \
     hipLaunchKernelGGL(k_mark<DPV>, dim3(tiles), dim3(SCAN_THREADS), 0, s, J.X, J.ldx, J.d, rows, W.counts + 0, W.thr, \
-                       W.clowp, W.ncp, k_pad, W.fwords, W.flags);                                                    \
+                       W.clp, W.ncp, k_pad, W.fwords, W.flags);                                                      \
     break;
     GEEK_MARK_CASE(32)
     GEEK_MARK_CASE(64)
@@ -1519,7 +1500,7 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
   ScanBlocks sb{};
   const bool blocked = C.marked;
   if (blocked) esc = blocked_marks(J, C, sb, s);
-  scan_any<ModeF32, true>(C.het_on, C.DP, esc_grid(J.n, 128), s, J, 0, esc, W.counts + 0, blocked ? W.cl32p : W.cl32, W,
+  scan_any<ModeF32, true>(C.het_on, C.DP, esc_grid(J.n, 128), s, J, 0, esc, W.counts + 0, blocked ? W.clp : W.cl, W,
                           C.k_pad, C.het, st, sb, blocked ? W.ncp : W.nc);
   hipLaunchKernelGGL(k_finalize_win, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids,
                      J.k, C.het, (int64_t)0, esc, W.counts + 0, W.rec, RECW, J.assign, C.dist, W.fb, W.counts + 1,
@@ -1616,7 +1597,6 @@ int32_t assign_euclid_batch(const geek_assign_job* jobs, int njobs, void* ws, si
   }
   // one persistent launch per padded depth, jobs in call order, with the
   // tile shape set for that (precision, depth)
-  const bool low = low_precision(J0);
   prof_begin(GEEK_PROF_ASSIGN_SCAN, s);
   int tslot = 0;
   for (const int DP : {32, 64, 128, 256}) {
@@ -1631,10 +1611,10 @@ int32_t assign_euclid_batch(const geek_assign_job* jobs, int njobs, void* ws, si
       e.X = J.X;
       e.ldx = J.ldx;
       e.n = J.n;
-      e.cl = low ? W.cllow : static_cast<const void*>(W.cl32);
+      e.cl = W.cl;
       e.nc = W.nc;
       e.cmax = W.cmax;
-      e.cabs = W.cmax + 1;
+      e.scale = W.cmax + 1;
       e.rec = W.rec;
       e.tile_begin = total;
       e.d = J.d;

@@ -22,65 +22,69 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_BC = 64;   // centroids per LDS stage
 
 // ---------------------------------------------------------------- modes
-// float32 values as two float16 pieces.  Scaled by a power of two (rows of x
-// each by their own, the centroids by one) so that the largest magnitude lies
-// in [2^14, 2^15), a value v is hi + lo, both rounded to float16: the remainder
-// v - hi is exact in float32, so |v - hi - lo| <= 2^-22 |v| plus at most 2^-14
-// where lo is subnormal.  A product is hi hi + hi lo + lo hi in float32
-// accumulators (float16 products are exact there); lo lo is dropped.  Against
-// float32 matrix instructions (64 cycles for 2 of K, and no vector work
-// beside them) three float16 ones take 96 cycles for 16.
+// float32 values as three bf16 pieces: v = hi + mid + lo, each piece the bf16
+// nearest to what the ones before it leave.  bf16 has float32's exponents, so no
+// scale is needed, and three pieces of eight bits hold all 24: the sum is exact
+// (where a piece would be subnormal, within 2^-125).  With |mid| <= 2^-8 |v| and
+// |lo| <= 2^-16 |v|, of the nine products of two values those of mid and lo, lo
+// and mid, and lo and lo are left out, at most 2^-23 (1 + 2^-8) |x c|; the six
+// others are exact in float32 accumulators.  Six bf16 instructions take 192
+// cycles for 16 of K, float32 matrix instructions 512 (64 for 2 of K, and no
+// vector work beside them); two float16 pieces in three products take 96, but
+// hold 22 of the 24 bits.  Error of a value against float64 in units of
+// 2^-24 (|x| + |c|) |c|, root mean square over 4,096 x 512 pairs of a Gaussian
+// mixture in [-50, 50]^d, float32 instructions / two float16 pieces / three bf16
+// pieces: first pass d = 8 0.51 / 0.64 / 0.42, d = 32 0.44 / 0.42 / 0.37, d = 128
+// 0.43 / 0.33 / 0.30; rescan (blocked sums) d = 16 0.44 / 0.51 / 0.38, d = 128 0.32
+// / 0.32 / 0.30.
 struct ModeF32 {
-  struct frag16 {
-    f16x8 hi, lo;
+  struct frag3 {
+    bf16x8 p[3];
   };
   static constexpr int KPER = 8;
   static constexpr int KB = 16;   // products per fresh-accumulator block (0 = one chain)
-  static constexpr bool SPLIT = true;
-  using ce = uint32_t;            // 4 bytes per element: per 8, 16 bytes of hi then 16 of lo
-  using frag = frag16;
-  static constexpr double UX = 0x1p-22;
-  static constexpr double UC = 0x1p-22 + 0x1p-23;  // and the float64 -> float32 rounding
-  static constexpr double A0 = 0x1p-14;   // absolute error per element (scaled units)
-  static constexpr double DROP = 0x1p-21; // lo lo, and the roundings among the small products
-  GEEK_D static f32x16 mfma(f16x8 a, f16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
-  // 2^e with largest magnitude * 2^e in [2^14, 2^15); e <= 120
-  GEEK_HD static float scale_of(float largest) {
-    const uint32_t e = (__builtin_bit_cast(uint32_t, largest) >> 23) & 255u;
-    const int q = 141 - (int)e;
-    return __builtin_bit_cast(float, (uint32_t)((q < 120 ? q : 120) + 127) << 23);
-  }
-  GEEK_D static frag from_f32(const float* v, float sc) {
+  static constexpr int PIECES = 3;
+  static constexpr bool SCALED = false;
+  using ce = __bf16;              // pieces lie in planes: [PIECES][k_pad][DP]
+  using frag = frag3;
+  static constexpr double UX = 0.0;       // x is already float32
+  static constexpr double UC = 0x1p-24;   // float64 -> float32 rounding
+  static constexpr double A0 = 0x1p-125;  // absolute error per element
+  static constexpr double DROP = 0x1.02p-23;
+  GEEK_D static f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+  GEEK_D static frag from_f32(const float* v, float) {
     frag f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float y = v[e] * sc;
-      f.hi[e] = (_Float16)y;
-      f.lo[e] = (_Float16)(y - (float)f.hi[e]);
+      float y = v[e];
+#pragma unroll
+      for (int z = 0; z < 3; ++z) {
+        f.p[z][e] = (__bf16)y;
+        y -= (float)f.p[z][e];  // exact
+      }
     }
     return f;
   }
-  GEEK_D static void store(ce* p, const float* v, float sc) {
-    const frag f = from_f32(v, sc);
-    *reinterpret_cast<f16x8*>(p) = f.hi;
-    *reinterpret_cast<f16x8*>(p + 4) = f.lo;
-  }
-  GEEK_D static void store_zero(ce* p) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) p[e] = 0u;
+  // the five small products, smallest first
+  GEEK_D static f32x16 small(const frag& a, const frag& b, f32x16 c) {
+    c = mfma(a.p[2], b.p[0], c);
+    c = mfma(a.p[0], b.p[2], c);
+    c = mfma(a.p[1], b.p[1], c);
+    c = mfma(a.p[1], b.p[0], c);
+    return mfma(a.p[0], b.p[1], c);
   }
 };
 
 struct ModeBF16 {
   static constexpr int KPER = 8;
   static constexpr int KB = 0;  // input rounding (2^-8) dominates the accumulation
-  static constexpr bool SPLIT = false;
+  static constexpr int PIECES = 1;
+  static constexpr bool SCALED = false;
   using ce = __bf16;
   using frag = bf16x8;
   static constexpr double UX = 0x1p-8;  // conservative for any rounding to bf16
   static constexpr double UC = 0x1p-8;
   static constexpr double A0 = 0.0, DROP = 0.0;
-  GEEK_HD static float scale_of(float) { return 1.0f; }
   GEEK_D static f32x16 mma(frag a, frag b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
@@ -90,14 +94,6 @@ struct ModeBF16 {
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] = (__bf16)v[e];
     return f;
-  }
-  GEEK_D static void store(ce* p, const float* v, float) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) p[e] = (__bf16)v[e];
-  }
-  GEEK_D static void store_zero(ce* p) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) p[e] = (__bf16)0.0f;
   }
 };
 
@@ -117,22 +113,26 @@ GEEK_D double gamma_n(double nn, double u) { return nn * u / (1.0 - nn * u); }
 // Rigorous bound on |(|x|^2 + v_j) - D64(i, j)| for every j, where v_j is the
 // float32 epilogue value fma(-2/s^2, acc, |c_j|^2) (+ gamma * mismatches)
 // and D64 the float64 reference.  X = |x|, cm = max |c|; the inputs are
-// rounded with relative error UX/UC and absolute error A0/s per element (s
-// the row's or the centroids' scale; inv_x, inv_c its inverse), so
+// rounded with relative error UX/UC and absolute error A0/s per element, so
 // |x^ - x| <= ex = UX X + A0 sqrt(DP) / s (likewise ec) and, by Cauchy-
 // Schwarz, |x^.c^ - x.c| <= ex cm + X ec + ex ec (+ DROP X cm for products
 // left out); the float32 accumulation of
 // the (exact) products adds gamma_n(2u) |x^| |c^| with n = DP + 1 roundings
 // per product for one accumulator chain, or n = KB + DP/KB + 1 when blocks of
 // KB products start from zero and their sums are added to the running value.
+// Of three pieces the large products (hi hi, at most (1 + 2^-7) |x c|) take
+// that many, one more where the small ones, at most 2^-6.9 |x c| in a chain of
+// 5 DP + 1 roundings (or of 5 KB within a block), are added last: DP + DP/16 + 3,
+// or KB + DP/KB + 4, in all.
 template <class M, int DP, bool T2, bool BLK>
-GEEK_D float two_eps(double xn, double cm, double inv_x, double inv_c, double het_max) {
+GEEK_D float two_eps(double xn, double cm, double inv_scale, double het_max) {
   const double u32 = 0x1p-24;
-  constexpr int NACC = BLK ? M::KB + DP / M::KB + 1 : DP + 1;
+  constexpr int MORE = M::PIECES == 1 ? 1 : BLK ? 4 : DP / 16 + 3;
+  constexpr int NACC = BLK ? M::KB + DP / M::KB + MORE : DP + MORE;
   const double g_acc = gamma_n(NACC, 2.0 * u32);
   const double g64 = gamma_n(DP + 2, 0x1p-53);
-  const double root = sqrt((double)DP);
-  const double ex = M::UX * xn + M::A0 * inv_x * root, ec = M::UC * cm + M::A0 * inv_c * root;
+  const double ab = M::A0 * inv_scale * sqrt((double)DP);
+  const double ex = M::UX * xn + ab, ec = M::UC * cm + ab;
   const double dot = ex * cm + xn * ec + ex * ec + M::DROP * xn * cm + g_acc * (xn + ex) * (cm + ec);
   const double vmax = cm * cm + 2.0 * (xn + ex) * (cm + ec) + het_max;
   const double s2 = (xn + cm) * (xn + cm) + het_max;
@@ -140,7 +140,7 @@ GEEK_D float two_eps(double xn, double cm, double inv_x, double inv_c, double he
   if (!(4.0 * vmax < 0x1p120)) return INFINITY;
   double eps = 2.0 * dot                       // 2 x.c
                + g_acc * cm * cm                // |c|^2 / 2 as the accumulator's start
-               + 0x1p-124 * inv_x * inv_c  // its float32 subnormal rounding
+               + 0x1p-124 * inv_scale * inv_scale  // its float32 subnormal rounding
                + (u32 + g64) * cm * cm          // |c|^2 stored as float32
                + 2.0 * u32 * vmax               // epilogue roundings
                + g64 * s2 + 0x1p-52 * het_max   // float64 reference rounding
@@ -175,12 +175,14 @@ __device__ __forceinline__ void scan_tiles(
     const float* __restrict__ X, int64_t ldx, int d, int64_t n_rows,
     const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
     const typename M::ce* __restrict__ cl, const float* __restrict__ nc, int k_pad,
-    const float* __restrict__ cmax_p, const float* __restrict__ cabs_p, Het het, int k,
+    const float* __restrict__ cmax_p, const float* __restrict__ scale_p, Het het, int k,
     int32_t* __restrict__ rec, int32_t* st, int64_t tile0, int64_t tile_end, int64_t tstep, ScanBlocks sb = {}) {
   using CE = typename M::ce;
-  // centroids per stage: half as many where an element takes four bytes and
-  // two stages are in LDS (three workgroups per CU at d = 128 then)
-  constexpr int BC = M::SPLIT && NBUF == 2 ? SCAN_BC / 2 : SCAN_BC;
+  // centroids per stage: half as many where an element takes three pieces and
+  // two stages are in LDS (two workgroups per CU at d = 128 then) or rows are
+  // widest
+  constexpr int NP = M::PIECES;
+  constexpr int BC = NP > 1 && (NBUF == 2 || DP > 128) ? SCAN_BC / 2 : SCAN_BC;
   constexpr int S = DP / 2 / M::KPER;             // MFMA steps over K
   constexpr int CH = DP * (int)sizeof(CE) / 16;   // 16-byte chunks per centroid row
   // DMA: stages stream global -> LDS directly (global_load_lds_dwordx4, one
@@ -190,12 +192,12 @@ __device__ __forceinline__ void scan_tiles(
   constexpr bool DMA = NBUF == 2 && CH >= 4;
   constexpr int STR = DMA ? DP : DP + 16 / (int)sizeof(CE);  // LDS row (elements)
   constexpr int BN = 128 * NCB;                   // rows per tile
-  constexpr int CPT = DMA ? 1 : (BC * CH + SCAN_THREADS - 1) / SCAN_THREADS;
+  constexpr int CPT = DMA ? 1 : (NP * BC * CH + SCAN_THREADS - 1) / SCAN_THREADS;
   // one LDS object per stage buffer: with the buffer known at compile time
   // the compiler can tell that reads of the current stage do not alias the
   // LDS DMA filling the next one, and does not wait for that DMA
-  __shared__ __attribute__((aligned(16))) CE lds_c0[BC * STR];
-  __shared__ __attribute__((aligned(16))) CE lds_c1[NBUF == 2 ? BC * STR : 1];
+  __shared__ __attribute__((aligned(16))) CE lds_c0[NP * BC * STR];
+  __shared__ __attribute__((aligned(16))) CE lds_c1[NBUF == 2 ? NP * BC * STR : 1];
   __shared__ float lds_nc[NBUF][BC];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mode0[HET ? BC * MAX_CAT : 1];
   __shared__ __attribute__((aligned(16))) uint32_t lds_mode1[HET && NBUF == 2 ? BC * MAX_CAT : 1];
@@ -225,10 +227,12 @@ __device__ __forceinline__ void scan_tiles(
 
   const int64_t count = rows ? (int64_t)*rows_count : n_rows;
   const double cm = (double)*cmax_p;
-  const float sc = M::SPLIT ? M::scale_of(*cabs_p) : 1.0f;
+  const float sc = M::SCALED ? *scale_p : 1.0f;
+  const float m2s = -2.0f / (sc * sc);  // power of two: exact rescaling
   // T2 starts every accumulator at -|c_j|^2 / 2, so acc = x.c - |c_j|^2 / 2
-  // and v_j = m2s * acc
-  const float m2s = -2.0f, nc_mul = T2 ? -0.5f : 1.0f;
+  // and v_j = m2s * acc (bf16 only: no scale)
+  static_assert(!(T2 && M::SCALED), "accumulators start unscaled");
+  const float nc_mul = T2 ? -0.5f : 1.0f;
   // padded centroids (|c|^2 = +inf) start T2 accumulators at -FLT_MAX / 4:
   // far below any real value, and finite even after the heterogeneous
   // epilogue doubles it (an infinity would turn into a NaN once the index
@@ -237,7 +241,11 @@ __device__ __forceinline__ void scan_tiles(
   const bool vec4 = ((d & 3) == 0) && ((ldx & 3) == 0);
   const double het_max = HET ? het.gamma * het.n_cat : 0.0;
 
-  // stage loading: registers <- global, LDS <- registers
+  // stage loading: registers <- global, LDS <- registers; with DMA, groups of
+  // 64 chunks, GW per wave
+  constexpr int NG = NP * BC * CH / 64, GW = (NG + 3) / 4;
+  static_assert(!DMA || BC * CH % 64 == 0, "a group lies in one plane");
+  const int64_t plane = (int64_t)k_pad * DP;
   constexpr int MPT = HET ? (BC * MAX_CAT + SCAN_THREADS - 1) / SCAN_THREADS : 1;
   uint4 stg[CPT];
   float stg_nc = 0.f;
@@ -245,10 +253,10 @@ __device__ __forceinline__ void scan_tiles(
 #define GEEK_LOAD_REGS(C0)                                                                                 \
   do {                                                                                                     \
     _Pragma("unroll") for (int u = 0; u < CPT; ++u) {                                                     \
-      const int q = min(tid + u * SCAN_THREADS, BC * CH - 1); /* clamped: always in bounds */        \
-      const int r = q / CH, c = q % CH;                                                                    \
-      stg[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(cl + (int64_t)((C0) + r) * DP) + \
-                                               c * 16);                                                    \
+      const int q = min(tid + u * SCAN_THREADS, NP * BC * CH - 1); /* clamped: always in bounds */        \
+      const int z = q / (BC * CH), r = q / CH % BC, c = q % CH;                                            \
+      stg[u] = *reinterpret_cast<const uint4*>(                                                            \
+          reinterpret_cast<const char*>(cl + z * plane + (int64_t)((C0) + r) * DP) + c * 16);              \
     }                                                                                                      \
     stg_nc = nc[(C0) + (tid & (BC - 1))];                                                             \
     if constexpr (HET) {                                                                                   \
@@ -265,8 +273,8 @@ __device__ __forceinline__ void scan_tiles(
   do {                                                                                                     \
     _Pragma("unroll") for (int u = 0; u < CPT; ++u) {                                                     \
       const int q = tid + u * SCAN_THREADS;                                                                \
-      if (q < BC * CH) {                                                                              \
-        const int r = q / CH, c = q % CH;                                                                  \
+      if (q < NP * BC * CH) {                                                                              \
+        const int r = q / CH, c = q % CH; /* rows of the planes follow each other */                       \
         *reinterpret_cast<uint4*>(reinterpret_cast<char*>(cbuf(IC<(B)>{}) + r * STR) + c * 16) = stg[u];   \
       }                                                                                                    \
     }                                                                                                      \
@@ -280,12 +288,13 @@ __device__ __forceinline__ void scan_tiles(
   } while (0)
 #define GEEK_DMA_STAGE(C0, B)                                                                              \
   do {                                                                                                     \
-    _Pragma("unroll") for (int u = 0; u < BC * CH / 256; ++u) {                                           \
-      const int slot0 = w * (BC * CH / 4) + u * 64; /* wave-uniform LDS chunk */                     \
-      const int slot = slot0 + lane;                                                                       \
+    _Pragma("unroll") for (int u = 0; u < GW; ++u) {                                                      \
+      const int slot0 = (w * GW + u) * 64; /* wave-uniform LDS chunk */                                    \
+      if (NG % 4 != 0 && w * GW + u >= NG) continue; /* (wave-uniform) */                                  \
+      const int z = slot0 / (BC * CH), slot = slot0 - z * (BC * CH) + lane;                                \
       const int r = slot / CH, c = (slot % CH) ^ (r & (CH - 1));                                           \
       __builtin_amdgcn_global_load_lds(                                                                    \
-          reinterpret_cast<const char*>(cl + (int64_t)((C0) + r) * DP) + c * 16,                           \
+          reinterpret_cast<const char*>(cl + z * plane + (int64_t)((C0) + r) * DP) + c * 16,               \
           reinterpret_cast<char*>(cbuf(IC<(B)>{})) + slot0 * 16, 16, 0, 0);                               \
     }                                                                                                      \
     /* raw |c|^2 in a register, converted when lds_nc[B] is stored: a use here \
@@ -299,7 +308,6 @@ __device__ __forceinline__ void scan_tiles(
 
   for (int64_t tile = tile0; tile < tile_end && tile * BN < count; tile += tstep) {
     typename M::frag xb[NCB][S];
-    float m2[NCB];  // -2 / (the row's scale * the centroids')
     float twoeps[NCB];
     int32_t crow[NCB][HET ? MAX_CAT : 1];
     bool valid[NCB];
@@ -339,21 +347,11 @@ __device__ __forceinline__ void scan_tiles(
         finite = finite && isfinite(xv[q]);
         nrm += (double)xv[q] * (double)xv[q];
       }
-      float sx = sc;
-      if constexpr (M::SPLIT) {
-        float mx = 0.f;
 #pragma unroll
-        for (int q = 0; q < DP / 2; ++q) mx = fmaxf(mx, fabsf(xv[q]));
-        sx = M::scale_of(fmaxf(mx, __shfl_xor(mx, 32)));
-        m2[cb] = -2.0f * (1.0f / sx) * (1.0f / sc);
-      } else {
-        m2[cb] = m2s;
-      }
-#pragma unroll
-      for (int s = 0; s < S; ++s) xb[cb][s] = M::from_f32(xv + s * M::KPER, sx);
+      for (int s = 0; s < S; ++s) xb[cb][s] = M::from_f32(xv + s * M::KPER, sc);
       if (!finite) set_status(st, GEEK_ERR_NONFINITE);
       nrm += __shfl_xor(nrm, 32);
-      twoeps[cb] = two_eps<M, DP, T2, BLK>(sqrt(nrm) * (1.0 + 1e-12), cm, 1.0 / sx, 1.0 / sc, het_max);
+      twoeps[cb] = two_eps<M, DP, T2, BLK>(sqrt(nrm) * (1.0 + 1e-12), cm, 1.0 / sc, het_max);
       if constexpr (HET) {
 #pragma unroll
         for (int a = 0; a < MAX_CAT; ++a)  // zero past n_cat, as mode16
@@ -459,9 +457,9 @@ __device__ __forceinline__ void scan_tiles(
       // block's loaded while this block's epilogue runs (modes with at most
       // eight K steps per block of one register quad; float32's pieces are
       // read step by step)
-      constexpr bool PF = S <= 8 && !M::SPLIT;
+      constexpr bool PF = S <= 8 && NP == 1;
       auto afrag_rb = [&](int rb, int s) -> typename M::frag {
-        if constexpr (!M::SPLIT) {
+        if constexpr (NP == 1) {
         const int R = rb * 32 + p;
         if constexpr (DMA) {
           const char* rowp = reinterpret_cast<const char*>(cbuf(IC<cur>{})) + R * CH * 16;
@@ -607,15 +605,16 @@ __device__ __forceinline__ void scan_tiles(
         const int R = rb * 32 + p;
         const char* rowp = reinterpret_cast<const char*>(cbuf(IC<cur>{})) + R * CH * 16;
         auto afrag = [&](int s) {
-          if constexpr (M::SPLIT) {
+          if constexpr (NP > 1) {
             typename M::frag f;
-            if constexpr (DMA) {
-              const int c = (h * (DP / 2) + s * M::KPER) / 4;  // 16-byte chunk of hi; lo follows
-              f.hi = *reinterpret_cast<const f16x8*>(rowp + ((c ^ (R & (CH - 1))) << 4));
-              f.lo = *reinterpret_cast<const f16x8*>(rowp + (((c + 1) ^ (R & (CH - 1))) << 4));
-            } else {
-              f.hi = *reinterpret_cast<const f16x8*>(ap + s * M::KPER);
-              f.lo = *reinterpret_cast<const f16x8*>(ap + s * M::KPER + 4);
+#pragma unroll
+            for (int z = 0; z < NP; ++z) {
+              if constexpr (DMA) {
+                const int c = (h * (DP / 2) + s * M::KPER) * (int)sizeof(CE) / 16;
+                f.p[z] = *reinterpret_cast<const bf16x8*>(rowp + z * (BC * CH * 16) + ((c ^ (R & (CH - 1))) << 4));
+              } else {
+                f.p[z] = *reinterpret_cast<const bf16x8*>(ap + z * (BC * STR) + s * M::KPER);
+              }
             }
             return f;
           } else if constexpr (DMA) {
@@ -625,8 +624,8 @@ __device__ __forceinline__ void scan_tiles(
             return M::load_lds(ap + s * M::KPER);
           }
         };
-        if constexpr (M::SPLIT && BLK) {
-          // blocks of 16 products in fresh accumulators, the small products
+        if constexpr (NP > 1 && BLK && DP > 32) {
+          // blocks of 16 attributes in fresh accumulators, the small products
           // first, then added to the running sums (see two_eps)
           static_assert(M::KB == 2 * M::KPER, "one step per block");
 #pragma unroll
@@ -634,15 +633,14 @@ __device__ __forceinline__ void scan_tiles(
             const typename M::frag a = afrag(s);
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
-              f32x16 blk = M::mfma(a.lo, xb[cb][s].hi, f32x16{});
-              blk = M::mfma(a.hi, xb[cb][s].lo, blk);
-              blk = M::mfma(a.hi, xb[cb][s].hi, blk);
+              const f32x16 sum = M::mfma(a.p[0], xb[cb][s].p[0], M::small(a, xb[cb][s], f32x16{}));
 #pragma unroll
-              for (int r = 0; r < 16; ++r) acc[cb][r] += blk[r];
+              for (int r = 0; r < 16; ++r) acc[cb][r] += sum[r];
             }
           }
-        } else if constexpr (M::SPLIT) {
-          // the small products in a chain of their own, added last
+        } else if constexpr (NP > 1) {
+          // the small products in a chain of their own, added last (up to 32
+          // attributes in blocked sums too: two blocks have no rounding to spare)
           f32x16 low[NCB];
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) low[cb] = f32x16{};
@@ -650,11 +648,16 @@ __device__ __forceinline__ void scan_tiles(
           for (int s = 0; s < S; ++s) {
             const typename M::frag a = afrag(s);
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) low[cb] = M::mfma(a.lo, xb[cb][s].hi, low[cb]);
+            for (int cb = 0; cb < NCB; ++cb) {
+              low[cb] = M::small(a, xb[cb][s], low[cb]);
+              if constexpr (BLK) {
+                const f32x16 sum = M::mfma(a.p[0], xb[cb][s].p[0], f32x16{});
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) acc[cb] = M::mfma(a.hi, xb[cb][s].hi, acc[cb]);
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) low[cb] = M::mfma(a.hi, xb[cb][s].lo, low[cb]);
+                for (int r = 0; r < 16; ++r) acc[cb][r] += sum[r];
+              } else {
+                acc[cb] = M::mfma(a.p[0], xb[cb][s].p[0], acc[cb]);
+              }
+            }
           }
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb)
@@ -703,7 +706,7 @@ __device__ __forceinline__ void scan_tiles(
           float v[16];
           float vmin = INFINITY;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) v[r] = __builtin_fmaf(m2[cb], acc[cb][r], ncv[r]);
+          for (int r = 0; r < 16; ++r) v[r] = __builtin_fmaf(m2s, acc[cb][r], ncv[r]);
           if constexpr (HET) {
             int mm[16];
             count_mismatches(cb, jb, mm);
@@ -870,7 +873,7 @@ struct ScanJob {
   const void* cl;
   const float* nc;
   const float* cmax;
-  const float* cabs;
+  const float* scale;
   int32_t* rec;
   int64_t tile_begin;  // first global tile of this job
   int d, k, k_pad, pad0;
@@ -907,7 +910,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_batch(const ScanJob* __re
     const int64_t tile = gt - J.tile_begin;
     scan_tiles<M, DP, false, NCB, NBUF, T2, false>(J.X, J.ldx, J.d, J.n, nullptr, nullptr,
                                             static_cast<const typename M::ce*>(J.cl), J.nc, J.k_pad, J.cmax,
-                                            J.cabs, none, J.k, J.rec, st, tile, tile + 1, 1);
+                                            J.scale, none, J.k, J.rec, st, tile, tile + 1, 1);
   }
 }
 
