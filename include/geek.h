@@ -252,11 +252,12 @@ typedef struct geek_silk_job {
  *   in float64 as: for t = 0..d-1, delta = x_it - c_jt, acc += delta*delta
  *   (each operation rounded, no fused multiply-add); lowest j on ties.
  *   The matrix cores compute an approximate D~ = |x|^2 - 2 x.c + |c|^2 in
- *   `precision` (FP32: from three bf16 pieces per value, exact; FP8 runs the bf16
- *   pass, which is as fast and settles more rows); every j whose D~ lies within a rigorous per-row error bound
+ *   `precision` (FP32: from three bf16 pieces per value, which hold all its
+ *   bits); every j whose D~ lies within a rigorous per-row error bound
  *   of the row minimum is a candidate.  Rows with one candidate (BF16, FP8) or
  *   at most 8 (FP32) have their candidates re-evaluated with the float64
- *   formula above; the other rows are rescanned in FP32 keeping up to 32
+ *   formula above; the other rows are rescanned, after FP8 (e4m3 products) in
+ *   BF16 and those it leaves, as after BF16, in FP32 keeping up to 32
  *   candidates, and rows with still more are evaluated in float64 against
  *   every seed, so the assignment is exact.
  * GEEK_METRIC_SIG: modes mode_j[f] = most frequent sig value of the members

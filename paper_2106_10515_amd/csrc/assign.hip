@@ -4,17 +4,17 @@
 //   k_centroids   float64 centroids, one thread per (seed, dim), members summed
 //                 in ascending order one rounding at a time (exact parity),
 //                 their values loaded 32 at a time.
-//   k_cprep       centroid copies for the matrix cores (three bf16 pieces),
+//   k_cprep       centroid copies for the matrix cores (three bf16 pieces, e4m3),
 //                 |c|^2 and max |c| for the error bound.
 //   k_scan<M,DP>  matrix-core tile |x|^2 - 2 x.c + |c|^2 over all centroids for
 //                 a block of rows.  Float32: per row it keeps every centroid
 //                 whose approximate distance lies within 2*eps_i of the
 //                 running minimum (eps_i a rigorous bound of the approximation
 //                 error), up to TCAND candidates (TCAND32 in the rescan of
-//                 ambiguous rows).  The BF16 first pass keeps only the best
-//                 and second-best values (branch-free); a row is settled when
-//                 the runner-up lies beyond 2*eps_i, else it is rescanned in
-//                 float32.
+//                 ambiguous rows).  The BF16 and FP8 (e4m3) first passes keep
+//                 only the best and second-best values (branch-free); a row is
+//                 settled when the runner-up lies beyond 2*eps_i, else it is
+//                 rescanned: after FP8 in BF16 the same way, then in float32.
 //   k_finalize    float64 distance (the reference formula, same operation
 //                 order) for each candidate; lowest index wins exact ties.
 //                 Rows whose candidate window overflowed are escalated.
@@ -218,15 +218,46 @@ static bool centroids_transposed(const geek_assign_job& J) {
 }
 static int64_t members_pad(const geek_assign_job& J) { return (J.n_members + 3) / 4 * 4; }
 
+// Largest |value| of a float32 matrix and of the centroids (FP8 scaling).
+template <class T>
+__global__ void k_absmax(const T* __restrict__ X, int64_t ldx, int64_t n, int d, float* __restrict__ out) {
+  const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  float m = 0.f;
+  for (int64_t e = g; e < n * d; e += (int64_t)gridDim.x * blockDim.x) {
+    const float v = fabsf((float)X[(e / d) * ldx + (e % d)]);
+    if (v > m) m = v;  // NaN compares false and is ignored here
+  }
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) == 0 && m > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomic_max_nonneg(out, m);
+}
+
+// scale = 2^floor(log2(224 / max)), so scaled values stay inside every
+// e4m3 variant's normal range; 1 when everything is zero.
+__global__ void k_fp8_scale(const float* __restrict__ mx, const float* __restrict__ mc, float* __restrict__ scale) {
+  if (blockIdx.x || threadIdx.x) return;
+  const float m = fmaxf(*mx, *mc);
+  // 2^e with max |value| * 2^e in [112, 224]; e is clamped at 60 for tiny
+  // data (the absolute error term covers it); data too large for a safe
+  // 2^e gets scale 0, which makes every row's bound infinite (escalation)
+  if (!(m > 0.f)) {
+    *scale = 1.0f;
+    return;
+  }
+  const float e = floorf(log2f(224.0f / m));
+  *scale = e < -60.f ? 0.0f : exp2f(fminf(e, 60.f));
+}
+
 // Matrix-core input copies of the centroids, zero-padded to [k_pad][DP]: the
 // three float32 pieces in planes, the first of which is the bf16 copy of a bf16
-// first pass.  A thread
+// first pass, and with `cl8` the e4m3 copy of an FP8 first pass.  A thread
 // takes eight attributes of a centroid, the DP / 8 threads of a centroid are
 // neighbours in a wavefront (a thread per centroid, walking its row, took 7 us
 // at k = 10 and one launch per copy).  Padded rows get |c|^2 = +inf so they
 // never enter a window.  |c|^2 may be summed in any order (two_eps).
 __global__ __launch_bounds__(256) void k_cprep(const double* __restrict__ C, int k, int d, int k_pad, int DP,
-                                               __bf16* __restrict__ cl, float* __restrict__ nc,
+                                               __bf16* __restrict__ cl, uint8_t* __restrict__ cl8,
+                                               const float* __restrict__ scale_p, float* __restrict__ nc,
                                                float* __restrict__ cmax, const uint32_t* __restrict__ kdev) {
   const int G = DP / 8;  // 4, 8, 16 or 32: all threads of a centroid are in one wavefront
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -247,6 +278,7 @@ __global__ __launch_bounds__(256) void k_cprep(const double* __restrict__ C, int
 #pragma unroll
   for (int z = 0; z < ModeF32::PIECES; ++z)
     *reinterpret_cast<bf16x8*>(cl + ((int64_t)z * k_pad + j) * DP + t) = f.p[z];
+  if (cl8) *reinterpret_cast<long*>(cl8 + (int64_t)j * DP + t) = ModeFP8::from_f32(v, *scale_p);
   if (t == 0) {
     nc[j] = real ? (float)sq : INFINITY;
     const float norm = (float)(sqrt(sq) * (1.0 + 0x1p-20));
@@ -263,7 +295,7 @@ __global__ __launch_bounds__(256) void k_cprep(const double* __restrict__ C, int
 template <class M, int DP, bool HET, int NCB, bool WIDE>
 constexpr int scan_min_blocks() {
   if (M::PIECES > 1) return !HET && !WIDE && NCB == 1 && DP <= 128 ? 2 : 1;
-  return (std::is_same<M, ModeBF16>::value && !HET && NCB == 2 && DP <= 128) ? 2 : 1;
+  return !HET && NCB == 2 && DP <= 128 ? 2 : 1;
 }
 
 template <class M, int DP, bool HET, int NCB, int NBUF, bool T2, bool WIDE, bool MARK>
@@ -386,7 +418,9 @@ __device__ void block_add2_u64(unsigned long long* dst0, unsigned long long* dst
   }
 }
 
-// Candidate windows (RECW records: the float32 first pass, the rescans): a lane per row, each lane walking its own row's candidates.
+// A lane per row, each lane walking its own row's candidates: candidate windows
+// (RECW records: the float32 first pass and rescan), and RECW_T2 records that
+// k_finalize does not take.
 __global__ __launch_bounds__(256) void k_finalize_win(const float* __restrict__ X, int64_t ldx, int d,
                            const double* __restrict__ C, int k, Het het, int64_t n_rows,
                            const uint32_t* __restrict__ rows, const uint32_t* __restrict__ rows_count,
@@ -1219,24 +1253,15 @@ size_t modes_ws(int64_t n_members, int F, int k);
 int32_t modes_compute(const uint32_t* V, int64_t ldv, int F, int64_t n, const uint32_t* so, const uint32_t* sm,
                       int k, int64_t NC, uint32_t* modes, void* ws, int32_t* st, hipStream_t s);
 
-// First passes on the bf16 matrix cores: GEEK_PREC_BF16 and GEEK_PREC_FP8.
-// e4m3 products run at the bf16 rate in the 32x32x16 form, and e4m3's error
-// window (2^-3) left most rows with more candidates than a lane's window holds,
-// so that a float32 rescan of nearly every row followed: 2 10^6 heterogeneous
-// rows, k = 1,000, hash and buckets included: 54.0 ms in e4m3, 9.5 ms now;
-// 805,748 x 115 rows, k = 1,312: 4.11 against 1.68 ms.
-static bool low_precision(const geek_assign_job& J) {
-  return J.precision == GEEK_PREC_BF16 || J.precision == GEEK_PREC_FP8;
-}
-
 struct AssignWs {
   __bf16* cl;  // the centroids' pieces (ModeF32), the first also the bf16 first pass's copy
   float* nc;
-  float* cmax;   // [0] max |c|
+  uint8_t* cl8;  // e4m3 copy for an FP8 first pass
+  float* cmax;   // [0] max |c|, [1] max |x_t|, [2] max |c_t|, [3] scale (FP8)
   int32_t* rec;
   uint32_t* esc;
   uint32_t* fb;
-  uint32_t* counts;  // [0] esc count, [1] fb count
+  uint32_t* counts;  // rows after each pass: [0] of esc, [1] of fb, [2] of esc again (FP8)
   double* part_d;    // per-split minima of the float64 full scans
   int32_t* part_j;
   unsigned long long* ctr;
@@ -1259,7 +1284,7 @@ struct AssignWs {
 
 
 static bool blocked_rescan(const geek_assign_job& J) {
-  return low_precision(J) && J.metric == GEEK_METRIC_EUCLID && J.k >= BLOCKED_K;
+  return J.precision == GEEK_PREC_BF16 && J.metric == GEEK_METRIC_EUCLID && J.k >= BLOCKED_K;
 }
 
 static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
@@ -1267,6 +1292,7 @@ static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
   const int DP = pick_dp(J.d);
   const int64_t k_pad = ((int64_t)J.k + SCAN_BC - 1) / SCAN_BC * SCAN_BC;
   out->cl = c.take<__bf16>(ModeF32::PIECES * k_pad * DP);
+  out->cl8 = c.take<uint8_t>(J.precision == GEEK_PREC_FP8 ? k_pad * DP : 16);
   out->nc = c.take<float>(k_pad);
   out->cmax = c.take<float>(4);
   out->rec = c.take<int32_t>(J.n * RECW);
@@ -1314,9 +1340,12 @@ size_t assign_euclid_ws(const geek_assign_job& J) {
 // blocks would leave one wavefront per SIMD (500,009 x 100 rows, 3,001 seeds:
 // whole call 2.20 ms with one block and two stages; 4.12 ms with float32 matrix
 // instructions).
-// The BF16 first pass keeps the best two values per row (T2); the float32
+// The BF16 and FP8 passes keep the best two values per row (T2); the float32
 // pass, which also rescans rows with several candidates, keeps the full
-// candidate window.
+// candidate window.  (An FP8 pass with windows, whose rows e4m3's rounding
+// leaves with a few candidates or many more, and float32 rescans of those: 2 10^6
+// heterogeneous rows, k = 1,000, hash and buckets included, 23.9 ms, of them
+// the pass 8.3 and the rescan 7.6; see assign_finish.)
 // Heterogeneous rows carry their categorical values in registers: one
 // column block.
 template <class M, bool HET> struct ScanShape {
@@ -1347,7 +1376,7 @@ static void launch_scan(int DP, int grid, hipStream_t s, const geek_assign_job& 
   case DPV:                                                                                            \
     hipLaunchKernelGGL((k_scan<M, DPV, HET, NCB, DPV == 256 ? NBUF256 : NBUF, T2, WIDE, MARK>), dim3(grid), dim3(SCAN_THREADS), 0, s, J.X,\
                        J.ldx, J.d, n_rows, rows, rows_count, static_cast<const CE*>(cl), nc, k_pad,  \
-                       W.cmax, W.cmax + 1, het, J.k, W.rec, st, sb);                                     \
+                       W.cmax, W.cmax + 3, het, J.k, W.rec, st, sb);                                     \
     break;
     GEEK_SCAN_CASE(32)
     GEEK_SCAN_CASE(64)
@@ -1412,8 +1441,15 @@ static int32_t assign_prep(const geek_assign_job& J, void* ws, AssignCtx& C, int
     hipLaunchKernelGGL(k_pad_modes, dim3(ceil_div((int64_t)k_pad * MAX_CAT, 256)), dim3(256), 0, s, J.modes, J.k,
                        J.n_cat, k_pad, W.mode16);
   }
+  const bool fp8 = J.precision == GEEK_PREC_FP8;
+  if (fp8) {
+    hipLaunchKernelGGL(k_absmax<float>, dim3(1024), dim3(256), 0, s, J.X, J.ldx, J.n, J.d, W.cmax + 1);
+    hipLaunchKernelGGL(k_absmax<double>, dim3(256), dim3(256), 0, s, J.centroids, (int64_t)J.d, (int64_t)J.k, J.d,
+                       W.cmax + 2);
+    hipLaunchKernelGGL(k_fp8_scale, dim3(1), dim3(1), 0, s, W.cmax + 1, W.cmax + 2, W.cmax + 3);
+  }
   hipLaunchKernelGGL(k_cprep, dim3(ceil_div((int64_t)k_pad * (DP / 8), 256)), dim3(256), 0, s, J.centroids, J.k, J.d,
-                     k_pad, DP, W.cl, W.nc, W.cmax, J.k_dev);
+                     k_pad, DP, W.cl, fp8 ? W.cl8 : nullptr, W.cmax + 3, W.nc, W.cmax, J.k_dev);
   GEEK_LAUNCH_CHECK();
   return GEEK_OK;
 }
@@ -1425,7 +1461,7 @@ static int esc_grid(int64_t n, int rows_per_group) {
 
 // The first pass of one job: every row gets a candidate record.
 static void assign_first_pass(const geek_assign_job& J, AssignCtx& C, int32_t* st, hipStream_t s) {
-  if (low_precision(J)) {
+  if (J.precision == GEEK_PREC_BF16) {
     const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeBF16>(C.het_on));
     C.marked = blocked_rescan(J);
     if (C.marked)
@@ -1433,6 +1469,9 @@ static void assign_first_pass(const geek_assign_job& J, AssignCtx& C, int32_t* s
                                       st, ScanBlocks{nullptr, 0, nullptr, C.W.thr});
     else
       scan_any<ModeBF16>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl, C.W, C.k_pad, C.het, st);
+  } else if (J.precision == GEEK_PREC_FP8) {
+    const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeFP8>(C.het_on));
+    scan_any<ModeFP8>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl8, C.W, C.k_pad, C.het, st);
   } else {
     const int grid_all = ceil_div(J.n, scan_rows_per_tile<ModeF32>(C.het_on));
     scan_any<ModeF32>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl, C.W, C.k_pad, C.het, st);
@@ -1482,7 +1521,7 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
   unsigned long long* ctr = W.ctr;
   const int fz_grid = (int)std::min<int64_t>(
       8192, std::max<int64_t>(ceil_div(J.n, 1024), std::min<int64_t>(ceil_div(J.n, 8 * FZ_ROWS), 2048)));
-  const int rstride = low_precision(J) ? RECW_T2 : RECW;
+  const int rstride = J.precision == GEEK_PREC_FP32 ? RECW : RECW_T2;
   // Eight lanes per row for the BF16 records of many wide rows, whose lines do
   // not stay in the caches between a lane's steps (whole assignment, k = 500,
   // eight lanes against one: 10^6 x 256 1.20 / 1.26 ms, 1.5 10^6 x 128 0.82 /
@@ -1494,25 +1533,37 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
   else
     hipLaunchKernelGGL(k_finalize_win, dim3((int)std::min<int64_t>(ceil_div(J.n, 256), 1024)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k,
                        C.het, J.n, nullptr, nullptr, W.rec, rstride, J.assign, C.dist, W.esc, W.counts + 0, ctr, 0);
-  // rows with several first-pass candidates: float32 rescan of those rows with
-  // a wider window (persistent grids, at most one row tile / block per group)
+  // rows with several first-pass candidates (persistent grids, at most one row
+  // tile / block per group)
   const uint32_t* esc = W.esc;
+  uint32_t *esc_n = W.counts + 0, *left = W.fb, *left_n = W.counts + 1;
+  if (J.precision == GEEK_PREC_FP8) {
+    // e4m3's window (2^-3) leaves most rows of close clusters; bf16 settles
+    // nearly all of those at a third of the float32 rescan's cost
+    scan_any<ModeBF16>(C.het_on, C.DP, esc_grid(J.n, scan_rows_per_tile<ModeBF16>(C.het_on)), s, J, 0, esc, esc_n, W.cl,
+                       W, C.k_pad, C.het, st);
+    hipLaunchKernelGGL(k_finalize_win, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k,
+                       C.het, (int64_t)0, esc, esc_n, W.rec, RECW_T2, J.assign, C.dist, left, left_n, ctr, 1);
+    esc = W.fb, esc_n = W.counts + 1;
+    left = W.esc, left_n = W.counts + 2;
+  }
+  // float32 rescan with a wider window
   ScanBlocks sb{};
   const bool blocked = C.marked;
   if (blocked) esc = blocked_marks(J, C, sb, s);
-  scan_any<ModeF32, true>(C.het_on, C.DP, esc_grid(J.n, 128), s, J, 0, esc, W.counts + 0, blocked ? W.clp : W.cl, W,
+  scan_any<ModeF32, true>(C.het_on, C.DP, esc_grid(J.n, 128), s, J, 0, esc, esc_n, blocked ? W.clp : W.cl, W,
                           C.k_pad, C.het, st, sb, blocked ? W.ncp : W.nc);
   hipLaunchKernelGGL(k_finalize_win, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids,
-                     J.k, C.het, (int64_t)0, esc, W.counts + 0, W.rec, RECW, J.assign, C.dist, W.fb, W.counts + 1,
+                     J.k, C.het, (int64_t)0, esc, esc_n, W.rec, RECW, J.assign, C.dist, left, left_n,
                      ctr, 1);
   const uint32_t* fpos = nullptr;
   if (blocked) {
     // the float64 scan visits marked groups too: its rows in the marked order
     // (k_finalize_win listed the same rows in any order)
     uint32_t *flag = W.rkey, *at = W.rkey2, *pos = esc == W.rid ? W.rid2 : W.rid;
-    hipLaunchKernelGGL(k_left_flags, dim3(1024), dim3(256), 0, s, W.counts + 0, W.rec, flag);
-    exscan_u32_dn(flag, at, J.n, W.counts + 0, W.rtmp, nullptr, s);
-    hipLaunchKernelGGL(k_left_list, dim3(1024), dim3(256), 0, s, W.counts + 0, esc, flag, at, W.fb, pos);
+    hipLaunchKernelGGL(k_left_flags, dim3(1024), dim3(256), 0, s, esc_n, W.rec, flag);
+    exscan_u32_dn(flag, at, J.n, esc_n, W.rtmp, nullptr, s);
+    hipLaunchKernelGGL(k_left_list, dim3(1024), dim3(256), 0, s, esc_n, esc, flag, at, left, pos);
     fpos = pos;
   }
   const int fb_grid = (int)std::min<int64_t>(FB_GRID, ceil_div(J.n, FB_R) * FB_SPLIT);
@@ -1520,7 +1571,7 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
 #define GEEK_FB_CASE(DPV)                                                                                  \
   case DPV:                                                                                                \
     hipLaunchKernelGGL(k_fallback64<DPV>, dim3(fb_grid), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k, \
-                       J.k_dev, C.het, W.fb, W.counts + 1, J.assign, C.dist, W.part_d, W.part_j, ctr, fpos, sb);\
+                       J.k_dev, C.het, left, left_n, J.assign, C.dist, W.part_d, W.part_j, ctr, fpos, sb);\
     break;
     GEEK_FB_CASE(32)
     GEEK_FB_CASE(64)
@@ -1528,7 +1579,7 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
     GEEK_FB_CASE(256)
 #undef GEEK_FB_CASE
   }
-  hipLaunchKernelGGL(k_fb_merge, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, W.fb, W.counts + 1, J.k, W.part_d,
+  hipLaunchKernelGGL(k_fb_merge, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, left, left_n, J.k, W.part_d,
                      W.part_j, J.assign, C.dist, ctr);
   sse_and_radius(C.dist, J.assign, J.n, J.k, J.sse, J.radius, C.het_on ? 0 : 1, W.sse_blk, true, s);
   if (J.t_done) {
@@ -1611,10 +1662,10 @@ int32_t assign_euclid_batch(const geek_assign_job* jobs, int njobs, void* ws, si
       e.X = J.X;
       e.ldx = J.ldx;
       e.n = J.n;
-      e.cl = W.cl;
+      e.cl = J0.precision == GEEK_PREC_FP8 ? static_cast<const void*>(W.cl8) : W.cl;
       e.nc = W.nc;
       e.cmax = W.cmax;
-      e.scale = W.cmax + 1;
+      e.scale = W.cmax + 3;
       e.rec = W.rec;
       e.tile_begin = total;
       e.d = J.d;

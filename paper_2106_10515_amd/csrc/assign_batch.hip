@@ -43,7 +43,7 @@ int cu_count() {
 
 template <class M, int DP, int NCB, int NBUF>
 void launch_one(dim3 grid, const ScanJob* table, int nj, int64_t total, int32_t* st, hipStream_t s) {
-  constexpr bool T2 = std::is_same<M, ModeBF16>::value;
+  constexpr bool T2 = !std::is_same<M, ModeF32>::value;
   hipLaunchKernelGGL((k_scan_batch<M, DP, NCB, NBUF, T2>), grid, dim3(SCAN_THREADS), 0, s, table, nj, total, st);
 }
 
@@ -100,8 +100,10 @@ void launch_scan_batch(int precision, int dp, const ScanJob* table, int nj, int6
   const ScanTiles t = scan_tiles_get(precision, dp);
   const int64_t want = (int64_t)t.blocks_per_cu * cu_count();
   const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(total_tiles, want)));
-  if (precision == GEEK_PREC_BF16 || precision == GEEK_PREC_FP8)  // both run bf16 products (assign.hip)
+  if (precision == GEEK_PREC_BF16)
     launch_prec<ModeBF16, GEEK_PREC_BF16>(dp, t, grid, table, nj, total_tiles, st, s);
+  else if (precision == GEEK_PREC_FP8)
+    launch_prec<ModeFP8, GEEK_PREC_FP8>(dp, t, grid, table, nj, total_tiles, st, s);
   else
     launch_prec<ModeF32, GEEK_PREC_FP32>(dp, t, grid, table, nj, total_tiles, st, s);
 }

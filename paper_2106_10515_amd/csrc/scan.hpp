@@ -17,7 +17,7 @@ using IC = std::integral_constant<int, V>;
 constexpr int TCAND = 8;       // candidates per lane window, float32 first pass
 constexpr int TCAND32 = 32;    // float32 pass (also the rescan of ambiguous rows)
 constexpr int RECW = TCAND32 + 1;  // candidate record per row: count, then ids
-constexpr int RECW_T2 = 2;         // the BF16 pass's record: 1 and the index, or -1
+constexpr int RECW_T2 = 2;         // the BF16 and FP8 passes' record: 1 and the index, or -1
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_BC = 64;   // centroids per LDS stage
 
@@ -94,6 +94,33 @@ struct ModeBF16 {
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] = (__bf16)v[e];
     return f;
+  }
+};
+
+// e4m3 inputs, scaled by a power of two into the normal range; products are
+// exact in float32.  Relative rounding 2^-3 (conservative), absolute error
+// 2^-10 per element in scaled units (half the smallest subnormal spacing of
+// either e4m3 variant).
+struct ModeFP8 {
+  static constexpr int KPER = 8;
+  static constexpr int KB = 0;
+  static constexpr int PIECES = 1;
+  static constexpr bool SCALED = true;
+  using ce = uint8_t;
+  using frag = long;
+  static constexpr double UX = 0x1p-3;
+  static constexpr double UC = 0x1p-3;
+  static constexpr double A0 = 0x1p-10, DROP = 0.0;
+  GEEK_D static f32x16 mma(frag a, frag b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a, b, c, 0, 0, 0);
+  }
+  GEEK_D static frag load_lds(const ce* p) { return *reinterpret_cast<const long*>(p); }
+  GEEK_D static frag from_f32(const float* v, float sc) {
+    int lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[0] * sc, v[1] * sc, 0, false);
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[2] * sc, v[3] * sc, lo, true);
+    int hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[4] * sc, v[5] * sc, 0, false);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[6] * sc, v[7] * sc, hi, true);
+    return (long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
   }
 };
 
@@ -229,10 +256,9 @@ __device__ __forceinline__ void scan_tiles(
   const double cm = (double)*cmax_p;
   const float sc = M::SCALED ? *scale_p : 1.0f;
   const float m2s = -2.0f / (sc * sc);  // power of two: exact rescaling
-  // T2 starts every accumulator at -|c_j|^2 / 2, so acc = x.c - |c_j|^2 / 2
-  // and v_j = m2s * acc (bf16 only: no scale)
-  static_assert(!(T2 && M::SCALED), "accumulators start unscaled");
-  const float nc_mul = T2 ? -0.5f : 1.0f;
+  // T2 starts every accumulator at -s^2 |c_j|^2 / 2 (exact power-of-two
+  // scalings), so acc = s^2 (x.c - |c_j|^2 / 2) and v_j = m2s * acc
+  const float nc_mul = T2 ? -0.5f * sc * sc : 1.0f;
   // padded centroids (|c|^2 = +inf) start T2 accumulators at -FLT_MAX / 4:
   // far below any real value, and finite even after the heterogeneous
   // epilogue doubles it (an infinity would turn into a NaN once the index
