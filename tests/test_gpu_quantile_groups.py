@@ -52,3 +52,13 @@ def test_more_rows_than_the_sample_sort_takes(t):
     X = g.normal(size=(24_600_001, 1)).astype(np.float32)
     X[::50] = 0.0
     _check(X, np.array([[1.5]], np.float32), t, np.arange(1), "rows")
+
+
+@pytest.mark.parametrize("n,t", [(1, 1), (70, 70), (257, 129), (8193, 8193), (30_011, 469), (30_011, 468), (30_016, 469),
+                                 (30_017, 469), (100_003, 50_002)])
+def test_small_buckets(n, t):
+    # buckets around 64 objects, of one and two, in tied and untied tables
+    g = np.random.default_rng(n + t)
+    X = g.normal(size=(n, 2)).astype(np.float32)
+    X[g.random(n) < 0.4, 0] = 0.0
+    _check(X, np.array([[1, 0], [0.3, 1]], np.float32), t, np.arange(2), "small buckets")
