@@ -60,7 +60,7 @@ __global__ void k_qv_prep(const float* __restrict__ A, int m, int d, int dpad, d
 // thread and both operands converted from LDS at every use).
 template <int NG>
 __global__ __launch_bounds__(QV_ROWS) void k_qv(const float* __restrict__ X, int64_t ldx, int64_t n, int d, int dpad,
-                                                const double* __restrict__ Ad, int p0,
+                                                const double* __restrict__ Ad, int p0, int m,
                                                 uint64_t* __restrict__ kv, int32_t* st) {
   __shared__ __attribute__((aligned(16))) float xs[2][QV_ROWS * QV_STR];
   const int64_t i0 = (int64_t)blockIdx.x * QV_ROWS;
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(QV_ROWS) void k_qv(const float* __restrict__ X, int
     finite = finite && isfinite(acc[u]);
     uint64_t uv = (uint64_t)__double_as_longlong(acc[u] + 0.0);  // -0 -> +0
     uv = (uv >> 63) ? ~uv : (uv | 0x8000000000000000ull);
-    kv[(int64_t)(p0 + u) * n + i] = uv;  // (kv holds whole groups of projections)
+    if (p0 + u < m) kv[(int64_t)(p0 + u) * n + i] = uv;
   }
   if (!finite) set_status(st, GEEK_ERR_NONFINITE);
 }
@@ -926,7 +926,7 @@ __global__ void k_q_offsets(int64_t n, int t, uint32_t* __restrict__ off) {
 
 struct QWs {
   double* Ad;
-  uint64_t* kv;  // [m rounded up to QV_GRP][n] value patterns of every table
+  uint64_t* kv;  // [m][n] value patterns of every table
   // sample sort, G tables at a time
   int C, S, nblk, G, ntile;
   uint64_t *smp, *spl, *rec;
@@ -943,7 +943,7 @@ static size_t carve_q(const geek_quantile_job& J, void* base, QWs& W) {
   const int64_t n = J.n;
   const int dpad = (J.d + QV_CHUNK - 1) / QV_CHUNK * QV_CHUNK;
   W.Ad = c.take<double>((size_t)((J.m + QV_GRP - 1) / QV_GRP) * QV_GRP * dpad);
-  W.kv = c.take<uint64_t>((size_t)((J.m + QV_GRP - 1) / QV_GRP) * QV_GRP * n);
+  W.kv = c.take<uint64_t>((size_t)J.m * n);
   W.C = q_cells(n);
   const bool second = (n + J.t - 1) / J.t > QS_MAX;  // the ids are sorted again by bucket
   if (W.C) {
@@ -971,15 +971,15 @@ static size_t carve_q(const geek_quantile_job& J, void* base, QWs& W) {
     W.hist = c.take<uint32_t>(g * 256 * W.ntile);
     W.digits = c.take<uint32_t>(g * 8 * 256);
   }
-  if (!W.C || second) {
+  if (!W.C) {
     W.klo = c.take<uint32_t>(n);
     W.khi = c.take<uint32_t>(n);
     W.ids = c.take<uint32_t>(n);
     W.klo2 = c.take<uint32_t>(n);
     W.khi2 = c.take<uint32_t>(n);
     W.ids2 = c.take<uint32_t>(n);
-    W.rtmp = c.take<uint32_t>(radix_tmp_words(n));
   }
+  if (!W.C || second) W.rtmp = c.take<uint32_t>(radix_tmp_words(n));
   return c.used + 256;
 }
 
@@ -991,7 +991,7 @@ size_t quantile_ws(const geek_quantile_job& J) {
 template <int NG>
 static void launch_qv(const geek_quantile_job& J, const QWs& W, int dpad, int p0, int32_t* st, hipStream_t s) {
   hipLaunchKernelGGL(k_qv<NG>, dim3(ceil_div(J.n, QV_ROWS)), dim3(QV_ROWS), 0, s, J.X, J.ldx, J.n, J.d, dpad, W.Ad, p0,
-                     W.kv, st);
+                     J.m, W.kv, st);
 }
 
 __global__ void k_q_clear(uint32_t* p) { p[threadIdx.x] = 0u; }
@@ -1104,9 +1104,11 @@ int32_t quantile_run(const geek_quantile_job& J, void* ws, int32_t* st, hipStrea
         emit(W.sid, p0, g, W.bad);
         continue;
       }
+      // in the group's records, which the ranks no longer need
+      uint32_t *a = reinterpret_cast<uint32_t*>(W.rec), *b = reinterpret_cast<uint32_t*>(W.tmp);
       for (int p = p0; p < p0 + g; ++p)
         q_sort_by_bucket(J, W, W.sid + (int64_t)(p - p0) * n, J.members + (int64_t)p * n,
-                         J.bucket_of ? J.bucket_of + (int64_t)p * n : nullptr, W.klo, W.ids, W.klo2, W.ids2, s);
+                         J.bucket_of ? J.bucket_of + (int64_t)p * n : nullptr, a, a + n, b, b + n, s);
     }
   } else {
     for (int p = 0; p < J.m; ++p) {
