@@ -1019,12 +1019,13 @@ static void q_rank_group(const geek_quantile_job& J, const QWs& W, int p0, int g
   // the listed tables: eight passes between their values and sid on one side,
   // their (unused) records and offsets on the other
   uint32_t* other = reinterpret_cast<uint32_t*>(W.tmp);
-  const int grid = (int)std::min<int64_t>(2048, (int64_t)g * W.ntile);
+  // (as many blocks as the chip holds: most calls list no table)
+  const int grid = (int)std::min<int64_t>(512, (int64_t)g * W.ntile);
   for (int pass = 0; pass < 8; ++pass) {
     const bool odd = pass & 1;
     hipLaunchKernelGGL(k_qr_hist, dim3(grid), dim3(QR_THREADS), 0, s, odd ? W.rec : kv, n, pass, W.ntile, W.state,
                        W.badlist, W.hist, W.digits);
-    hipLaunchKernelGGL(k_qr_scan, dim3(256, std::min(g, 8)), dim3(QR_THREADS), 0, s, W.hist, pass, W.ntile, W.state,
+    hipLaunchKernelGGL(k_qr_scan, dim3(256, std::min(g, 2)), dim3(QR_THREADS), 0, s, W.hist, pass, W.ntile, W.state,
                        W.badlist, W.digits);
     hipLaunchKernelGGL(k_qr_scatter, dim3(grid), dim3(QR_THREADS), 0, s, odd ? W.rec : kv, odd ? other : W.sid,
                        odd ? 2 * n : n, n, pass, W.ntile, W.state, W.badlist, W.hist, odd ? kv : W.rec,
