@@ -1153,7 +1153,11 @@ __global__ __launch_bounds__(BZ_THREADS) void k_bz_members(int64_t n, GroupOut g
 // Every object finds its key's slot (a slot holds the smallest id seen of
 // its key, any of which stands for the key in comparisons); heads in id order
 // rank the buckets, and a member's place is the number of smaller ids in its
-// bucket.
+// bucket.  Where a bucket holds more than SM_CROWD of them, that count is longer
+// than sorting all (rank, id) pairs (2,048 objects of one key: 412 us a call
+// counted, 92 us with the general path, 47 us sorted; buckets of 64: 39 counted,
+// of 100 47 either way, of 256 77 counted).
+constexpr int SM_CROWD = 96;
 constexpr int SM_MAX = 2048, SM_THREADS = 512, SM_PER = SM_MAX / SM_THREADS, SM_SLOTS = 2 * SM_MAX;
 __global__ __launch_bounds__(SM_THREADS) void k_bz_small(BzArgs a, uint32_t* __restrict__ members,
                                                          uint32_t* __restrict__ offsets,
@@ -1201,8 +1205,12 @@ __global__ __launch_bounds__(SM_THREADS) void k_bz_small(BzArgs a, uint32_t* __r
     if (i0 + e < n) atomicAdd(&fill[rank_of[head[e]]], 1u);
   __syncthreads();
   uint32_t sum = 0;
+  bool crowd = false;
 #pragma unroll
-  for (int e = 0; e < SM_PER; ++e) sum += fill[i0 + e];
+  for (int e = 0; e < SM_PER; ++e) {
+    sum += fill[i0 + e];
+    crowd = crowd || fill[i0 + e] > (uint32_t)SM_CROWD;
+  }
   uint32_t run = block_exscan(sum, nullptr, sh);
 #pragma unroll
   for (int e = 0; e < SM_PER; ++e) {
@@ -1211,10 +1219,36 @@ __global__ __launch_bounds__(SM_THREADS) void k_bz_small(BzArgs a, uint32_t* __r
     fill[i0 + e] = 0u;
   }
   if (threadIdx.x == 0) start[SM_MAX] = (uint32_t)n;
-  __syncthreads();
+  crowd = __syncthreads_or(crowd);
   uint32_t* off = offsets + (int64_t)t * (n + 1);
   for (uint32_t q = threadIdx.x; q <= nb; q += SM_THREADS) off[q] = start[q];  // start[nb] = n
   if (threadIdx.x == 0) nbuckets[t] = nb;
+  if (crowd) {  // uniform
+#pragma unroll
+    for (int e = 0; e < SM_PER; ++e) {
+      const bool in = i0 + e < n;
+      const uint32_t r = in ? rank_of[head[e]] : 0u;
+      mem[i0 + e] = in ? r * SM_MAX + (uint32_t)(i0 + e) : 0xFFFFFFFFu;
+      if (in && bucket_of) bucket_of[(int64_t)t * n + i0 + e] = r;
+    }
+    __syncthreads();
+    int P = 2;
+    while (P < n) P <<= 1;
+    for (int kk = 2; kk <= P; kk <<= 1)
+      for (int jj = kk >> 1; jj > 0; jj >>= 1) {
+        for (int q = threadIdx.x; q < P / 2; q += SM_THREADS) {
+          const int lo = 2 * q - (q & (jj - 1)), hi = lo + jj;
+          const uint32_t x = mem[lo], y = mem[hi];
+          if ((x > y) == ((lo & kk) == 0)) {
+            mem[lo] = y;
+            mem[hi] = x;
+          }
+        }
+        __syncthreads();
+      }
+    for (int q = threadIdx.x; q < n; q += SM_THREADS) members[(int64_t)t * n + q] = mem[q] & (SM_MAX - 1);
+    return;
+  }
 #pragma unroll
   for (int e = 0; e < SM_PER; ++e)
     if (i0 + e < n) {
