@@ -427,7 +427,8 @@ __global__ __launch_bounds__(256) void k_finalize_win(const float* __restrict__ 
                            const int32_t* __restrict__ rec, int rstride, int32_t* __restrict__ assign,
                            double* __restrict__ dist, uint32_t* __restrict__ esc,
                            uint32_t* __restrict__ esc_count, unsigned long long* __restrict__ ctr,
-                           int ctr_rows) {
+                           int ctr_rows, ScanBlocks sb) {
+  if (sb.flags && *sb.gate != 0u) rows = sb.rows;
   const int64_t count = rows ? (int64_t)*rows_count : n_rows;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t start = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -655,7 +656,7 @@ __global__ __launch_bounds__(256) void k_fallback64(
     __syncthreads();  // the previous item's reduction has read xs and rid
     int groups = T;
     bool listed = false;
-    if (sb.flags && sb.words <= 256) {
+    if (sb.flags && sb.words <= 256 && *sb.gate != 0u) {
       const int64_t p0 = g * FB_R, p1 = p0 + FB_R < (int64_t)count ? p0 + FB_R - 1 : (int64_t)count - 1;
       const int64_t t0 = fpos[p0] / 128, t1 = fpos[p1] / 128;
       uint32_t bits = 0u;
@@ -849,14 +850,38 @@ __global__ void k_fb_merge(const uint32_t* __restrict__ rows, const uint32_t* __
 // window (k_mark), and the float32 rescan visits the marked groups only.  The
 // marks are exact bounds; the orders decide how few there are.
 // 10^6 points, 90,343 seeds of 1,000 clusters: rescan and float64 scan 137 ms against 21 ms for
-// ordering, marking and rescanning.  Below BLOCKED_K seeds the rescan itself is
-// short, and the dozens of launches that order rows and seeds are not worth it.
+// ordering, marking and rescanning.
+// It takes BLOCKED_K seeds or more, at least BLOCKED_ROWS unsettled rows, and
+// BLOCKED_WORK (row, seed, padded attribute) products or more of those; the
+// host asks it of all rows, and launches nothing of this where even they are
+// too few, k_blocked_gate of the unsettled ones, and the kernels end at once
+// where they are too few (10^5 x 32 rows, 16,384 seeds apart, no row unsettled:
+// 0.41 ms plain, 0.59 ordered and marked, 0.48 ended at once).  Both routes, ms a call (k seeds of 64 clusters): n =
+// 100, 65,536 x 128 seeds 8.7 plain against 11.1 blocked; n = 300, 16,384 x 32
+// 1.47 / 1.92 and 65,536 x 32 4.83 / 4.77; n = 1,000, 16,384 x 32 0.91 / 1.14 and
+// 16,384 x 128 1.66 / 1.63; n = 3 10^5, 16,384 x 128 10.4 / 3.2.  Rows without
+// clusters, whose groups are all marked: n = 10^5, 16,384 x 32 0.93 / 1.18, x 128
+// 2.42 / 2.48, n = 3 10^5 x 128 6.6 / 6.1.
 constexpr int BLOCKED_K = 16384;
+constexpr int BLOCKED_ROWS = 256;
+constexpr int64_t BLOCKED_WORK = (int64_t)1 << 30;
+GEEK_HD bool blocked_pays(int64_t rows, int k, int DP) {
+  return rows >= BLOCKED_ROWS && rows * k >= BLOCKED_WORK / DP;
+}
+// gate: seeds and rows that take part, both zero if too few rows are unsettled.
+__global__ void k_blocked_gate(const uint32_t* __restrict__ count, int k, int DP, uint32_t* __restrict__ gate) {
+  if (threadIdx.x) return;
+  const bool use = blocked_pays(*count, k, DP);
+  gate[0] = use ? (uint32_t)k : 0u;
+  gate[1] = use ? *count : 0u;
+}
 constexpr int CODE_BITS = 24;
 
 // Mean over up to 1,024 seeds spread over all; one block per dimension.
-__global__ __launch_bounds__(256) void k_seed_mean(const double* __restrict__ C, int k, int d, double* __restrict__ mean) {
+__global__ __launch_bounds__(256) void k_seed_mean(const double* __restrict__ C, const uint32_t* __restrict__ gate, int k,
+                                                   int d, double* __restrict__ mean) {
   __shared__ double part[4];
+  if (!*gate) return;
   const int t = blockIdx.x, m = k < 1024 ? k : 1024;
   double a = 0.0;
   for (int q = threadIdx.x; q < m; q += 256) a += C[(int64_t)((int64_t)q * k / m) * d + t];
@@ -868,12 +893,12 @@ __global__ __launch_bounds__(256) void k_seed_mean(const double* __restrict__ C,
 
 // Code of every seed: bit b is the sign of a random +-1 combination of its
 // coordinates about the mean.  One wavefront per seed.
-__global__ __launch_bounds__(256) void k_seed_code(const double* __restrict__ C, int k, int d,
+__global__ __launch_bounds__(256) void k_seed_code(const double* __restrict__ C, const uint32_t* __restrict__ gate, int d,
                                                    const double* __restrict__ mean, uint32_t* __restrict__ key,
                                                    uint32_t* __restrict__ id) {
   const int lane = threadIdx.x & 63;
-  const int64_t j = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= k) return;
+  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (j >= (int64_t)*gate) return;
   float s[CODE_BITS];
 #pragma unroll
   for (int b = 0; b < CODE_BITS; ++b) s[b] = 0.f;
@@ -898,10 +923,12 @@ __global__ __launch_bounds__(256) void k_seed_code(const double* __restrict__ C,
 
 // Matrix-core copies in seed order `sid` (padding rows stay last), and the
 // place of every seed.  One thread per eight attributes.
-__global__ __launch_bounds__(256) void k_seed_permute(const uint32_t* __restrict__ sid, int k, int k_pad, int DP,
+__global__ __launch_bounds__(256) void k_seed_permute(const uint32_t* __restrict__ sid,
+                                                      const uint32_t* __restrict__ gate, int k, int k_pad, int DP,
                                                       const __bf16* __restrict__ cl, const float* __restrict__ nc,
                                                       __bf16* __restrict__ clp, float* __restrict__ ncp,
                                                       uint32_t* __restrict__ spos) {
+  if (!*gate) return;
   const int G = DP / 8;
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t r = gid / G;
@@ -1058,7 +1085,8 @@ __global__ void k_left_list(const uint32_t* __restrict__ count, const uint32_t* 
     }
 }
 
-__global__ void k_clear_words(uint32_t* __restrict__ p, int64_t n) {
+__global__ void k_clear_words(uint32_t* __restrict__ p, const uint32_t* __restrict__ gate, int64_t n) {
+  if (!*gate) return;
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
 }
@@ -1277,14 +1305,15 @@ struct AssignWs {
   uint32_t *skey, *sid, *skey2, *sid2, *spos;  // seeds by code
   uint32_t *rkey, *rid, *rkey2, *rid2;         // unsettled rows by their best seed's place
   __bf16* clp;  // the pieces in seed order
-  uint32_t *flags, *rtmp;
+  uint32_t *gate, *flags, *rtmp;
   int fwords;
 };
 
 
 
 static bool blocked_rescan(const geek_assign_job& J) {
-  return J.precision == GEEK_PREC_BF16 && J.metric == GEEK_METRIC_EUCLID && J.k >= BLOCKED_K;
+  return J.precision == GEEK_PREC_BF16 && J.metric == GEEK_METRIC_EUCLID && J.k >= BLOCKED_K && J.k < (1 << 26) &&
+         blocked_pays(J.n, J.k, pick_dp(J.d));
 }
 
 static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
@@ -1313,6 +1342,7 @@ static size_t carve_assign(const geek_assign_job& J, void* ws, AssignWs* out) {
     out->thr = c.take<float>(n);
     out->ncp = c.take<float>(k_pad);
     out->mean = c.take<double>(DP);
+    out->gate = c.take<uint32_t>(2);
     out->skey = c.take<uint32_t>(k);
     out->sid = c.take<uint32_t>(k);
     out->skey2 = c.take<uint32_t>(k);
@@ -1365,7 +1395,7 @@ int scan_rows_per_tile(bool het_on) {
 template <class M, bool HET, bool WIDE, bool MARK>
 static void launch_scan(int DP, int grid, hipStream_t s, const geek_assign_job& J, int64_t n_rows,
                         const uint32_t* rows, const uint32_t* rows_count, const void* cl, const AssignWs& W,
-                        int k_pad, const Het& het, int32_t* st, const ScanBlocks& sb, const float* nc) {
+                        int k_pad, const Het& het, int32_t* st, const ScanBlocks& sb) {
   using CE = typename M::ce;
   constexpr int NCB = ScanShape<M, HET>::NCB;
   constexpr bool T2 = ScanShape<M, HET>::T2;
@@ -1375,7 +1405,7 @@ static void launch_scan(int DP, int grid, hipStream_t s, const geek_assign_job& 
 #define GEEK_SCAN_CASE(DPV)                                                                            \
   case DPV:                                                                                            \
     hipLaunchKernelGGL((k_scan<M, DPV, HET, NCB, DPV == 256 ? NBUF256 : NBUF, T2, WIDE, MARK>), dim3(grid), dim3(SCAN_THREADS), 0, s, J.X,\
-                       J.ldx, J.d, n_rows, rows, rows_count, static_cast<const CE*>(cl), nc, k_pad,  \
+                       J.ldx, J.d, n_rows, rows, rows_count, static_cast<const CE*>(cl), W.nc, k_pad, \
                        W.cmax, W.cmax + 3, het, J.k, W.rec, st, sb);                                     \
     break;
     GEEK_SCAN_CASE(32)
@@ -1389,15 +1419,14 @@ static void launch_scan(int DP, int grid, hipStream_t s, const geek_assign_job& 
 template <class M, bool WIDE = false, bool MARK = false>
 static void scan_any(bool het_on, int DP, int grid, hipStream_t s, const geek_assign_job& J, int64_t n_rows,
                      const uint32_t* rows, const uint32_t* rows_count, const void* cl, const AssignWs& W,
-                     int k_pad, const Het& het, int32_t* st, const ScanBlocks& sb = {}, const float* nc = nullptr) {
-  if (!nc) nc = W.nc;
+                     int k_pad, const Het& het, int32_t* st, const ScanBlocks& sb = {}) {
   if constexpr (!MARK) {
     if (het_on) {
-      launch_scan<M, true, WIDE, false>(DP, grid, s, J, n_rows, rows, rows_count, cl, W, k_pad, het, st, sb, nc);
+      launch_scan<M, true, WIDE, false>(DP, grid, s, J, n_rows, rows, rows_count, cl, W, k_pad, het, st, sb);
       return;
     }
   }
-  launch_scan<M, false, WIDE, MARK>(DP, grid, s, J, n_rows, rows, rows_count, cl, W, k_pad, het, st, sb, nc);
+  launch_scan<M, false, WIDE, MARK>(DP, grid, s, J, n_rows, rows, rows_count, cl, W, k_pad, het, st, sb);
 }
 
 // Per-job state between the three phases of an assignment.
@@ -1466,7 +1495,7 @@ static void assign_first_pass(const geek_assign_job& J, AssignCtx& C, int32_t* s
     C.marked = blocked_rescan(J);
     if (C.marked)
       scan_any<ModeBF16, false, true>(false, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl, C.W, C.k_pad, C.het,
-                                      st, ScanBlocks{nullptr, 0, nullptr, C.W.thr});
+                                      st, ScanBlocks{nullptr, 0, nullptr, C.W.thr, nullptr, nullptr, nullptr, nullptr});
     else
       scan_any<ModeBF16>(C.het_on, C.DP, grid_all, s, J, J.n, nullptr, nullptr, C.W.cl, C.W, C.k_pad, C.het, st);
   } else if (J.precision == GEEK_PREC_FP8) {
@@ -1479,29 +1508,30 @@ static void assign_first_pass(const geek_assign_job& J, AssignCtx& C, int32_t* s
 }
 
 // Orders seeds and unsettled rows and marks the groups of seeds each 128 rows
-// need; returns the rows in their new order.
-static const uint32_t* blocked_marks(const geek_assign_job& J, const AssignCtx& C, ScanBlocks& sb, hipStream_t s) {
+// need.
+static ScanBlocks blocked_marks(const geek_assign_job& J, const AssignCtx& C, hipStream_t s) {
   const AssignWs& W = C.W;
   const int k = J.k, k_pad = C.k_pad;
-  hipLaunchKernelGGL(k_seed_mean, dim3(J.d), dim3(256), 0, s, J.centroids, k, J.d, W.mean);
-  hipLaunchKernelGGL(k_seed_code, dim3(ceil_div(k, 4)), dim3(256), 0, s, J.centroids, k, J.d, W.mean, W.skey, W.sid);
+  hipLaunchKernelGGL(k_blocked_gate, dim3(1), dim3(64), 0, s, W.counts + 0, k, C.DP, W.gate);
+  hipLaunchKernelGGL(k_seed_mean, dim3(J.d), dim3(256), 0, s, J.centroids, W.gate, k, J.d, W.mean);
+  hipLaunchKernelGGL(k_seed_code, dim3(ceil_div(k, 4)), dim3(256), 0, s, J.centroids, W.gate, J.d, W.mean, W.skey, W.sid);
   const int zero[4] = {0, 0, 0, 0}, shifts[4] = {0, 8, 16, 24};
   RsView A{{W.skey, nullptr, nullptr, nullptr}, W.sid}, B{{W.skey2, nullptr, nullptr, nullptr}, W.sid2};
-  const uint32_t* sid = radix_sort(A, B, 1, k, zero, shifts, CODE_BITS / 8, W.rtmp, s) ? W.sid2 : W.sid;
-  hipLaunchKernelGGL(k_seed_permute, dim3(ceil_div((int64_t)k_pad * (C.DP / 8), 256)), dim3(256), 0, s, sid, k, k_pad,
+  const uint32_t* sid = radix_sort_dn(A, B, 1, k, W.gate, zero, shifts, CODE_BITS / 8, W.rtmp, s) ? W.sid2 : W.sid;
+  hipLaunchKernelGGL(k_seed_permute, dim3(ceil_div((int64_t)k_pad * (C.DP / 8), 256)), dim3(256), 0, s, sid, W.gate, k, k_pad,
                      C.DP, W.cl, W.nc, W.clp, W.ncp, W.spos);
-  hipLaunchKernelGGL(k_row_keys, dim3(1024), dim3(256), 0, s, W.esc, W.counts + 0, W.rec, W.spos, W.rkey, W.rid);
+  hipLaunchKernelGGL(k_row_keys, dim3(1024), dim3(256), 0, s, W.esc, W.gate + 1, W.rec, W.spos, W.rkey, W.rid);
   int np = 1;
   while (np < 4 && (uint32_t)(k - 1) >> (8 * np)) ++np;
   RsView R{{W.rkey, nullptr, nullptr, nullptr}, W.rid}, R2{{W.rkey2, nullptr, nullptr, nullptr}, W.rid2};
   const uint32_t* rows =
-      radix_sort_dn(R, R2, 1, J.n, W.counts + 0, zero, shifts, np, W.rtmp, s) ? W.rid2 : W.rid;
+      radix_sort_dn(R, R2, 1, J.n, W.gate + 1, zero, shifts, np, W.rtmp, s) ? W.rid2 : W.rid;
   const int64_t tiles = ceil_div(J.n, 256), fw = tiles * 2 * W.fwords;
-  hipLaunchKernelGGL(k_clear_words, dim3(ceil_div(fw, 256)), dim3(256), 0, s, W.flags, fw);
+  hipLaunchKernelGGL(k_clear_words, dim3(ceil_div(fw, 256)), dim3(256), 0, s, W.flags, W.gate, fw);
   switch (C.DP) {
 #define GEEK_MARK_CASE(DPV)                                                                                          \
   case DPV:                                                                                                          \
-    hipLaunchKernelGGL(k_mark<DPV>, dim3(tiles), dim3(SCAN_THREADS), 0, s, J.X, J.ldx, J.d, rows, W.counts + 0, W.thr, \
+    hipLaunchKernelGGL(k_mark<DPV>, dim3(tiles), dim3(SCAN_THREADS), 0, s, J.X, J.ldx, J.d, rows, W.gate + 1, W.thr,   \
                        W.clp, W.ncp, k_pad, W.fwords, W.flags);                                                      \
     break;
     GEEK_MARK_CASE(32)
@@ -1510,8 +1540,7 @@ static const uint32_t* blocked_marks(const geek_assign_job& J, const AssignCtx& 
     GEEK_MARK_CASE(256)
 #undef GEEK_MARK_CASE
   }
-  sb = ScanBlocks{W.flags, W.fwords, sid, nullptr};
-  return rows;
+  return ScanBlocks{W.flags, W.fwords, sid, nullptr, W.gate, rows, W.clp, W.ncp};
 }
 
 // Float64 checks, rescans and fallbacks, SSE, radius, counters.
@@ -1532,7 +1561,7 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
                        nullptr, nullptr, W.rec, rstride, J.assign, C.dist, W.esc, W.counts + 0, ctr, 0);
   else
     hipLaunchKernelGGL(k_finalize_win, dim3((int)std::min<int64_t>(ceil_div(J.n, 256), 1024)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k,
-                       C.het, J.n, nullptr, nullptr, W.rec, rstride, J.assign, C.dist, W.esc, W.counts + 0, ctr, 0);
+                       C.het, J.n, nullptr, nullptr, W.rec, rstride, J.assign, C.dist, W.esc, W.counts + 0, ctr, 0, ScanBlocks{});
   // rows with several first-pass candidates (persistent grids, at most one row
   // tile / block per group)
   const uint32_t* esc = W.esc;
@@ -1543,27 +1572,27 @@ static void assign_finish(const geek_assign_job& J, AssignCtx& C, int32_t* st, h
     scan_any<ModeBF16>(C.het_on, C.DP, esc_grid(J.n, scan_rows_per_tile<ModeBF16>(C.het_on)), s, J, 0, esc, esc_n, W.cl,
                        W, C.k_pad, C.het, st);
     hipLaunchKernelGGL(k_finalize_win, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids, J.k,
-                       C.het, (int64_t)0, esc, esc_n, W.rec, RECW_T2, J.assign, C.dist, left, left_n, ctr, 1);
+                       C.het, (int64_t)0, esc, esc_n, W.rec, RECW_T2, J.assign, C.dist, left, left_n, ctr, 1,
+                       ScanBlocks{});
     esc = W.fb, esc_n = W.counts + 1;
     left = W.esc, left_n = W.counts + 2;
   }
   // float32 rescan with a wider window
   ScanBlocks sb{};
   const bool blocked = C.marked;
-  if (blocked) esc = blocked_marks(J, C, sb, s);
-  scan_any<ModeF32, true>(C.het_on, C.DP, esc_grid(J.n, 128), s, J, 0, esc, esc_n, blocked ? W.clp : W.cl, W,
-                          C.k_pad, C.het, st, sb, blocked ? W.ncp : W.nc);
+  if (blocked) sb = blocked_marks(J, C, s);
+  scan_any<ModeF32, true>(C.het_on, C.DP, esc_grid(J.n, 128), s, J, 0, esc, esc_n, W.cl, W, C.k_pad, C.het, st, sb);
   hipLaunchKernelGGL(k_finalize_win, dim3(esc_grid(J.n, 256)), dim3(256), 0, s, J.X, J.ldx, J.d, J.centroids,
                      J.k, C.het, (int64_t)0, esc, esc_n, W.rec, RECW, J.assign, C.dist, left, left_n,
-                     ctr, 1);
+                     ctr, 1, sb);
   const uint32_t* fpos = nullptr;
   if (blocked) {
     // the float64 scan visits marked groups too: its rows in the marked order
     // (k_finalize_win listed the same rows in any order)
-    uint32_t *flag = W.rkey, *at = W.rkey2, *pos = esc == W.rid ? W.rid2 : W.rid;
-    hipLaunchKernelGGL(k_left_flags, dim3(1024), dim3(256), 0, s, esc_n, W.rec, flag);
-    exscan_u32_dn(flag, at, J.n, esc_n, W.rtmp, nullptr, s);
-    hipLaunchKernelGGL(k_left_list, dim3(1024), dim3(256), 0, s, esc_n, esc, flag, at, left, pos);
+    uint32_t *flag = W.rkey, *at = W.rkey2, *pos = sb.rows == W.rid ? W.rid2 : W.rid;
+    hipLaunchKernelGGL(k_left_flags, dim3(1024), dim3(256), 0, s, W.gate + 1, W.rec, flag);
+    exscan_u32_dn(flag, at, J.n, W.gate + 1, W.rtmp, nullptr, s);
+    hipLaunchKernelGGL(k_left_list, dim3(1024), dim3(256), 0, s, W.gate + 1, sb.rows, flag, at, left, pos);
     fpos = pos;
   }
   const int fb_grid = (int)std::min<int64_t>(FB_GRID, ceil_div(J.n, FB_R) * FB_SPLIT);

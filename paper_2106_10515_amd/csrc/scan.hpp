@@ -195,6 +195,10 @@ struct ScanBlocks {
   int words;              // 32-bit words per tile
   const uint32_t* perm;   // seed of a permuted position
   float* thr;             // out: per unsettled row the largest candidate value
+  const uint32_t* gate;   // zero: the scan visits every seed, in the usual order
+  const uint32_t* rows;   // rows in the marked order
+  const void* cl;         // the seeds' copies and |c|^2 in the permuted order
+  const float* nc;
 };
 
 template <class M, int DP, bool HET, int NCB, int NBUF, bool T2, bool WIDE, bool MARK = false>
@@ -252,6 +256,15 @@ __device__ __forceinline__ void scan_tiles(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (scalar) for LDS DMA bases
   const int p = lane & 31, h = lane >> 5;
 
+  [[maybe_unused]] bool blocked = false;
+  if constexpr (WIDE) {
+    blocked = sb.flags && *sb.gate != 0u;
+    if (blocked) {
+      rows = sb.rows;
+      cl = static_cast<const CE*>(sb.cl);
+      nc = sb.nc;
+    }
+  }
   const int64_t count = rows ? (int64_t)*rows_count : n_rows;
   const double cm = (double)*cmax_p;
   const float sc = M::SCALED ? *scale_p : 1.0f;
@@ -415,7 +428,7 @@ __device__ __forceinline__ void scan_tiles(
     // the stage after the one at c0 (k_pad: none): with flags, the next stage
     // of a flagged group of 64 seeds
     [[maybe_unused]] const uint32_t* frow = nullptr;
-    if constexpr (WIDE) frow = sb.flags ? sb.flags + tile * sb.words : nullptr;
+    if constexpr (WIDE) frow = blocked ? sb.flags + tile * sb.words : nullptr;
     auto group_from = [&](int g) {
       int w = g >> 5;
       uint32_t bits = w < sb.words ? frow[w] & (~0u << (g & 31)) : 0u;
@@ -879,7 +892,7 @@ __device__ __forceinline__ void scan_tiles(
         } else {
           if (h == 0) rr[0] = kept + kept_o;
           const int off = h ? kept_o : 0;
-          for (int q = 0; q < kept; ++q) rr[1 + off + q] = WIDE && sb.perm ? (int)sb.perm[lj[q]] : lj[q];
+          for (int q = 0; q < kept; ++q) rr[1 + off + q] = WIDE && blocked ? (int)sb.perm[lj[q]] : lj[q];
         }
       }
     }

@@ -36,6 +36,9 @@ LARGEST = np.finfo(np.float32).max  # infinite in bf16: its products with both s
     (400, 32, 16_400, 1.0, LARGEST),
     (500, 16, 17_000, 0.1, LARGEST),
     (300, 200, 16_500, 0.2, LARGEST),
+    (2_300, 32, 16_400, 1.0, 1e25),
+    (2_300, 20, 16_400, 1.0, LARGEST),
+    (700, 100, 16_384, 1.0, 1e25),
 ])
 @pytest.mark.parametrize("prec", [1, 2])
 def test_marks_of_rows_without_a_bound(n, d, k, share, size, prec):
