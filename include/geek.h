@@ -218,7 +218,8 @@ typedef struct geek_bucketize_job {
  * Requires 1 <= T <= 128 (GEEK_ERR_UNSUPPORTED above), T * n < 2^31 and a C
  * capacity below 2^31.  The workspace grows with T * n (about 100 bytes per
  * (table, object); small jobs process several SILK tables at a time, about 70
- * bytes per (table, object) and further SILK table up to T * n = 2^23 in all)
+ * bytes per (table, object) and 4 KB or more per further SILK table, up to
+ * T * n = 2^23 in all)
  * and with the C capacity (about 50 bytes per member).
  */
 typedef struct geek_silk_job {

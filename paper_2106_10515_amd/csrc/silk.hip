@@ -43,7 +43,10 @@ constexpr int SILK_MAX_T = 128;  // transform tables the vote kernel holds in LD
 // Entries (T n) of the tables processed together.  20,000 points, 16 tables:
 // one table at a time, the 900 launches of a call set its time (4.3 ms; 32
 // tables of 10^6 points, 32 10^6 entries, are bound by their memory accesses).
-constexpr int64_t SILK_BATCH = 1 << 23;
+// Tables of fewer than SILK_TINY entries count as that many: each has 1,024 slots,
+// and a launch holds 65,535 tables (blockIdx.y).
+constexpr int64_t SILK_BATCH = 1 << 23, SILK_TINY = 512;
+static_assert(SILK_BATCH / SILK_TINY < 65536, "tables of a batch are a launch's blockIdx.y");
 
 // Device-side sizes and counters of one call.
 struct SilkState {
@@ -850,7 +853,7 @@ static size_t carve_silk(const geek_silk_job& J, void* ws, SilkWs& W) {
   uint64_t slots = 1024;
   while (slots < 2u * (uint64_t)W.Tn && slots < 0x80000000ull) slots <<= 1;
   W.ht_slots = (uint32_t)slots;
-  W.B = (int)std::max<int64_t>(1, std::min<int64_t>(J.L, SILK_BATCH / W.Tn));
+  W.B = (int)std::max<int64_t>(1, std::min<int64_t>(J.L, SILK_BATCH / std::max(W.Tn, SILK_TINY)));
   const int64_t NS = W.NS, Tn = W.Tn, Cc = W.Ccap, Cs = W.Cs;
   const int64_t B = W.B, BT = B * Tn, NBT = NS > BT ? NS : BT;
   const int64_t npairs = B * W.KPmax > Cc ? B * W.KPmax : Cc;
