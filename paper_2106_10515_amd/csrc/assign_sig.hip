@@ -49,6 +49,13 @@ GEEK_D uint32_t mode_members(const uint32_t* __restrict__ so, int64_t j, int64_t
 // position's values of the seed's members (a row's positions are contiguous)
 // into a column of LDS and compares them with each other.  64,000 members in
 // 2,000 seeds, F = 256: 0.1 ms where sorting the 1.6 10^7 items took 2.0 ms.
+// MODE_SMALL: the columns set the LDS and with it how many workgroups run.  Whole
+// calls of 20,000 rows, ms, sorted / columns of 48 / of 96: F = 256, 2,000 seeds of
+// 16 1.17 / 0.55 / 0.60, of 32 2.20 / 0.65 / 0.78, of 48 3.19 / 0.80 / 1.08, of 64
+// 4.22 / - / 1.47; ten categorical attributes, 2,000 seeds of 32 0.54 / 0.46 /
+// 0.59, of 48 0.551 / 0.548 / 0.82, of 64 0.59 / - / 1.16: at 48 the counting no
+// longer gains where few positions share a workgroup, and columns for more cost
+// the smaller seeds.
 constexpr int MODE_SMALL = 48, MODE_THREADS = 256;
 __global__ __launch_bounds__(MODE_THREADS) void k_mode_small(const uint32_t* __restrict__ V, int64_t ldv, int F,
                                                              int64_t n, const uint32_t* __restrict__ so,
