@@ -844,8 +844,8 @@ __global__ void k_fb_merge(const uint32_t* __restrict__ rows, const uint32_t* __
 // pass, and a rescan of every such row against every seed in float32 takes most
 // of the call.  The bf16 values already exclude nearly all seeds of a row: so
 // the seeds are reordered by a code that nearby seeds share (the signs of
-// CODE_BITS random projections about their mean), the rows by the place of
-// their best seed in that order, a bf16 pass over the reordered rows marks for
+// CODE_BITS random projections about their mean), the rows by the group of 64
+// places of their best seed in that order, a bf16 pass over the reordered rows marks for
 // every 128 of them the groups of 64 seeds that hold a value within some row's
 // window (k_mark), and the float32 rescan visits the marked groups only.  The
 // marks are exact bounds; the orders decide how few there are.
@@ -856,7 +856,7 @@ __global__ void k_fb_merge(const uint32_t* __restrict__ rows, const uint32_t* __
 // host asks it of all rows, and launches nothing of this where even they are
 // too few, k_blocked_gate of the unsettled ones, and the kernels end at once
 // where they are too few (10^5 x 32 rows, 16,384 seeds apart, no row unsettled:
-// 0.41 ms plain, 0.59 ordered and marked, 0.48 ended at once).  Both routes, ms a call (k seeds of 64 clusters): n =
+// 0.41 ms plain, 0.59 ordered and marked, 0.47 ended at once).  Both routes, ms a call (k seeds of 64 clusters): n =
 // 100, 65,536 x 128 seeds 8.7 plain against 11.1 blocked; n = 300, 16,384 x 32
 // 1.47 / 1.92 and 65,536 x 32 4.83 / 4.77; n = 1,000, 16,384 x 32 0.91 / 1.14 and
 // 16,384 x 128 1.66 / 1.63; n = 3 10^5, 16,384 x 128 10.4 / 3.2.  Rows without
@@ -945,17 +945,20 @@ __global__ __launch_bounds__(256) void k_seed_permute(const uint32_t* __restrict
   }
 }
 
-// Sort keys of the unsettled rows: the place of their best seed.
+// Sort keys of the unsettled rows: the group of 64 places that holds their best
+// seed; the rows' flags cleared.
 __global__ void k_row_keys(const uint32_t* __restrict__ rows, const uint32_t* __restrict__ count,
                            const int32_t* __restrict__ rec, const uint32_t* __restrict__ spos,
-                           uint32_t* __restrict__ key, uint32_t* __restrict__ id) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t c = *count;
-  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < c; q += stride) {
+                           uint32_t* __restrict__ key, uint32_t* __restrict__ id, uint32_t* __restrict__ flags,
+                           int words) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, q0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t c = *count, fw = (c + 255) / 256 * 2 * words;
+  for (int64_t q = q0; q < c; q += stride) {
     const uint32_t i = rows[q];
-    key[q] = spos[rec[(int64_t)i * RECW_T2 + 1]];
+    key[q] = spos[rec[(int64_t)i * RECW_T2 + 1]] / SCAN_BC;
     id[q] = i;
   }
+  for (int64_t q = q0; q < fw; q += stride) flags[q] = 0u;
 }
 
 // Marks for every tile of 128 rows the groups of 64 seeds in which some row has
@@ -1083,12 +1086,6 @@ __global__ void k_left_list(const uint32_t* __restrict__ count, const uint32_t* 
       left[at[q]] = rows[q];
       pos[at[q]] = (uint32_t)q;
     }
-}
-
-__global__ void k_clear_words(uint32_t* __restrict__ p, const uint32_t* __restrict__ gate, int64_t n) {
-  if (!*gate) return;
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
 }
 
 // ---------------------------------------------------------------- SSE, radius
@@ -1520,14 +1517,14 @@ static ScanBlocks blocked_marks(const geek_assign_job& J, const AssignCtx& C, hi
   const uint32_t* sid = radix_sort_dn(A, B, 1, k, W.gate, zero, shifts, CODE_BITS / 8, W.rtmp, s) ? W.sid2 : W.sid;
   hipLaunchKernelGGL(k_seed_permute, dim3(ceil_div((int64_t)k_pad * (C.DP / 8), 256)), dim3(256), 0, s, sid, W.gate, k, k_pad,
                      C.DP, W.cl, W.nc, W.clp, W.ncp, W.spos);
-  hipLaunchKernelGGL(k_row_keys, dim3(1024), dim3(256), 0, s, W.esc, W.gate + 1, W.rec, W.spos, W.rkey, W.rid);
+  hipLaunchKernelGGL(k_row_keys, dim3(1024), dim3(256), 0, s, W.esc, W.gate + 1, W.rec, W.spos, W.rkey, W.rid,
+                     W.flags, W.fwords);
   int np = 1;
-  while (np < 4 && (uint32_t)(k - 1) >> (8 * np)) ++np;
+  while (np < 4 && (uint32_t)((k - 1) / SCAN_BC) >> (8 * np)) ++np;
   RsView R{{W.rkey, nullptr, nullptr, nullptr}, W.rid}, R2{{W.rkey2, nullptr, nullptr, nullptr}, W.rid2};
   const uint32_t* rows =
       radix_sort_dn(R, R2, 1, J.n, W.gate + 1, zero, shifts, np, W.rtmp, s) ? W.rid2 : W.rid;
-  const int64_t tiles = ceil_div(J.n, 256), fw = tiles * 2 * W.fwords;
-  hipLaunchKernelGGL(k_clear_words, dim3(ceil_div(fw, 256)), dim3(256), 0, s, W.flags, W.gate, fw);
+  const int64_t tiles = ceil_div(J.n, 256);
   switch (C.DP) {
 #define GEEK_MARK_CASE(DPV)                                                                                          \
   case DPV:                                                                                                          \
