@@ -84,10 +84,10 @@ __global__ __launch_bounds__(1024) void k_gs_scan_tot(uint32_t* ctot, int nch, u
   if (threadIdx.x == 0 && total_out) *total_out = tot;
 }
 
-__global__ __launch_bounds__(GS_THREADS) void k_gs_apply(const uint32_t* __restrict__ in, int64_t n,
+__global__ __launch_bounds__(GS_THREADS) void k_gs_apply(const uint32_t* in, int64_t n,
                                                          const uint32_t* __restrict__ n_dev,
                                                          const uint32_t* __restrict__ ctot,
-                                                         uint32_t* __restrict__ out) {
+                                                         uint32_t* out) {  // in may equal out
   __shared__ uint32_t sh[17];
   n = dev_count(n, n_dev);
   if ((int64_t)blockIdx.x * GS_CHUNK >= n) return;  // uniform: the chunk lies past the count
@@ -108,11 +108,10 @@ __global__ __launch_bounds__(GS_THREADS) void k_gs_apply(const uint32_t* __restr
 }
 
 // Short arrays in one launch: one workgroup goes through the chunks in turn
-// (16,384 words take about 2 us, a launch about 5).
+// (16,384 words take about 2 us, a launch about 5).  in may equal out.
 constexpr int GS_SMALL = 2 * 1024 * GS_PER;
-__global__ __launch_bounds__(1024) void k_gs_small(const uint32_t* __restrict__ in, int64_t n,
-                                                   const uint32_t* __restrict__ n_dev, uint32_t* __restrict__ out,
-                                                   uint32_t* __restrict__ total) {
+__global__ __launch_bounds__(1024) void k_gs_small(const uint32_t* in, int64_t n, const uint32_t* __restrict__ n_dev,
+                                                   uint32_t* out, uint32_t* __restrict__ total) {
   __shared__ uint32_t sh[17];
   const int64_t cnt = dev_count(n, n_dev);
   uint32_t carry = 0;

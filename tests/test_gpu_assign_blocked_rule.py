@@ -60,3 +60,49 @@ def test_more_groups_than_the_lists_hold(n, d, k):
     X = g.normal(size=(n, d)).astype(np.float32)
     sm = g.integers(0, n, size=k).astype(np.uint32)
     _run(X, sm, np.arange(0, n, 7), "groups")
+
+
+def test_device_seed_count_batch_and_graph():
+    # the same seeds as a host count, as a device count with capacity to spare,
+    # in a batched call, and recorded in a graph whose rows change between replays
+    api = gpu_api()
+    g = np.random.default_rng(9)
+    n, d, k, cap = 2_100, 40, 16_500, 16_700
+    centers = g.uniform(-50, 50, size=(8, d))
+    sets = [torch.from_numpy((centers[g.integers(0, 8, size=n)] + g.normal(size=(n, d)) * s).astype(np.float32)).cuda()
+            for s in (1.0, 3.0, 0.01)]
+    sm = cuda(g.integers(0, n, size=cap).astype(np.uint32))
+    so = torch.arange(cap + 1, dtype=torch.int32, device="cuda")
+    kd = torch.tensor([k], dtype=torch.int32, device="cuda")
+    announce(f"assign blocked graph n={n} d={d} k={k}")
+
+    def plain(X):
+        return api.assign_euclid(X, so[:k + 1], sm[:k], k, 1)
+
+    def same(a, b):
+        for name in ("assign", "dist", "sse", "counters"):
+            assert torch.equal(a[name], b[name]), name
+
+    X = sets[0].clone()
+    ref = plain(X)
+    assert int(ref["counters"][1] + ref["counters"][2]) > 1_000
+    same(ref, api.assign_euclid(X, so, sm, cap, 1, k_dev=kd))
+    outs, _ = api.assign_euclid_batch([(X, so[:k + 1], sm[:k], k), (X, so[:11], sm[:10], 10)], 1)
+    for name in ("assign", "dist", "sse", "radius"):
+        assert torch.equal(ref[name], outs[0][name]), name
+
+    status = api.new_status("cuda")
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        api.assign_euclid(X, so, sm, cap, 1, k_dev=kd, status=status, check=False)  # grows the stream's workspace
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        rec = api.assign_euclid(X, so, sm, cap, 1, k_dev=kd, status=status, check=False)
+    for Y in sets[1:] + sets[:1]:
+        X.copy_(Y)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0
+        same(plain(X), rec)
