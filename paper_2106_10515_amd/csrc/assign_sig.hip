@@ -749,7 +749,6 @@ static bool sig_use_bits(const geek_assign_job& J) {
 }
 
 struct SigWs {
-  int64_t NI;  // mode items sorted together: members * positions of a slice
   uint32_t *val, *seg, *val2, *seg2;
   uint32_t *boff, *bcount;  // modes by sorting: first member of each seed; members, items
   uint32_t *wj, *wv, *wf, *wj2, *wv2, *wf2;
@@ -788,7 +787,6 @@ static size_t carve_sig(const geek_assign_job& J, void* ws, SigWs& W) {
   const int64_t NI = J.n_members * mode_slice(J.n_members, J.F);
   const int64_t KI = (int64_t)J.k * F;
   const int64_t NR = NI > KI ? NI : KI;
-  W.NI = NI;
   W.val = c.take<uint32_t>(NR + 1);
   W.seg = c.take<uint32_t>(NR + 1);
   W.val2 = c.take<uint32_t>(NR + 1);

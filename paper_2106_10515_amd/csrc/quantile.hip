@@ -13,7 +13,8 @@
 //             made hard go to an exact comparison sort in LDS
 //             (k_qs_cell_exact); a table with a cell beyond even that (one
 //             value shared by thousands of objects) is ranked by a stable
-//             radix sort (k_qr_*), decided on the device.
+//             radix sort of its (value, id) pairs (k_qr_*), decided on the
+//             device.
 //   buckets   every bucket's ids in ascending order: by counting the smaller ids
 //             of buckets of at most QT_MAX objects, ranked in LDS per bucket
 //             when buckets hold at most QS_MAX objects, else by a stable sort
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(QV_ROWS) void k_qv(const float* __restrict__ X, int
 // rest is the scatter's short runs and LDS latency.
 constexpr int QF_MEAN = 3000;        // objects per cell aimed at (n / cells is at most this)
 constexpr int QF_CELLS_MAX = 8192;   // cells per table (splitters and counts in LDS)
-constexpr int QF_OVER = 16;          // sample values per cell: a cell stays below 2.6 x the mean
+constexpr int QF_OVER = 16;          // sample values per cell: nearly all cells stay below 2.6 x the mean
 constexpr int QF_CHUNK = 16384;      // sample values sorted by one block
 constexpr int QF_BLK = 32768;        // objects counted and scattered by one block
 constexpr int QF_STAGE = 8192;       // records staged at a time by the scatter
