@@ -34,8 +34,8 @@ constexpr int SCAN_BC = 64;   // centroids per LDS stage
 // hold 22 of the 24 bits.  Error of a value against float64 in units of
 // 2^-24 (|x| + |c|) |c|, root mean square over 4,096 x 512 pairs of a Gaussian
 // mixture in [-50, 50]^d, float32 instructions / two float16 pieces / three bf16
-// pieces: first pass d = 8 0.51 / 0.64 / 0.42, d = 32 0.44 / 0.42 / 0.37, d = 128
-// 0.43 / 0.33 / 0.30; rescan (blocked sums) d = 16 0.44 / 0.51 / 0.38, d = 128 0.32
+// pieces: first pass d = 8 0.51 / 0.64 / 0.42, d = 32 0.44 / 0.42 / 0.33, d = 128
+// 0.43 / 0.33 / 0.30; rescan (blocked sums) d = 16 0.43 / 0.51 / 0.37, d = 128 0.32
 // / 0.32 / 0.30.
 struct ModeF32 {
   struct frag3 {
